@@ -199,7 +199,8 @@ enum CounterSlot : int {
   kCtrPairI = kMaxPasses + 8,        // sort-based pairing: non-unique items paired this round
   kCtrPairU = kMaxPasses + 9,        // sort-based pairing: unique items kept for the next round
   kCtrStage = kMaxPasses + 10,       // staged ISA writes of the last re-rank
-  kCtrCount = kMaxPasses + 11,
+  kCtrSplitOver = kMaxPasses + 11,   // a bucket of the split sort overflowed: keys unsorted
+  kCtrCount = kMaxPasses + 12,
 };
 
 }  // namespace sa

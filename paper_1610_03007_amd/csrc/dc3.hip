@@ -303,7 +303,7 @@ sa_status dc3_level(sa_ctx* c, const T* x, u64 m, u32 add, u64 max_sym, u32* sa,
                          bsym, full.kA, full.vA);
   }
   const int word_bits = 3 * bsym <= 64 ? 3 * bsym : 2 * bsym;
-  run_sort(c, full, m12, npass_for(c, word_bits), 1, 0, s);
+  run_sort(c, full, m12, npass_for(c, word_bits), 1, 0, s, true);
   RerankArgs a = single_args(m12, m12, 0, kRerankScatterIsa);
   if (3 * bsym > 64) {
     // Run names of the low word, then the high word x[p] sorted stably with
@@ -347,7 +347,7 @@ sa_status dc3_level(sa_ctx* c, const T* x, u64 m, u32 add, u64 max_sym, u32* sa,
     hipLaunchKernelGGL((dc3_pack_s0_kernel<T>), dim3(stream_grid(c, n0, 256)), dim3(256), 0, s,
                        str, n0, L.rankp, brank, full.kA, full.vA);
   }
-  run_sort(c, full, n0, npass_for(c, bsym + brank), 1, 0, s);
+  run_sort(c, full, n0, npass_for(c, bsym + brank), 1, 0, s, true);
 
   // Step 4: comparison records, merge-path splits, merge by tiles.
   const u64 ntiles = ceil_div(m, u64(kDc3Tile));
@@ -404,7 +404,9 @@ extern "C" {
 sa_status sa_build_dc3(sa_ctx* ctx, const uint8_t* d_text, uint64_t n, uint32_t* d_sa,
                        uint32_t* d_rank12, void* stream) {
   if (!ctx) return SA_EINVAL;
-  const sa_status st = build_dc3(ctx, d_text, n, d_sa, d_rank12, static_cast<hipStream_t>(stream));
+  const sa_status st = with_lsd_repeat(ctx, [&] {
+    return build_dc3(ctx, d_text, n, d_sa, d_rank12, static_cast<hipStream_t>(stream));
+  });
   settle_trace(ctx, st);
   return st;
 }

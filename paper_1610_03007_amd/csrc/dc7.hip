@@ -297,7 +297,7 @@ sa_status build_dc7(sa_ctx* c, const u8* text, u64 n, u32* d_sa, u32* d_rank, hi
     hipLaunchKernelGGL(d7_pack_sample_kernel, dim3(stream_grid(c, ms, 256)), dim3(256), 0, s, txt,
                        L, ms, full.kA, full.vA);
   }
-  run_sort(c, full, ms, npass_for(c, 63), 1, 0, s);
+  run_sort(c, full, ms, npass_for(c, 63), 1, 0, s, true);
   {
     // The re-rank's first-round form: names into `child`, the order of unique
     // ones into tmp, the others counted.
@@ -328,7 +328,7 @@ sa_status build_dc7(sa_ctx* c, const u8* text, u64 n, u32* d_sa, u32* d_rank, hi
       hipLaunchKernelGGL(d7_pack_rest_kernel, dim3(stream_grid(c, nns, 256)), dim3(256), 0, s,
                          txt, nns, A.rankp, full.kA, full.vA);
     }
-    run_sort(c, full, nns, npass_for(c, 62), 1, 0, s);
+    run_sort(c, full, nns, npass_for(c, 62), 1, 0, s, true);
   }
 
   // Step 4: records, then the merges (2 with 4, 5 with 6, those two, and the
@@ -365,8 +365,9 @@ extern "C" {
 sa_status sa_build_dc7(sa_ctx* ctx, const uint8_t* d_text, uint64_t n, uint32_t* d_sa,
                        uint32_t* d_rank_sample, void* stream) {
   if (!ctx) return SA_EINVAL;
-  const sa_status st =
-      build_dc7(ctx, d_text, n, d_sa, d_rank_sample, static_cast<hipStream_t>(stream));
+  const sa_status st = with_lsd_repeat(ctx, [&] {
+    return build_dc7(ctx, d_text, n, d_sa, d_rank_sample, static_cast<hipStream_t>(stream));
+  });
   settle_trace(ctx, st);
   return st;
 }

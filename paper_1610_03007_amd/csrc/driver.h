@@ -130,6 +130,8 @@ struct sa_ctx {
   std::string arch;         // architecture name without feature suffixes
   u32 sigma_hint = 0;       // alphabet hint of the current sa_build (0: none)
   int tuned_from_cache = 0; // 1 if the last build took its knobs from the table
+  bool force_lsd = false;   // the split sort overflowed: the repeat takes the LSD sort
+  bool split_over = false;  // set by readback() when it did
   bool trace = false;
   std::vector<TraceRec> recs;
   std::vector<hipEvent_t> event_pool;
@@ -266,9 +268,29 @@ void begin_sort(sa_ctx* c, u64 bound, const u64* dev_count, RoundCtl* rc, int np
                 hipStream_t s, u64 dense_n = 0, int log2a = 1);
 void sort_passes(sa_ctx* c, const Bufs& bf, u64 bound, int npass, int vals_present, int log_row,
                  u64 trace_count, hipStream_t s);
-// A sort of `count` pairs known on the host.
+// A sort of `count` pairs known on the host. any_order: pairs of equal keys may
+// come out in any order and no key has bits above the npass digits, so the split
+// sort may run (where split_usable()); a readback() that finds c->split_over set
+// then asks for the work to be repeated with force_lsd.
 void run_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_present, int slot,
-              hipStream_t s);
+              hipStream_t s, bool any_order = false);
+bool split_usable(const sa_ctx* c, u64 count);
+sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_present, int slot,
+                     hipStream_t s);
+// Runs a whole build; once more with the LSD sort if the split sort overflowed.
+template <typename F>
+sa_status with_lsd_repeat(sa_ctx* c, F&& build) {
+  c->split_over = false;
+  sa_status st = build();
+  if (st == SA_OK || !c->split_over) return st;
+  c->split_over = false;
+  c->recs.clear();
+  c->event_used = 0;
+  c->force_lsd = true;
+  st = build();
+  c->force_lsd = false;
+  return st;
+}
 // Re-rank of the current sort (ctl->count elements, at most `bound`).
 void run_rerank(sa_ctx* c, const Bufs& bf, const RerankArgs& args, u32* d_sa, u64 bound,
                 u64 trace_count, hipStream_t s);

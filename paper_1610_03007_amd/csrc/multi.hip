@@ -231,59 +231,65 @@ struct Engine {
     if (hipMemcpyAsync(dev, h_up, up, hipMemcpyHostToDevice, s) != hipSuccess)
       return SA_EDEVICE;
     NewList nl{d_new_t, d_new_out, d_new_chunk0, m, nchunk.back()};
-    {
-      Tracer tr(c, s, SA_KERNEL_OTHER, 0);
-      launch_fill_u64(c->counters, kCtrCount, 0, s);
-      launch_fill_u32(tab.surv, slots, 0, s);
-    }
-    if (m) {
-      {
-        Tracer tr(c, s, SA_KERNEL_OTHER, double(A0));
-        launch_multi_presence(text_arena, tab, nl, s);
-        // A compact layout's character budget ends on a digit boundary already.
-        launch_multi_codes(tab, nl, idbits, round0_shift, compact0 ? 0 : c->round0_trim,
-                           c->radix_bits, s);
-      }
-      Tracer tr(c, s, SA_KERNEL_PACK_TEXT, double(A0) * 13.0);
-      launch_multi_pack0(text_arena, tab, nl, round0_shift, c->keysA, c->valsA, s);
-    }
-    const Bufs bufs = lazy ? later : full;
-    if (active) {
-      Tracer tr(c, s, SA_KERNEL_PACK_PAIRS, double(active) * 24.0);
-      if (lazy)
-        launch_multi_pack_pairs_lazy(c->act_ti, c->act_rank, active, tab, B, idshift,
-                                     round0_shift, c->isa, c->live, text_arena, keys0, bufs.kA,
-                                     bufs.vA, s);
-      else
-        launch_multi_pack_pairs(c->act_ti, c->act_rank, active, tab, B, idshift, c->isa,
-                                c->keysA + A0, c->valsA + A0, s);
-    }
     const u64 total = A0 + active;
-    if (total) {
-      run_sort(c, bufs, total, npass_for(c, 64), 1, slot_info, s);
-      RerankArgs a{};
-      a.count = total;
-      a.n = 0;
-      a.gshift = B;  // group = (slot, rank) for texts past round 0
-      a.rshift = B;
-      a.rmask = (u64(1) << B) - 1;
-      a.idshift = m ? round0_shift : idshift;  // (equal when the round mixes)
-      a.mode = (defer_round0_isa && m) ? 0 : kRerankScatterIsa;
-      a.tbase = tab.base;
-      a.tlen = tab.len;
-      a.tround0 = tab.round0;
-      a.tstart = tab.start;
-      run_rerank(c, bufs, a, sa_arena, total, total, s);
-      last_args = a;
-      // Survivors per text; their number is read on the device.
-      Tracer tr(c, s, SA_KERNEL_OTHER, 0);
-      launch_multi_count_survivors(c->act_ti, c->counters + kCtrActive, total, tab.surv, s);
-    }
-    if (hipMemcpyAsync(h_surv, tab.surv, slots * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
-      return SA_EDEVICE;
-    if (m && hipMemcpyAsync(h_wc, tab.wc, slots * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
-      return SA_EDEVICE;
-    sa_status st = readback(c, s);  // synchronises the stream
+    // The round's kernels up to the survivor counts; again with the LSD sort if
+    // the split sort overflowed (its input is packed anew: texts, survivors and
+    // names are as they were).
+    auto enqueue = [&]() -> sa_status {
+      {
+        Tracer tr(c, s, SA_KERNEL_OTHER, 0);
+        launch_fill_u64(c->counters, kCtrCount, 0, s);
+        launch_fill_u32(tab.surv, slots, 0, s);
+      }
+      if (m) {
+        {
+          Tracer tr(c, s, SA_KERNEL_OTHER, double(A0));
+          launch_multi_presence(text_arena, tab, nl, s);
+          // A compact layout's character budget ends on a digit boundary already.
+          launch_multi_codes(tab, nl, idbits, round0_shift, compact0 ? 0 : c->round0_trim,
+                             c->radix_bits, s);
+        }
+        Tracer tr(c, s, SA_KERNEL_PACK_TEXT, double(A0) * 13.0);
+        launch_multi_pack0(text_arena, tab, nl, round0_shift, c->keysA, c->valsA, s);
+      }
+      const Bufs bufs = lazy ? later : full;
+      if (active) {
+        Tracer tr(c, s, SA_KERNEL_PACK_PAIRS, double(active) * 24.0);
+        if (lazy)
+          launch_multi_pack_pairs_lazy(c->act_ti, c->act_rank, active, tab, B, idshift,
+                                       round0_shift, c->isa, c->live, text_arena, keys0, bufs.kA,
+                                       bufs.vA, s);
+        else
+          launch_multi_pack_pairs(c->act_ti, c->act_rank, active, tab, B, idshift, c->isa,
+                                  c->keysA + A0, c->valsA + A0, s);
+      }
+      if (total) {
+        run_sort(c, bufs, total, npass_for(c, 64), 1, slot_info, s, true);
+        RerankArgs a{};
+        a.count = total;
+        a.n = 0;
+        a.gshift = B;  // group = (slot, rank) for texts past round 0
+        a.rshift = B;
+        a.rmask = (u64(1) << B) - 1;
+        a.idshift = m ? round0_shift : idshift;  // (equal when the round mixes)
+        a.mode = (defer_round0_isa && m) ? 0 : kRerankScatterIsa;
+        a.tbase = tab.base;
+        a.tlen = tab.len;
+        a.tround0 = tab.round0;
+        a.tstart = tab.start;
+        run_rerank(c, bufs, a, sa_arena, total, total, s);
+        last_args = a;
+        // Survivors per text; their number is read on the device.
+        Tracer tr(c, s, SA_KERNEL_OTHER, 0);
+        launch_multi_count_survivors(c->act_ti, c->counters + kCtrActive, total, tab.surv, s);
+      }
+      if (hipMemcpyAsync(h_surv, tab.surv, slots * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
+        return SA_EDEVICE;
+      if (m && hipMemcpyAsync(h_wc, tab.wc, slots * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
+        return SA_EDEVICE;
+      return readback(c, s);  // synchronises the stream
+    };
+    const sa_status st = with_lsd_repeat(c, enqueue);
     if (st != SA_OK) return st;
     const u64 next_active = total ? c->h_counters[kCtrActive] : 0;
     // Advance every text that took part.
@@ -372,7 +378,8 @@ sa_status build_batch_impl(sa_ctx* c, const u8* text, const u64* h_off, u32 T, u
   if (N >= (u64(1) << 40)) return SA_ETOOBIG;
   if (N == 0) return SA_OK;
   if (!text || !d_sa) return SA_EINVAL;
-  if (T == 1) return build_rounds(c, text, N, 0, d_sa, nullptr, s);
+  if (T == 1)
+    return with_lsd_repeat(c, [&] { return build_rounds(c, text, N, 0, d_sa, nullptr, s); });
   const int idbits = bits_of(u64(T) - 1);
   const int B = bits_of(max_n);
   if (idbits + 2 * B > 64) return SA_ETOOBIG;

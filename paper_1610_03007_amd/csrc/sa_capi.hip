@@ -236,7 +236,11 @@ void sort_passes(sa_ctx* c, const Bufs& bf, u64 bound, int npass, int vals_prese
 }
 
 void run_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_present, int slot,
-              hipStream_t s) {
+              hipStream_t s, bool any_order) {
+  // (The split sort's kernels are checked for launch errors by the readback.)
+  if (any_order && split_usable(c, count) &&
+      split_sort(c, bf, count, npass, vals_present, slot, s) == SA_OK)
+    return;
   begin_sort(c, count, nullptr, nullptr, npass, true, s);
   sort_passes(c, bf, count, npass, vals_present, slot, count, s);
 }
@@ -294,6 +298,10 @@ sa_status readback(sa_ctx* c, hipStream_t s) {
     return SA_EDEVICE;
   if (hipStreamSynchronize(s) != hipSuccess) return SA_EDEVICE;
   if (hipGetLastError() != hipSuccess) return SA_EDEVICE;
+  if (c->h_counters[kCtrSplitOver] != 0) {
+    c->split_over = true;
+    return SA_EDEVICE;
+  }
   if (c->h_counters[kCtrError] != 0) return SA_EDEVICE;
   return SA_OK;
 }
@@ -492,7 +500,7 @@ sa_status build_rounds(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_
     launch_pack_text(text, n, c->code, c->counters, c->keysA, s);
   }
   const int npass0 = npass_for(c, 64);
-  run_sort(c, full, n, npass0, 0, 0, s);
+  run_sort(c, full, n, npass0, 0, 0, s, true);
   run_rerank(c, full, single_args(n, n, 0, 0), d_sa, n, n, s);
   st = readback(c, s);
   if (st != SA_OK) return st;
@@ -629,7 +637,8 @@ void settle_trace(sa_ctx* c, sa_status st) {
 sa_status build_impl(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_sa, u32* d_isa,
                      hipStream_t s) {
   if (!c) return SA_EINVAL;
-  sa_status st = build_rounds(c, text, n, max_rounds, d_sa, d_isa, s);
+  sa_status st = with_lsd_repeat(
+      c, [&] { return build_rounds(c, text, n, max_rounds, d_sa, d_isa, s); });
   settle_trace(c, st);
   return st;
 }

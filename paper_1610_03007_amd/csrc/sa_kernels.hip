@@ -1280,6 +1280,7 @@ void rerank_compact_kernel(
   static_assert(R <= 16, "flag bits of a lane: heads in 0..15, uniques in 16..31");
   const u64 count = ctl->count;
   const int mode = a.mode;
+  if (counters[kCtrSplitOver]) return;  // the keys are not sorted: the host repeats the sort
   __shared__ u32 s_wh[NW], s_wg[NW], s_ws[NW];
   __shared__ u64 s_prefix[2];
   // Survivors of the workgroup's tiles, gathered here and written out in one

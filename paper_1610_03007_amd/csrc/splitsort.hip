@@ -1,0 +1,1113 @@
+// Split sort: (key, value) pairs ordered by 64-bit key in at most two scattering
+// sweeps and one pass of sorts in LDS, for sorts whose order among equal keys
+// does not matter (the re-rank gives equal keys one name whatever their order).
+//
+// The LSD sort moves every pair once per key digit (7 or 8 sweeps of 24 bytes a
+// pair for a round-0 key). Here the number of sweeps depends on the count only:
+//
+//   1. A stratified sample of the keys, sorted, gives F - 1 splitters (F a power
+//      of two, count / 1024 <= F, at most 2^20): bucket b holds the keys in
+//      (splitter[b - 1], splitter[b]]. Whatever the keys' distribution, a bucket
+//      holds about count / F pairs. A key that the sample holds several times
+//      fills several splitters; all its pairs go to the bucket that begins with
+//      the second of them, which holds nothing else (an equality bucket: it is
+//      sorted already, however large).
+//   2. Up to kSplitMaxD buckets: one sweep scatters the pairs into them. Above:
+//      F = D1 * D2, one sweep into D1 groups of D2 neighbouring buckets, one
+//      inside each group.
+//   3. Every bucket is sorted in LDS by one workgroup: again a sample (128 keys),
+//      a scatter into 128 parts of about eight pairs, and each pair's place in its
+//      part by counting the smaller keys.
+//
+// Measured on MI355X for the 2^28 round-0 keys of a Markov text (7 varying bytes):
+// 8.0 ms (sample 0.4, histograms 0.5 + 0.5, sweeps 1.8 + 1.6, LDS 3.3) against
+// 12.1 ms for seven LSD sweeps of 1.68 ms and their histogram. For 2^20 DNA keys
+// 0.11 ms against 0.22, for 2^16 keys 0.05 against 0.11.
+//
+// Bucket counts come from a histogram before each sweep; a tile reserves its
+// part of each bucket with one atomic add per bucket, so the order among equal
+// keys (and inside a bucket before step 3) varies from run to run.
+//
+// A bucket that is no equality bucket and is larger than LDS holds
+// (kSplitCap pairs, about four times the mean) raises kCtrSplitOver: the keys
+// are then unsorted, the re-rank returns at once, and the host repeats the work
+// with the LSD sort. With `over` samples per bucket the size of a bucket follows
+// a Gamma(over) law; over = 12 (8 up to 1024 buckets, 4 where their mean is at
+// most 512) puts the chance of an overflow below 1e-3 at the largest count. The sample positions are a fixed
+// function of the count, so a given input always behaves alike.
+
+#include <type_traits>
+
+#include "driver.h"
+
+namespace sa {
+
+namespace {
+
+constexpr int kSplitBlock = 512;
+constexpr int kSplitMaxLogD = 10;
+constexpr u32 kSplitMaxD = 1u << kSplitMaxLogD;
+constexpr u32 kSplitCap = 3840;       // pairs of a bucket sorted in LDS
+constexpr u32 kSplitRankMax = 8192;   // samples sorted by counting
+constexpr u32 kSplitXcds = 8;
+constexpr int kPosBits = 12;          // a place in a bucket
+static_assert(kSplitCap <= 1u << kPosBits, "places");
+constexpr int kSearchGang = 4;        // searches of a thread side by side
+
+__device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
+
+__device__ inline u32 wave_inclusive_sum(u32 v) {
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const u32 t = __shfl_up(v, off, kWave);
+    if (lane_id() >= off) v += t;
+  }
+  return v;
+}
+
+// Exclusive sum over the workgroup's kSplitBlock threads (every thread calls).
+__device__ inline u32 block_exclusive_sum(u32 v, u32* s_w) {
+  const int wave = threadIdx.x / kWave;
+  const u32 inc = wave_inclusive_sum(v);
+  if (lane_id() == kWave - 1) s_w[wave] = inc;
+  __syncthreads();
+  u32 off = 0;
+#pragma unroll
+  for (int w = 0; w < kSplitBlock / kWave; ++w)
+    if (w < wave) off += s_w[w];
+  __syncthreads();
+  return off + inc - v;
+}
+
+// Splitters sp[0 .. D - 2] (ascending, D = 2^logd) sit in LDS as a search tree in
+// breadth-first order: node k has the children 2k and 2k + 1. The nodes of one
+// depth are neighbours, so the lanes' reads of a step spread over the banks (in
+// sorted order, those of the first steps are multiples of a large power of two
+// apart and fall on one bank).
+__device__ inline u32 tree_node(u32 i, int logd) {
+  const u32 t = u32(__builtin_ctz(i + 1));
+  return (1u << (logd - 1 - int(t))) + ((i + 1) >> (t + 1));
+}
+
+// Bucket of every key: the number of splitters below it, or the next one when
+// the key equals a splitter that fills the next splitter too (bit b of fl). The
+// searches of a thread's items go side by side, so that their LDS reads overlap
+// (one after the other, the reads' latency alone took longer than the sweep's
+// memory traffic).
+template <int ITEMS>
+__device__ inline void buckets_of(const u64* tree, const u32* fl, int logd, const u64* key,
+                                  u32 (&b)[ITEMS]) {
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) b[j] = 1;
+  for (int d = 0; d < logd; ++d) {
+    u64 x[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) x[j] = tree[b[j]];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) b[j] = 2 * b[j] + (x[j] < key[j] ? 1u : 0u);
+  }
+  const u32 n = 1u << logd;
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    b[j] -= n;
+    if ((fl[b[j] >> 5] >> (b[j] & 31u)) & 1u)
+      if (tree[tree_node(b[j], logd)] == key[j]) ++b[j];
+  }
+}
+
+__device__ inline void flag(u64* counters, u64 bits) {
+  atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrError), (unsigned long long)bits);
+}
+
+__device__ inline u32 mix32(u32 x) {
+  x ^= x >> 16;
+  x *= 0x7feb352du;
+  x ^= x >> 15;
+  x *= 0x846ca68bu;
+  x ^= x >> 16;
+  return x;
+}
+
+}  // namespace
+
+// Shape of one split sort, from its count alone (host).
+struct SplitShape {
+  u32 count;
+  int log1, log2;     // buckets of the first and the second sweep (log2; 0, 0: LDS only)
+  u32 over;           // samples per bucket
+  u32 samples;        // F * over
+  u32 tile;           // pairs per sweep workgroup
+  u32 tiles;          // of the first sweep
+  u32 groups;         // tile groups of the first sweep, one per XCD (or one)
+  u32 per;            // tiles per group
+  u32 nb() const { return 1u << (log1 + log2); }
+};
+
+// Device arrays of one split sort.
+struct SplitArrays {
+  u64* splitters;  // [F], ascending, the last all ones
+  u64* top;        // [D1] splitters between the groups of the first sweep
+  u32* top_flag;   // [D1 / 32] bit i: top[i] equals the splitter after it
+  u32* tot1;       // [groups][D1] counts
+  u32* cur1;       // [groups][D1] pairs placed so far
+  u32* tot2;       // [D1][D2]
+  u32* cur2;       // [D1][D2]
+  u32* start1;     // [D1 + 1] first pair of each group of buckets
+  u32* tile0;      // [D1 + 1] first tile of the second sweep of each group
+  u32* start;      // [F + 1] first pair of each bucket
+  u32* big;        // number of buckets left to the large local sort, then those
+};
+
+// First kernel: control words of the sort and cleared counts.
+__global__ __launch_bounds__(256) void split_begin_kernel(SortCtl* __restrict__ ctl, u64 count,
+                                                          u32* __restrict__ clear, u64 words,
+                                                          u64* __restrict__ counters) {
+  const u64 stride = u64(gridDim.x) * blockDim.x;
+  for (u64 i = u64(blockIdx.x) * blockDim.x + threadIdx.x; i < words; i += stride) clear[i] = 0;
+  if (!ctl || blockIdx.x != 0) return;
+  if (threadIdx.x == 0) {
+    ctl->count = count;
+    ctl->dense = 0;
+  }
+  for (u32 i = threadIdx.x; i <= u32(kCtrActive); i += blockDim.x) counters[i] = 0;
+}
+
+// Sample i: the key of a position drawn in the i-th of `samples` equal stretches.
+__global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict__ keys, u32 count,
+                                                           u32 samples, u64* __restrict__ out) {
+  const u32 i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= samples) return;
+  const u32 lo = u32(u64(i) * count / samples), hi = u32(u64(i + 1) * count / samples);
+  const u32 w = hi > lo ? hi - lo : 1;
+  u32 p = lo + mix32(i + 0x9e3779b9u) % w;
+  if (p >= count) p = count - 1;
+  out[i] = keys[p];
+}
+
+// Sorts up to kSplitRankMax samples by counting, for each, the smaller ones
+// (ties by index): 16 samples per workgroup, each counted by 32 threads that
+// read neighbouring samples, so that 8192 samples occupy every CU.
+__global__ __launch_bounds__(kSplitBlock) void split_rank_kernel(const u64* __restrict__ in,
+                                                                 u32 samples,
+                                                                 u64* __restrict__ out) {
+  constexpr u32 PER = 16, PARTS = kSplitBlock / PER;
+  __shared__ u64 s_k[kSplitRankMax];
+  __shared__ u32 s_r[PER];
+  for (u32 i = threadIdx.x; i < samples; i += kSplitBlock) s_k[i] = in[i];
+  if (threadIdx.x < PER) s_r[threadIdx.x] = 0;
+  __syncthreads();
+  const u32 i = blockIdx.x * PER + threadIdx.x % PER;
+  const u32 p = threadIdx.x / PER;
+  if (i < samples) {
+    const u64 k = s_k[i];
+    u32 r = 0;
+    u32 j = p;
+    // Before sample i an equal one counts, after it does not.
+#pragma unroll 8
+    for (; j < i; j += PARTS) r += s_k[j] <= k ? 1u : 0u;
+#pragma unroll 8
+    for (; j < samples; j += PARTS) r += s_k[j] < k ? 1u : 0u;
+    atomicAdd(&s_r[threadIdx.x % PER], r);
+  }
+  __syncthreads();
+  if (p == 0 && i < samples) out[s_r[threadIdx.x]] = s_k[i];
+}
+
+// Splitters from the sorted samples: every over-th, and the table of the first
+// sweep (group i + 1 begins after splitter (i + 1) * D2 - 1).
+__global__ __launch_bounds__(256) void split_pick_kernel(const u64* __restrict__ sorted, int log1,
+                                                         int log2, u32 over, u32 samples,
+                                                         SplitArrays A) {
+  const u32 f = 1u << (log1 + log2);
+  auto at = [&](u32 i) {
+    const u64 q = u64(i + 1) * over;
+    return i + 1 < f && q < samples ? sorted[q] : ~u64(0);
+  };
+  const u32 i = blockIdx.x * 256 + threadIdx.x;
+  if (i < f) A.splitters[i] = at(i);
+  const u32 d1 = 1u << log1;
+  if (blockIdx.x * 256 < d1) {
+    const u32 last = ((i + 1) << log2) - 1;  // of group i
+    const u64 k = i < d1 ? at(last) : 0;
+    const bool same = i + 1 < d1 && at(last + 1) == k;
+    if (i < d1) A.top[i] = k;
+    const u64 m = __ballot(same);
+    if ((lane_id() & 31) == 0 && i < d1) A.top_flag[i >> 5] = u32(m >> lane_id());
+  }
+}
+
+// The pairs [base, base + n) and tables of one tile, for the kernels below.
+// Level 1: tile k of group g (g = workgroup mod groups, so that a group stays on
+// one XCD, whose L2 joins the partial lines at the ends of neighbouring tiles'
+// runs). Level 2: the workgroups of one XCD take consecutive tiles.
+struct SplitTile {
+  u32 row;   // row of the counts
+  u32 base;  // first pair
+  u32 n;     // pairs (0: none)
+  u32 out0;  // level 2: first pair of the group of buckets
+  bool first;
+};
+
+__device__ inline SplitTile split_tile2(const SplitArrays& A, u32 d1, u32 tile, u32 bid,
+                                        u32* s_row) {
+  SplitTile t{0, 0, 0, 0, false};
+  const u32 total = A.tile0[d1];
+  const u32 per = (total + kSplitXcds - 1) / kSplitXcds;
+  const u32 id = (bid % kSplitXcds) * per + bid / kSplitXcds;
+  if (bid / kSplitXcds >= per || id >= total) return t;  // uniform
+  for (u32 j = threadIdx.x; j < d1; j += kSplitBlock)
+    if (A.tile0[j] <= id && id < A.tile0[j + 1]) *s_row = j;
+  __syncthreads();
+  t.row = *s_row;
+  const u32 k = id - A.tile0[t.row];
+  t.out0 = A.start1[t.row];
+  const u32 size = A.start1[t.row + 1] - t.out0;
+  t.first = k == 0;
+  t.base = t.out0 + k * tile;
+  const u32 left = k * tile < size ? size - k * tile : 0;
+  t.n = left < tile ? left : tile;
+  if (t.n == 0 && !t.first) t.first = false;
+  return t;
+}
+
+// Splitter tree of a sweep into LDS: level 1 the `top` table and its flags, level 2
+// the row's own splitters. (Bit D - 1 of the flags is never set.)
+template <bool SECOND>
+__device__ inline void load_splitters(const SplitArrays& A, u32 row, int logd, u64* s_sp,
+                                      u32* s_fl) {
+  const u32 d = 1u << logd;
+  if (!SECOND) {
+    for (u32 i = threadIdx.x; i + 1 < d; i += kSplitBlock) s_sp[tree_node(i, logd)] = A.top[i];
+    for (u32 i = threadIdx.x; i < (d + 31) / 32; i += kSplitBlock) s_fl[i] = A.top_flag[i];
+  } else {
+    const u64* sp = A.splitters + (u64(row) << logd);
+    for (u32 i0 = 0; i0 < d; i0 += kSplitBlock) {
+      const u32 i = i0 + threadIdx.x;
+      const u64 k = i < d ? sp[i] : 0;
+      const bool same = i + 1 < d && sp[i + 1] == k;
+      if (i + 1 < d) s_sp[tree_node(i, logd)] = k;
+      const u64 m = __ballot(same);
+      if ((lane_id() & 31) == 0 && i < d) s_fl[i >> 5] = u32(m >> lane_id());
+    }
+  }
+}
+
+// Counts per bucket. Bound by the key reads (8 bytes a pair) and the search:
+// log2(D) LDS reads a pair. Level 1 also ORs the keys and their complements.
+template <int ITEMS, bool SECOND>
+__global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __restrict__ keys,
+                                                                 SplitShape S, SplitArrays A,
+                                                                 u64* __restrict__ counters) {
+  __shared__ u64 s_sp[kSplitMaxD];
+  __shared__ u32 s_cnt[kSplitMaxD];
+  __shared__ u32 s_fl[kSplitMaxD / 32];
+  __shared__ u32 s_row;
+  __shared__ u64 s_or[kSplitBlock / kWave], s_not[kSplitBlock / kWave];
+  constexpr u32 TILE = u32(ITEMS) * kSplitBlock;
+  const u32 tid = threadIdx.x;
+  const int logd = SECOND ? S.log2 : S.log1;
+  const u32 d = 1u << logd;
+  u32 row = 0, k0 = 0, kstep = 1, kend = 1;
+  SplitTile t{0, 0, 0, 0, false};
+  if (SECOND) {
+    t = split_tile2(A, 1u << S.log1, TILE, blockIdx.x, &s_row);
+    if (t.n == 0) return;
+    row = t.row;
+  } else {
+    row = blockIdx.x % S.groups;
+    k0 = blockIdx.x / S.groups;
+    kstep = gridDim.x / S.groups;
+    kend = S.per;
+  }
+  load_splitters<SECOND>(A, row, logd, s_sp, s_fl);
+  for (u32 i = tid; i < d; i += kSplitBlock) s_cnt[i] = 0;
+  __syncthreads();
+  u64 kor = 0, knot = 0;
+  for (u32 k = k0; k < kend; k += kstep) {
+    u32 base, n;
+    if (SECOND) {
+      base = t.base;
+      n = t.n;
+    } else {
+      const u64 b = (u64(row) * S.per + k) * TILE;
+      if (b >= S.count) break;
+      base = u32(b);
+      n = S.count - base < TILE ? S.count - base : TILE;
+    }
+    u64 key[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const u32 e = u32(j) * kSplitBlock + tid;
+      key[j] = e < n ? keys[u64(base) + e] : 0;
+    }
+    u32 bk[ITEMS];
+    buckets_of<ITEMS>(s_sp, s_fl, logd, key, bk);
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const u32 e = u32(j) * kSplitBlock + tid;
+      if (e < n) {
+        atomicAdd(&s_cnt[bk[j]], 1u);
+        if (!SECOND) {
+          kor |= key[j];
+          knot |= ~key[j];
+        }
+      }
+    }
+  }
+  if (!SECOND) {
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) {
+      kor |= __shfl_xor(kor, off, kWave);
+      knot |= __shfl_xor(knot, off, kWave);
+    }
+    if (lane_id() == 0) {
+      s_or[tid / kWave] = kor;
+      s_not[tid / kWave] = knot;
+    }
+  }
+  __syncthreads();
+  u32* tot = SECOND ? A.tot2 : A.tot1;
+  for (u32 i = tid; i < d; i += kSplitBlock) {
+    const u32 c = s_cnt[i];
+    if (c) atomicAdd(&tot[(u64(row) << logd) + i], c);
+  }
+  if (!SECOND && counters && tid == 0) {
+    u64 o = 0, n = 0;
+    for (int w = 0; w < kSplitBlock / kWave; ++w) {
+      o |= s_or[w];
+      n |= s_not[w];
+    }
+    if (o) atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyOr),
+                    (unsigned long long)o);
+    if (n) atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyNot),
+                    (unsigned long long)n);
+  }
+}
+
+// One scattering sweep. Bound by memory: 24 bytes a pair (20 when the values are
+// generated), each bucket's run of a tile written contiguously from LDS. A pair's
+// place in its run is its LDS fetch-add on the bucket's count (no order among
+// equal keys is kept, which saves the LSD sweep's ballots).
+// ITEMS = 12 fills 78 KB of LDS at 1024 buckets (two workgroups a CU).
+template <int ITEMS, bool SECOND>
+__global__ __launch_bounds__(kSplitBlock) __attribute__((amdgpu_waves_per_eu(4)))
+void split_sweep_kernel(
+    const u64* __restrict__ kin, const u32* __restrict__ vin, u64* __restrict__ kout,
+    u32* __restrict__ vout, SplitShape S, SplitArrays A, int iota, u64* __restrict__ counters) {
+  constexpr u32 TILE = u32(ITEMS) * kSplitBlock;
+  static_assert(kSplitMaxD <= 2 * kSplitBlock, "two buckets per thread");
+  __shared__ u64 s_buf[TILE];       // keys, then values
+  __shared__ u16 s_dig[TILE];
+  __shared__ u64 s_sp[kSplitMaxD];  // splitters, then (as u32) the output offsets
+  __shared__ u32 s_cnt[kSplitMaxD];
+  __shared__ u32 s_fl[kSplitMaxD / 32];
+  __shared__ u32 s_w[kSplitBlock / kWave];
+  __shared__ u32 s_row;
+  const u32 tid = threadIdx.x;
+  const int logd = SECOND ? S.log2 : S.log1;
+  const u32 d = 1u << logd;
+  SplitTile t{0, 0, 0, 0, false};
+  if (SECOND) {
+    t = split_tile2(A, 1u << S.log1, TILE, blockIdx.x, &s_row);
+    if (t.n == 0 && !t.first) return;  // uniform
+  } else {
+    t.row = blockIdx.x % S.groups;
+    const u32 k = blockIdx.x / S.groups;
+    const u64 b = (u64(t.row) * S.per + k) * TILE;
+    t.first = blockIdx.x == 0;
+    if (k >= S.per || b >= S.count) return;  // (workgroup 0 always has a tile)
+    t.base = u32(b);
+    t.n = S.count - t.base < TILE ? S.count - t.base : TILE;
+  }
+  // The tile's pairs are requested first.
+  u64 key[ITEMS];
+  u32 val[ITEMS];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const u32 e = u32(j) * kSplitBlock + tid;
+    key[j] = e < t.n ? __builtin_nontemporal_load(kin + t.base + e) : 0;
+  }
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const u32 e = u32(j) * kSplitBlock + tid;
+    val[j] = iota ? t.base + e : (vin && e < t.n) ? __builtin_nontemporal_load(vin + t.base + e) : 0;
+  }
+  load_splitters<SECOND>(A, t.row, logd, s_sp, s_fl);
+  for (u32 i = tid; i < d; i += kSplitBlock) s_cnt[i] = 0;
+  // Where the buckets 2 tid and 2 tid + 1 of this row start: their totals
+  // scanned, plus (level 1) what earlier groups put there.
+  u32 all[2] = {0, 0}, below[2] = {0, 0};
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const u32 b = 2 * tid + q;
+    if (b >= d) continue;
+    if (SECOND) {
+      all[q] = A.tot2[(u64(t.row) << logd) + b];
+    } else {
+      for (u32 g = 0; g < S.groups; ++g) {
+        const u32 c = A.tot1[(g << logd) + b];
+        all[q] += c;
+        if (g < t.row) below[q] += c;
+      }
+    }
+  }
+  u32 at[2];
+  at[0] = t.out0 + block_exclusive_sum(all[0] + all[1], s_w);  // (two barriers: the tables are set)
+  at[1] = at[0] + all[0];
+  if (t.first) {
+    // What the next kernels read: the start of every bucket and, after the
+    // first of two sweeps, the tiles of the second (at least one per group).
+    u32* start = SECOND ? A.start + (u64(t.row) << logd) : S.log2 ? A.start1 : A.start;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (2 * tid + q < d) start[2 * tid + q] = at[q];
+    if (tid == 0 && (!SECOND || t.row + 1 == (1u << S.log1))) start[d] = S.count;
+    if (!SECOND && S.log2) {
+      u32 nt[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        nt[q] = 2 * tid + q < d ? (all[q] ? (all[q] - 1) / S.tile + 1 : 1u) : 0u;
+      const u32 t0 = block_exclusive_sum(nt[0] + nt[1], s_w);
+      if (2 * tid < d) A.tile0[2 * tid] = t0;
+      if (2 * tid + 1 < d) A.tile0[2 * tid + 1] = t0 + nt[0];
+      if (2 * tid + 2 == d) A.tile0[d] = t0 + nt[0] + nt[1];
+    }
+  }
+  if (t.n == 0) return;  // uniform
+  u32 place[ITEMS];  // bucket, then the pair's place in the tile
+  u32 rank[ITEMS];
+  buckets_of<ITEMS>(s_sp, s_fl, logd, key, place);
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const u32 e = u32(j) * kSplitBlock + tid;
+    rank[j] = e < t.n ? atomicAdd(&s_cnt[place[j]], 1u) : 0u;
+  }
+  __syncthreads();
+  u32 cnt[2] = {0, 0}, off[2] = {0, 0};
+  u32* cur = SECOND ? A.cur2 : A.cur1;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const u32 b = 2 * tid + q;
+    if (b < d) {
+      cnt[q] = s_cnt[b];
+      if (cnt[q]) off[q] = at[q] + below[q] + atomicAdd(&cur[(u64(t.row) << logd) + b], cnt[q]);
+    }
+  }
+  const u32 l0 = block_exclusive_sum(cnt[0] + cnt[1], s_w);
+  u32* s_delta = reinterpret_cast<u32*>(s_sp);  // every search is done
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const u32 b = 2 * tid + q;
+    if (b < d) {
+      const u32 l = q ? l0 + cnt[0] : l0;
+      s_cnt[b] = l;
+      s_delta[b] = off[q] - l;  // modulo 2^32
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const u32 e = u32(j) * kSplitBlock + tid;
+    if (e < t.n) {
+      const u32 b = place[j];
+      const u32 p = s_cnt[b] + rank[j];  // < t.n: the counts of the tile sum to t.n
+      place[j] = p;
+      s_buf[p] = key[j];
+      s_dig[p] = u16(b);
+    }
+  }
+  __syncthreads();
+  bool bad = false;
+  u32 o[ITEMS];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const u32 q = u32(j) * kSplitBlock + tid;
+    o[j] = ~0u;
+    if (q < t.n) {
+      o[j] = s_delta[s_dig[q]] + q;
+      if (o[j] < S.count) kout[o[j]] = s_buf[q];
+      else bad = true;
+    }
+  }
+  if (bad) flag(counters, kErrBounds);
+  if (!vout) return;
+  __syncthreads();
+  u32* s_val = reinterpret_cast<u32*>(s_buf);
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const u32 e = u32(j) * kSplitBlock + tid;
+    if (e < t.n) s_val[place[j]] = val[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const u32 q = u32(j) * kSplitBlock + tid;
+    if (q < t.n && o[j] < S.count) vout[o[j]] = s_val[q];
+  }
+}
+
+// x of the lane whose number differs in the bits of MASK (1, 2, 3, 4, 7, 8, 15 by
+// data-parallel moves inside rows of 16 lanes, others through LDS hardware).
+template <int MASK>
+__device__ inline u32 lane_xor(u32 x) {
+  auto dpp = [](u32 v, auto ctrl) {
+    return u32(__builtin_amdgcn_mov_dpp(int(v), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  if constexpr (MASK == 1) return dpp(x, std::integral_constant<int, 0xB1>{});
+  else if constexpr (MASK == 2) return dpp(x, std::integral_constant<int, 0x4E>{});
+  else if constexpr (MASK == 3) return dpp(x, std::integral_constant<int, 0x1B>{});
+  else if constexpr (MASK == 7) return dpp(x, std::integral_constant<int, 0x141>{});
+  else if constexpr (MASK == 4) return lane_xor<3>(lane_xor<7>(x));
+  else if constexpr (MASK == 8) return dpp(x, std::integral_constant<int, 0x128>{});
+  else if constexpr (MASK == 15) return dpp(x, std::integral_constant<int, 0x140>{});
+  else return u32(__shfl_xor(int(x), MASK, kWave));
+}
+
+// One compare-exchange step with the lane MASK away: the lower lane keeps the
+// smaller key.
+template <int MASK>
+__device__ inline u64 exchange(u64 v) {
+  const u64 o = (u64(lane_xor<MASK>(u32(v >> 32))) << 32) | lane_xor<MASK>(u32(v));
+  const bool lower = (lane_id() & MASK) < (MASK + 1) / 2;
+  return ((o < v) == lower) ? o : v;
+}
+
+// The wave's 64 keys in ascending lane order (bitonic merges of mirrored runs).
+__device__ inline u64 wave_sort(u64 v) {
+  v = exchange<1>(v);
+  v = exchange<3>(v); v = exchange<1>(v);
+  v = exchange<7>(v); v = exchange<2>(v); v = exchange<1>(v);
+  v = exchange<15>(v); v = exchange<4>(v); v = exchange<2>(v); v = exchange<1>(v);
+  v = exchange<31>(v); v = exchange<8>(v); v = exchange<4>(v); v = exchange<2>(v);
+  v = exchange<1>(v);
+  v = exchange<63>(v); v = exchange<16>(v); v = exchange<8>(v); v = exchange<4>(v);
+  v = exchange<2>(v); v = exchange<1>(v);
+  return v;
+}
+
+// Every bucket sorted in place, one workgroup each (a persistent grid strides
+// over them). The workgroup's first BLOCK keys, sorted (each wave its 64 in
+// registers, then their places among the other waves' by binary search), are the
+// splitters of BLOCK parts of about four pairs; the pairs go to their parts in
+// LDS, and each takes its place there by counting the smaller keys of its part.
+// Bound by memory (24 bytes a pair) as long as the LDS work (about 25 reads a
+// pair) and the waits between its steps stay below it: the next bucket's pairs
+// are requested as soon as this one's are in LDS, and a workgroup is small (two
+// waves and ten workgroups a CU for buckets of 512, four and five for 1024) so
+// that others work while one waits.
+// A bucket of more than CAP pairs goes to the list `big` for a launch of the
+// larger shape (which takes its buckets from there: from_list), or if there is no
+// list raises kCtrSplitOver. start == nullptr: the whole input (count <= CAP) is
+// the one bucket, with generated values when iota is set and the key ORs left in
+// the counters.
+template <int CAP, int BLOCK>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5)))
+void split_local_kernel(
+    u64* __restrict__ keys, u32* __restrict__ vals, u32 count, u32 nbuckets,
+    const u32* __restrict__ start, const u64* __restrict__ splitters, u32* __restrict__ big,
+    int from_list, int iota, u64* __restrict__ counters) {
+  constexpr int IT = (CAP + BLOCK - 1) / BLOCK;
+  constexpr int P = BLOCK;          // parts, and samples
+  constexpr int NW = BLOCK / kWave;
+  constexpr int LOGP = __builtin_ctz(P);
+  constexpr int PER = P / kWave;    // parts per lane of the scanning wave
+  constexpr int GANG = 2;           // counts of a thread side by side
+  static_assert(IT % kSearchGang == 0 && IT % GANG == 0, "whole gangs");
+  typedef typename std::conditional<(P <= 256), u8, u16>::type Part;
+  __shared__ u64 s_key[CAP + 4];
+  __shared__ u32 s_val[CAP];
+  __shared__ Part s_part[CAP];
+  __shared__ u64 s_raw[P];   // samples
+  __shared__ u64 s_sp[P];    // splitter tree
+  __shared__ u32 s_cnt[P];
+  __shared__ u32 s_off[P + 1];
+  __shared__ u32 s_fl[P / 32];
+  const u32 tid = threadIdx.x;
+  if (from_list) {
+    nbuckets = big[0];
+    if (nbuckets == 0) return;
+  }
+  // Bucket w of the launch: its first pair, its size (0: nothing to sort), the
+  // key below it and whether its keys, less that one, leave the low kPosBits
+  // bits free.
+  auto bucket = [&](u32 w, u32& a, u32& m, u64& low, bool& narrow) {
+    a = 0;
+    m = 0;
+    low = 0;
+    narrow = false;
+    if (w >= nbuckets) return;
+    if (!start) {
+      m = count;
+      return;
+    }
+    const u32 f = from_list ? big[1 + w] : w;
+    a = start[f];
+    const u32 z = start[f + 1];
+    low = f > 0 ? splitters[f - 1] : 0;
+    const u64 width = splitters[f] - low;
+    const bool same = f > 0 && width == 0;
+    narrow = (width >> (64 - kPosBits)) == 0;
+    if (z < a || z > count) {
+      if (tid == 0) flag(counters, kErrBounds);
+      return;
+    }
+    // An equality bucket is in order already, and so is a single pair.
+    if (z - a <= 1 || same) return;
+    if (z - a > u32(CAP)) {
+      if (tid == 0) {
+        if (big && !from_list)
+          big[1 + atomicAdd(&big[0], 1u)] = f;
+        else
+          counters[kCtrSplitOver] = 1;
+      }
+      return;
+    }
+    m = z - a;
+  };
+  u64 key[IT];
+  u32 val[IT];
+  auto load = [&](u32 a, u32 m) {
+#pragma unroll
+    for (int j = 0; j < IT; ++j) {
+      const u32 e = u32(j) * BLOCK + tid;
+      key[j] = 0;
+      val[j] = 0;
+      if (e < m) {
+        key[j] = keys[u64(a) + e];
+        val[j] = iota ? e : vals ? vals[u64(a) + e] : 0;
+      }
+    }
+  };
+  u32 a, m;
+  u64 low;
+  bool narrow;
+  bucket(blockIdx.x, a, m, low, narrow);
+  load(a, m);
+  for (u32 w = blockIdx.x; w < nbuckets; w += gridDim.x) {
+    u32 na, nm;
+    u64 nlow;
+    bool nnarrow;
+    bucket(w + gridDim.x, na, nm, nlow, nnarrow);
+    if (!start && counters) {
+      // The whole input: the bits that vary, for the plan.
+      u64 o = 0, n = 0;
+#pragma unroll
+      for (int j = 0; j < IT; ++j)
+        if (u32(j) * BLOCK + tid < m) {
+          o |= key[j];
+          n |= ~key[j];
+        }
+#pragma unroll
+      for (int off = kWave / 2; off >= 1; off >>= 1) {
+        o |= __shfl_xor(o, off, kWave);
+        n |= __shfl_xor(n, off, kWave);
+      }
+      if (lane_id() != 0) o = n = 0;
+      if (o) atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyOr),
+                      (unsigned long long)o);
+      if (n) atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyNot),
+                      (unsigned long long)n);
+    }
+    const bool split = m >= u32(P);  // fewer pairs: one part
+    s_cnt[tid] = 0;
+    if (split) {
+      const u64 k = wave_sort(key[0]);
+      s_raw[tid] = k;
+      __syncthreads();
+      // Place among all samples: equal ones of earlier waves come first.
+      const u32 wave = tid / kWave;
+      u32 r = u32(lane_id());
+#pragma unroll
+      for (u32 o = 1; o < u32(NW); ++o) {
+        const u32 other = (wave + o) % NW;
+        const u64* list = s_raw + other * kWave;
+        const u64 lim = other < wave ? 1 : 0;  // count keys <= k, or < k
+        u32 c = 0;
+#pragma unroll
+        for (u32 step = kWave / 2; step; step >>= 1) {
+          const u64 x = list[c + step - 1];
+          c += (lim ? x <= k : x < k) ? step : 0u;
+        }
+        const u64 x = list[c];
+        r += c + ((lim ? x <= k : x < k) ? 1u : 0u);
+      }
+      __syncthreads();
+      // Sorted samples 1 .. P - 1 are the splitters.
+      s_raw[r] = k;
+      if (r > 0) s_sp[tree_node(r - 1, LOGP)] = k;
+      __syncthreads();
+      // Bit b: splitters b and b + 1 (sorted samples b + 1 and b + 2) are equal.
+      const bool same = tid + 2 < u32(P) && s_raw[tid + 1] == s_raw[tid + 2];
+      const u64 ms = __ballot(same);
+      if ((lane_id() & 31) == 0) s_fl[tid >> 5] = u32(ms >> lane_id());
+    }
+    __syncthreads();
+    u32 pr[IT];  // part | place in it << 16
+    if (split) {
+#pragma unroll
+      for (int j = 0; j < IT; j += kSearchGang) {
+        if (u32(j) * BLOCK < m) {  // uniform
+          u32 part[kSearchGang];
+          buckets_of<kSearchGang>(s_sp, s_fl, LOGP, key + j, part);
+#pragma unroll
+          for (int y = 0; y < kSearchGang; ++y) {
+            const u32 e = u32(j + y) * BLOCK + tid;
+            pr[j + y] = e < m ? part[y] | (atomicAdd(&s_cnt[part[y]], 1u) << 16) : 0u;
+          }
+        }
+      }
+    } else {
+      pr[0] = tid << 16;  // m < P = BLOCK: one pair a thread
+      if (tid == 0) s_cnt[0] = m;
+    }
+    __syncthreads();
+    if (tid < u32(kWave)) {
+      u32 c[PER], sum = 0;
+#pragma unroll
+      for (int y = 0; y < PER; ++y) {
+        c[y] = s_cnt[PER * tid + y];
+        sum += c[y];
+      }
+      u32 run = wave_inclusive_sum(sum) - sum;
+#pragma unroll
+      for (int y = 0; y < PER; ++y) {
+        s_off[PER * tid + y] = run;
+        run += c[y];
+      }
+      if (tid == u32(kWave) - 1) s_off[P] = run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < IT; ++j) {
+      const u32 e = u32(j) * BLOCK + tid;
+      if (e < m) {
+        const u32 b = pr[j] & 0xFFFFu;
+        const u32 p = s_off[b] + (pr[j] >> 16);
+        // Narrow buckets: the key's offset with the place below it, so that no
+        // two are equal and one comparison orders a pair.
+        s_key[p] = narrow ? ((key[j] - low) << kPosBits) | p : key[j];
+        s_val[p] = val[j];
+        s_part[p] = Part(b);
+      }
+    }
+    if (tid < 4u) s_key[m + tid] = ~u64(0);  // read, never counted, by the last part
+    __syncthreads();
+    load(na, nm);
+    // Pair q: its place is its part's start plus the smaller keys of the part.
+    // (Parts are ordered: keys read past the part's end are larger.) A part of
+    // equal keys is in order already.
+#pragma unroll
+    for (int j = 0; j < IT; j += GANG) {
+      if (u32(j) * BLOCK >= m) break;  // uniform
+      u64 k[GANG];
+      u32 at[GANG], lo[GANG], longest = 0;
+#pragma unroll
+      for (int y = 0; y < GANG; ++y) {
+        const u32 q = u32(j + y) * BLOCK + tid;
+        k[y] = q < m ? s_key[q] : 0;
+        const u32 b = q < m ? s_part[q] : 0u;
+        lo[y] = s_off[b];
+        u32 size = q < m ? s_off[b + 1] - lo[y] : 0u;
+        if (split && b > 0 && ((s_fl[(b - 1) >> 5] >> ((b - 1) & 31u)) & 1u)) {
+          lo[y] = q;
+          size = 1;
+        }
+        at[y] = lo[y];
+        longest = size > longest ? size : longest;
+      }
+      if (narrow) {
+        for (u32 x = 0; x < longest; x += 4) {
+#pragma unroll
+          for (int y = 0; y < GANG; ++y) {
+            const u32 z = lo[y] + x < m ? lo[y] + x : m;
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) at[y] += s_key[z + i] < k[y] ? 1u : 0u;
+          }
+        }
+      } else {
+        for (u32 x = 0; x < longest; x += 4) {
+#pragma unroll
+          for (int y = 0; y < GANG; ++y) {
+            const u32 z = lo[y] + x < m ? lo[y] + x : m;
+            const u32 before = u32(j + y) * BLOCK + tid - z;  // keys of the four before q
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+              const u64 kx = s_key[z + i];
+              at[y] += (kx < k[y] || (kx == k[y] && int(i) < int(before))) ? 1u : 0u;
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int y = 0; y < GANG; ++y) {
+        const u32 q = u32(j + y) * BLOCK + tid;
+        if (q < m) {
+          keys[u64(a) + at[y]] = narrow ? (k[y] >> kPosBits) + low : k[y];
+          if (vals) vals[u64(a) + at[y]] = s_val[q];
+        }
+      }
+    }
+    __syncthreads();  // the next bucket reuses the LDS arrays
+    a = na;
+    m = nm;
+    low = nlow;
+    narrow = nnarrow;
+  }
+}
+
+// The sort's plan as the re-rank and the round log read it: the buffer that
+// holds the output, and which digits vary (skip flags).
+__global__ void split_plan_kernel(const u64* __restrict__ counters, int npass, u32 final_buf,
+                                  SortPlan* __restrict__ plan, u32* __restrict__ plan_log,
+                                  int log_row, int rb) {
+  const int p = threadIdx.x;
+  if (p >= kMaxPasses) return;
+  const u64 varying = counters[kCtrKeyOr] & counters[kCtrKeyNot];
+  u32 skip = !(p < npass && ((varying >> (p * rb)) & ((u64(1) << rb) - 1)) != 0);
+  if (varying == 0) skip = p != npass - 1;  // all keys equal: the LSD sort's one copy pass
+  plan->skip[p] = skip;
+  u32* f = plan_log + size_t(log_row) * kPlanLogWords;
+  f[p] = skip;
+  f[kMaxPasses + p] = 0;
+  f[2 * kMaxPasses + p] = 0;
+  if (p == 0) {
+    plan->final_buf = final_buf;
+    f[3 * kMaxPasses] = final_buf;
+  }
+}
+
+namespace {
+
+SplitShape split_shape(u64 count) {
+  SplitShape S{};
+  S.count = u32(count);
+  int lf = 0;
+  if (count > kSplitCap) {
+    // Buckets of at most 512 pairs on average; of up to 1024 where one sweep then
+    // does for two, and above 2^29 pairs.
+    while (lf < 2 * kSplitMaxLogD && (count >> 9) > (u64(1) << lf)) ++lf;
+    if (lf == kSplitMaxLogD + 1 && (count >> kSplitMaxLogD) <= kSplitMaxD) lf = kSplitMaxLogD;
+    // Small inputs: buckets of 256, so that more CUs take part.
+    while (lf < kSplitMaxLogD && (count >> 8) > (u64(1) << lf)) ++lf;
+  }
+  // One sweep up to 1024 buckets (2^20 pairs); above, two of about equal width.
+  if (lf <= kSplitMaxLogD) {
+    S.log1 = lf;
+    S.log2 = 0;
+  } else {
+    S.log2 = lf / 2;
+    S.log1 = lf - S.log2;
+  }
+  S.over = lf > kSplitMaxLogD ? 12 : count > (u64(512) << lf) ? 8 : 4;
+  S.samples = S.over << lf;
+  // Small inputs: small tiles, so that more CUs take part.
+  S.tile = count < (u64(1) << 22) ? 4 * kSplitBlock : 12 * kSplitBlock;
+  S.tiles = u32(ceil_div(count, S.tile));
+  S.groups = S.tiles >= 16 * kSplitXcds ? kSplitXcds : 1;
+  S.per = (S.tiles + S.groups - 1) / S.groups;
+  return S;
+}
+
+struct Carver {
+  char* p;
+  size_t left;
+  bool ok = true;
+  void* take(size_t bytes) {
+    bytes = (bytes + 255) / 256 * 256;
+    if (bytes > left) {
+      ok = false;
+      return nullptr;
+    }
+    void* r = p;
+    p += bytes;
+    left -= bytes;
+    return r;
+  }
+  template <typename T>
+  T* get(u64 n) { return static_cast<T*>(take(size_t(n) * sizeof(T))); }
+};
+
+// Arrays of one sort; the counts to clear come first, in one piece.
+SplitArrays carve(Carver& cv, const SplitShape& S, u32** clear, u64* clear_words) {
+  SplitArrays A{};
+  const u64 d1 = u64(1) << S.log1, f = S.nb(), rows1 = u64(S.groups) * d1;
+  const u64 words = 2 * rows1 + (S.log2 ? 2 * f : 0) + 1;
+  u32* p = cv.get<u32>(words + f);
+  *clear = p;
+  *clear_words = words;
+  A.tot1 = p;
+  A.cur1 = p + rows1;
+  A.tot2 = p + 2 * rows1;
+  A.cur2 = p + 2 * rows1 + f;
+  A.big = p + words - 1;
+  A.splitters = cv.get<u64>(f);
+  A.top = cv.get<u64>(d1);
+  A.top_flag = cv.get<u32>(ceil_div(d1, 32));
+  A.start1 = cv.get<u32>(d1 + 1);
+  A.tile0 = cv.get<u32>(d1 + 1);
+  A.start = cv.get<u32>(f + 1);
+  return A;
+}
+
+}  // namespace
+}  // namespace sa
+
+namespace drv {
+
+// Sorts `count` pairs in (kA, vA) (values optional) within `cv`'s scratch; the
+// result ends in buffer A or B (*fin). top: the build's own sort, whose control
+// words and plan row are set; otherwise a sort of samples inside one.
+static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, int iota, Carver cv, bool top,
+                           int npass, int log_row, u32* fin, hipStream_t s) {
+  const SplitShape S = split_shape(count);
+  u32* clear = nullptr;
+  u64 words = 0;
+  const SplitArrays A = carve(cv, S, &clear, &words);
+  const bool sweeps = S.log1 > 0;
+  u64 *sk = nullptr, *sk2 = nullptr;
+  if (sweeps) {
+    sk = cv.get<u64>(S.samples);
+    sk2 = cv.get<u64>(S.samples);
+  }
+  if (!cv.ok) return SA_EDEVICE;  // split_fits() has checked this
+  u64* ctr = c->counters;
+  u64* const ctr_top = top ? ctr : nullptr;
+  *fin = 0;
+  {
+    Tracer t(c, s, SA_KERNEL_OTHER, 0);
+    const u32 g = u32(std::min<u64>(std::max<u64>(1, ceil_div(words, 1024)), 1024));
+    if (top || words)
+      hipLaunchKernelGGL(split_begin_kernel, dim3(g), dim3(256), 0, s, top ? c->ctl : nullptr,
+                         count, clear, words, ctr);
+  }
+  u64* kout = bf.kA;
+  u32* vout = bf.vA;
+  if (!sweeps) {
+    Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (iota ? 20.0 : 24.0));
+    hipLaunchKernelGGL((split_local_kernel<int(kSplitCap), kSplitBlock>), dim3(1),
+                       dim3(kSplitBlock), 0, s, bf.kA, bf.vA, u32(count), 1u, nullptr, nullptr,
+                       nullptr, 0, iota, ctr);
+  } else {
+    {
+      Tracer t(c, s, SA_KERNEL_OTHER, 0);
+      hipLaunchKernelGGL(split_sample_kernel, dim3(u32(ceil_div(S.samples, 256))), dim3(256), 0, s,
+                         bf.kA, S.count, S.samples, sk);
+      u64* sorted = sk2;
+      if (S.samples <= kSplitRankMax) {
+        hipLaunchKernelGGL(split_rank_kernel, dim3(u32(ceil_div(S.samples, 16))),
+                           dim3(kSplitBlock), 0, s, sk, S.samples, sk2);
+      } else {
+        u32 sf = 0;
+        const Bufs sb{sk, sk2, nullptr, nullptr};
+        const sa_status st = split_run(c, sb, S.samples, 0, cv, false, 0, 0, &sf, s);
+        if (st != SA_OK) return st;
+        sorted = sf ? sk2 : sk;
+      }
+      hipLaunchKernelGGL(split_pick_kernel, dim3(u32(ceil_div(S.nb(), 256))), dim3(256), 0, s,
+                         sorted, S.log1, S.log2, S.over, S.samples, A);
+    }
+    const bool small = S.tile == 4 * kSplitBlock;
+    const u32 hgrid = S.groups * std::min<u32>(S.per, 2048 / S.groups);
+    {
+      Tracer t(c, s, SA_KERNEL_HISTOGRAM, double(count) * 8.0);
+      if (small)
+        hipLaunchKernelGGL((split_hist_kernel<4, false>), dim3(hgrid), dim3(kSplitBlock), 0, s,
+                           bf.kA, S, A, ctr_top);
+      else
+        hipLaunchKernelGGL((split_hist_kernel<12, false>), dim3(hgrid), dim3(kSplitBlock), 0, s,
+                           bf.kA, S, A, ctr_top);
+    }
+    const u32* vin = iota ? nullptr : bf.vA;
+    {
+      Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (iota ? 20.0 : 24.0));
+      if (small)
+        hipLaunchKernelGGL((split_sweep_kernel<4, false>), dim3(S.groups * S.per),
+                           dim3(kSplitBlock), 0, s, bf.kA, vin, bf.kB, bf.vB, S, A, iota, ctr);
+      else
+        hipLaunchKernelGGL((split_sweep_kernel<12, false>), dim3(S.groups * S.per),
+                           dim3(kSplitBlock), 0, s, bf.kA, vin, bf.kB, bf.vB, S, A, iota, ctr);
+    }
+    kout = bf.kB;
+    vout = bf.vB;
+    *fin = 1;
+    if (S.log2) {
+      // At most one partly filled tile per group; a multiple of the XCDs.
+      const u32 grid = u32(ceil_div(u64(S.tiles) + (u64(1) << S.log1), kSplitXcds) * kSplitXcds);
+      {
+        Tracer t(c, s, SA_KERNEL_HISTOGRAM, double(count) * 8.0);
+        if (small)
+          hipLaunchKernelGGL((split_hist_kernel<4, true>), dim3(grid), dim3(kSplitBlock), 0, s,
+                             bf.kB, S, A, nullptr);
+        else
+          hipLaunchKernelGGL((split_hist_kernel<12, true>), dim3(grid), dim3(kSplitBlock), 0, s,
+                             bf.kB, S, A, nullptr);
+      }
+      {
+        Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * 24.0);
+        if (small)
+          hipLaunchKernelGGL((split_sweep_kernel<4, true>), dim3(grid), dim3(kSplitBlock), 0, s,
+                             bf.kB, bf.vB, bf.kA, bf.vA, S, A, 0, ctr);
+        else
+          hipLaunchKernelGGL((split_sweep_kernel<12, true>), dim3(grid), dim3(kSplitBlock), 0, s,
+                             bf.kB, bf.vB, bf.kA, bf.vA, S, A, 0, ctr);
+      }
+      kout = bf.kA;
+      vout = bf.vA;
+      *fin = 0;
+    }
+    Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * 24.0);
+    const u32 nb = S.nb();
+    if ((count >> 9) <= nb)
+      hipLaunchKernelGGL((split_local_kernel<1016, 128>),
+                         dim3(std::min<u32>(nb, u32(c->num_cus) * 10)), dim3(128), 0, s, kout, vout,
+                         u32(count), nb, A.start, A.splitters, A.big, 0, 0, ctr);
+    else
+      hipLaunchKernelGGL((split_local_kernel<2032, 256>),
+                         dim3(std::min<u32>(nb, u32(c->num_cus) * 5)), dim3(256), 0, s, kout, vout,
+                         u32(count), nb, A.start, A.splitters, A.big, 0, 0, ctr);
+    hipLaunchKernelGGL((split_local_kernel<int(kSplitCap), kSplitBlock>),
+                       dim3(std::min<u32>(nb, u32(c->num_cus) * 2)), dim3(kSplitBlock), 0, s,
+                       kout, vout, u32(count), nb, A.start, A.splitters, A.big, 1, 0, ctr);
+  }
+  if (top) {
+    Tracer t(c, s, SA_KERNEL_OTHER, 0);
+    hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(kWave), 0, s, ctr, npass, *fin, c->plan,
+                       c->plan_log, log_row, c->radix_bits);
+  }
+  return SA_OK;
+}
+
+// Whether a sort of `count` pairs may take the split sort. An explicit tuning
+// asks for the LSD sweeps it describes. Above 1280 * 2^20 pairs a bucket's mean
+// comes too close to kSplitCap. The scratch is the active list's position
+// array (4 bytes a suffix; no sort's input needs it any more and no sort's output
+// yet). The ranks beside it stay: a multi-text round can be repeated.
+bool split_usable(const sa_ctx* c, u64 count) {
+  if (c->tuning_explicit || c->force_lsd || count == 0 || count > (u64(1280) << 20)) return false;
+  // Arrays and samples of the sort and of the sorts of samples inside it.
+  size_t need = 0;
+  for (u64 n = count;;) {
+    const SplitShape S = split_shape(n);
+    Carver cv{nullptr, ~size_t(0)};
+    u32* clear;
+    u64 words;
+    carve(cv, S, &clear, &words);
+    if (S.log1) {
+      cv.get<u64>(S.samples);
+      cv.get<u64>(S.samples);
+    }
+    need += ~size_t(0) - cv.left;
+    if (S.log1 == 0 || S.samples <= kSplitRankMax) break;
+    n = S.samples;
+  }
+  return need <= size_t(c->cap) * 4;
+}
+
+sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_present, int slot,
+                     hipStream_t s) {
+  u32 fin = 0;
+  const Carver cv{reinterpret_cast<char*>(c->act_idx), size_t(c->cap) * 4};
+  return split_run(c, bf, count, vals_present ? 0 : 1, cv, true, npass, slot, &fin, s);
+}
+
+}  // namespace drv

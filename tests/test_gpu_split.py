@@ -1,0 +1,106 @@
+"""Builds whose round-0 sort takes the split sort (sampled splitters, up to two
+scattering sweeps, buckets sorted in LDS) against the oracle, at the edges of its
+shapes: one bucket in LDS, one sweep, two sweeps, partly filled tiles; keys that
+fill equality buckets; and an input whose sample misses most of its keys, so that
+a bucket overflows and the LSD sort repeats the work."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as W
+from paper_1610_03007_amd import SuffixArrayBuilder
+
+pytestmark = pytest.mark.gpu
+
+LDS_PAIRS = 3840
+
+
+@pytest.fixture(scope="module")
+def builder():
+    b = SuffixArrayBuilder(0, tune_cache="")
+    yield b
+    b.close()
+
+
+def check(b, text):
+    t = np.ascontiguousarray(text, dtype=np.uint8)
+    sa = b.build(torch.from_numpy(t.copy()).to("cuda:0"))
+    torch.cuda.synchronize()
+    assert np.array_equal(sa.cpu().numpy().view(np.uint32), oracle.sa(t, parallel=True)), t.size
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 127, 128, 129, LDS_PAIRS - 1, LDS_PAIRS, LDS_PAIRS + 1,
+                               4 * 2048, 4 * 2048 + 1, (1 << 20) - 1, 1 << 20, (1 << 20) + 1,
+                               (1 << 22) - 3, (1 << 22) + 6144 * 3 + 1])
+def test_shapes(builder, n):
+    check(builder, W.dna(n, seed=n))
+    rng = np.random.default_rng(n)
+    check(builder, rng.integers(0, 256, n))
+
+
+@pytest.mark.parametrize("n", [3000, 50001, 1500000, 5000000])
+def test_equal_keys(builder, n):
+    """Few distinct keys: every key, or all but a few, in equality buckets (among
+    them the largest key there is, eight bytes of the last of 255 codes)."""
+    rng = np.random.default_rng(n)
+    check(builder, np.full(n, 7))
+    check(builder, np.where(rng.random(n) < 0.999, 200, rng.integers(0, 200, n)))
+    t = np.where(rng.random(n) < 0.9, 255, rng.integers(1, 256, n))
+    check(builder, t)
+    t = rng.integers(0, 4, n)
+    t[n // 4:n // 2] = 2
+    check(builder, t)
+    check(builder, np.tile(rng.integers(0, 96, 997), n // 997 + 1)[:n])
+
+
+def mix32(x):
+    x = x ^ (x >> 16)
+    x = (x * 0x7feb352d) & 0xFFFFFFFF
+    x = x ^ (x >> 15)
+    x = (x * 0x846ca68b) & 0xFFFFFFFF
+    return x ^ (x >> 16)
+
+
+def test_overflow_repeats_with_lsd(builder):
+    n, samples = 20000, 512  # 128 buckets of 4 samples
+    rng = np.random.default_rng(5)
+    t = rng.integers(1, 256, n).astype(np.uint8)
+    for i in range(samples):
+        lo, hi = i * n // samples, (i + 1) * n // samples
+        p = lo + mix32((i + 0x9e3779b9) & 0xFFFFFFFF) % (hi - lo)
+        t[p:p + 8] = 1
+    builder.set_trace(True)
+    try:
+        builder.reset_stats()
+        check(builder, rng.integers(1, 256, n))
+        few = builder.kernel_stats()["sort_pass"]["launches"]
+        builder.reset_stats()
+        check(builder, t)
+        many = builder.kernel_stats()["sort_pass"]["launches"]
+    finally:
+        builder.set_trace(False)
+    assert many > few + 4, (few, many)
+
+
+def test_batch_and_dc_builds(builder):
+    """The other builds that sort this way: a batch (text number in the keys), DC3
+    and DC7, over both local sort shapes."""
+    rng = np.random.default_rng(11)
+    for total in (9000, 700000, 2600000):
+        cuts = np.sort(rng.integers(0, total + 1, 30))
+        off = np.concatenate([[0], cuts, [total]]).astype(np.uint64)
+        t = rng.integers(0, 3, total).astype(np.uint8)
+        t[total // 3:total // 2] = 1
+        d = torch.from_numpy(t).to("cuda:0")
+        sa = builder.build_batch(d, off)
+        torch.cuda.synchronize()
+        sa = sa.cpu().numpy().view(np.uint32)
+        for a, z in zip(off[:-1], off[1:]):
+            if z > a:
+                assert np.array_equal(sa[int(a):int(z)], oracle.sa(t[int(a):int(z)], parallel=True))
+        for fn in (builder.build_dc3, builder.build_dc7):
+            sa = fn(d)
+            torch.cuda.synchronize()
+            assert np.array_equal(sa.cpu().numpy().view(np.uint32), oracle.sa(t, parallel=True))
