@@ -274,6 +274,7 @@ void sort_passes(sa_ctx* c, const Bufs& bf, u64 bound, int npass, int vals_prese
 // then asks for the work to be repeated with force_lsd.
 void run_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_present, int slot,
               hipStream_t s, bool any_order = false);
+constexpr u64 kSplitRoundMin = u64(1) << 21;  // active suffixes of a later round that may take it
 bool split_usable(const sa_ctx* c, u64 count);
 sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_present, int slot,
                      hipStream_t s);

@@ -376,8 +376,10 @@ void enqueue_quad_round(sa_ctx* c, const LaterRound& L, bool reserve, int log_ro
   run_rerank(c, L.bufs, a, L.d_sa, L.bound, trace_count, s);
 }
 
+// split_count != 0: the round's count, known to the host, is sorted by the split
+// sort (log_row >= 0 then).
 void enqueue_later_round(sa_ctx* c, const LaterRound& L, bool reserve, int log_row,
-                         u64 trace_count, bool trace_dense, hipStream_t s) {
+                         u64 trace_count, bool trace_dense, hipStream_t s, u64 split_count = 0) {
   if (L.quad) {
     enqueue_quad_round(c, L, reserve, log_row, trace_count, trace_dense, s);
     return;
@@ -396,7 +398,10 @@ void enqueue_later_round(sa_ctx* c, const LaterRound& L, bool reserve, int log_r
       launch_pack_pairs(c->act_idx, c->act_rank, c->ctl, c->rc, L.n, L.b, c->isa, L.bufs.kA,
                         L.bufs.vA, grid, s);
   }
-  sort_passes(c, L.bufs, L.bound, L.npass, 1, log_row, trace_count, s);
+  if (split_count)
+    (void)split_sort(c, L.bufs, split_count, L.npass, trace_dense ? 0 : 1, log_row, s);
+  else
+    sort_passes(c, L.bufs, L.bound, L.npass, 1, log_row, trace_count, s);
   run_rerank(c, L.bufs, single_args(L.bound, L.n, L.b, kRerankScatterIsa), L.d_sa, L.bound,
              trace_count, s);
 }
@@ -582,7 +587,13 @@ sa_status build_rounds(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_
     if (max_rounds) todo = std::min<u32>(todo, max_rounds - info.rounds);
     todo = std::min<u32>(todo, u32(SA_MAX_ROUNDS - 1) - done);
     if (todo == 0) return SA_EDEVICE;  // cannot happen for n < 2^32
-    hipGraphExec_t exec = use_graphs ? later_graph(c, L) : nullptr;
+    // A large round goes to the split sort, whose shape follows the count: one
+    // round per readback, as in tracing.
+    const bool dense_now = L.dense_n && 4 * active >= 3 * L.dense_n;
+    const u64 now_count = dense_now ? n : active;
+    const bool split = !quad && active >= kSplitRoundMin && split_usable(c, now_count);
+    if (split) todo = 1;
+    hipGraphExec_t exec = use_graphs && !split ? later_graph(c, L) : nullptr;
     if (exec) {
       reserve_gens(c, u32(L.npass) * todo * (quad ? 2u : 1u), s);
       for (u32 r = 0; r < todo; ++r)
@@ -590,11 +601,11 @@ sa_status build_rounds(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_
       c->graph_launches += todo;
       info.graph_rounds += todo;
     } else {
-      // With tracing (one round per readback) the host knows the round's count.
-      const bool dense = L.dense_n && 4 * active >= 3 * L.dense_n;
+      // With one round per readback the host knows the round's count.
+      const bool known = trace || split;
       for (u32 r = 0; r < todo; ++r)
-        enqueue_later_round(c, L, true, trace ? int(done + 1 + r) : -1,
-                            trace ? (dense ? n : active) : 0, dense, s);
+        enqueue_later_round(c, L, true, known ? int(done + 1 + r) : -1, known ? now_count : 0,
+                            dense_now, s, split ? now_count : 0);
     }
     st = readback(c, s);
     if (st != SA_OK) return st;
@@ -611,7 +622,7 @@ sa_status build_rounds(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_
     info.rounds = 1 + done;
     info.prefix_len = chars0 << ((quad ? 2 : 1) * done);
     active = c->h_counters[kCtrActive];
-    if (!c->rounds_ahead) ahead = std::min<u32>(2 * ahead, 16);
+    if (!c->rounds_ahead && !split) ahead = std::min<u32>(2 * ahead, 16);
   }
   if (d_isa) {
     if (lazy)

@@ -47,10 +47,11 @@ namespace {
 constexpr int kSplitBlock = 512;
 constexpr int kSplitMaxLogD = 10;
 constexpr u32 kSplitMaxD = 1u << kSplitMaxLogD;
-constexpr u32 kSplitCap = 3840;       // pairs of a bucket sorted in LDS
+constexpr u32 kSplitOne = 3840;       // pairs of an input sorted as one bucket
+constexpr u32 kSplitCap = 9216;       // pairs of a bucket sorted in LDS at most
 constexpr u32 kSplitRankMax = 8192;   // samples sorted by counting
 constexpr u32 kSplitXcds = 8;
-constexpr int kPosBits = 12;          // a place in a bucket
+constexpr int kPosBits = 14;          // a place in a bucket
 static_assert(kSplitCap <= 1u << kPosBits, "places");
 constexpr int kSearchGang = 4;        // searches of a thread side by side
 
@@ -606,13 +607,13 @@ void split_local_kernel(
     u64* __restrict__ keys, u32* __restrict__ vals, u32 count, u32 nbuckets,
     const u32* __restrict__ start, const u64* __restrict__ splitters, u32* __restrict__ big,
     int from_list, int iota, u64* __restrict__ counters) {
-  constexpr int IT = (CAP + BLOCK - 1) / BLOCK;
+  constexpr int IT = (CAP + BLOCK * kSearchGang - 1) / (BLOCK * kSearchGang) * kSearchGang;
   constexpr int P = BLOCK;          // parts, and samples
   constexpr int NW = BLOCK / kWave;
   constexpr int LOGP = __builtin_ctz(P);
   constexpr int PER = P / kWave;    // parts per lane of the scanning wave
   constexpr int GANG = 2;           // counts of a thread side by side
-  static_assert(IT % kSearchGang == 0 && IT % GANG == 0, "whole gangs");
+  static_assert(kSearchGang % GANG == 0, "whole gangs");
   typedef typename std::conditional<(P <= 256), u8, u16>::type Part;
   __shared__ u64 s_key[CAP + 4];
   __shared__ u32 s_val[CAP];
@@ -882,7 +883,7 @@ SplitShape split_shape(u64 count) {
   SplitShape S{};
   S.count = u32(count);
   int lf = 0;
-  if (count > kSplitCap) {
+  if (count > kSplitOne) {
     // Buckets of at most 512 pairs on average; of up to 1024 where one sweep then
     // does for two, and above 2^29 pairs.
     while (lf < 2 * kSplitMaxLogD && (count >> 9) > (u64(1) << lf)) ++lf;
@@ -984,7 +985,7 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, int iota, Carve
   u32* vout = bf.vA;
   if (!sweeps) {
     Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (iota ? 20.0 : 24.0));
-    hipLaunchKernelGGL((split_local_kernel<int(kSplitCap), kSplitBlock>), dim3(1),
+    hipLaunchKernelGGL((split_local_kernel<int(kSplitOne), kSplitBlock>), dim3(1),
                        dim3(kSplitBlock), 0, s, bf.kA, bf.vA, u32(count), 1u, nullptr, nullptr,
                        nullptr, 0, iota, ctr);
   } else {
@@ -1065,8 +1066,8 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, int iota, Carve
       hipLaunchKernelGGL((split_local_kernel<2032, 256>),
                          dim3(std::min<u32>(nb, u32(c->num_cus) * 5)), dim3(256), 0, s, kout, vout,
                          u32(count), nb, A.start, A.splitters, A.big, 0, 0, ctr);
-    hipLaunchKernelGGL((split_local_kernel<int(kSplitCap), kSplitBlock>),
-                       dim3(std::min<u32>(nb, u32(c->num_cus) * 2)), dim3(kSplitBlock), 0, s,
+    hipLaunchKernelGGL((split_local_kernel<int(kSplitCap), 1024>),
+                       dim3(std::min<u32>(nb, u32(c->num_cus))), dim3(1024), 0, s,
                        kout, vout, u32(count), nb, A.start, A.splitters, A.big, 1, 0, ctr);
   }
   if (top) {

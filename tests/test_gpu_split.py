@@ -14,7 +14,7 @@ from paper_1610_03007_amd import SuffixArrayBuilder
 
 pytestmark = pytest.mark.gpu
 
-LDS_PAIRS = 3840
+LDS_PAIRS = 3840  # an input of one bucket
 
 
 @pytest.fixture(scope="module")
@@ -82,6 +82,18 @@ def test_overflow_repeats_with_lsd(builder):
     finally:
         builder.set_trace(False)
     assert many > few + 4, (few, many)
+
+
+@pytest.mark.parametrize("copies,n", [(400, (1 << 21) + 12345), (5000, 1 << 22)])
+def test_later_rounds(builder, copies, n):
+    """Rounds of more than 2^21 active suffixes: dense ones (every suffix, values
+    generated) and ones over the list of survivors, with the names of each round."""
+    rng = np.random.default_rng(copies)
+    t = np.tile(rng.integers(0, 96, n // copies + 1), copies)[:n].astype(np.uint8)
+    t[rng.integers(0, n, 40)] = 97
+    check(builder, t)
+    info = builder.last_info()
+    assert info["rounds"] > 4 and info["dense_rounds"]
 
 
 def test_batch_and_dc_builds(builder):
