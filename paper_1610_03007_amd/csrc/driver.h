@@ -278,6 +278,14 @@ constexpr u64 kSplitRoundMin = u64(1) << 21;  // active suffixes of a later roun
 bool split_usable(const sa_ctx* c, u64 count);
 sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_present, int slot,
                      hipStream_t s);
+// Round 0 of one text, or of a batch whose round-0 keys are packed (text slot at
+// idshift, texts in slot order), from the keys' sort to the active list in one go:
+// sorted keys in the plan's final buffer, their positions in d_sa (in place of a
+// value buffer), the suffixes whose key is not unique in the active list. The ISA's
+// memory is scratch. Only where split_usable().
+sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, hipStream_t s);
+sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u64* tbase, int idshift, u32* d_sa,
+                       hipStream_t s);
 // Runs a whole build; once more with the LSD sort if the split sort overflowed.
 template <typename F>
 sa_status with_lsd_repeat(sa_ctx* c, F&& build) {

@@ -93,6 +93,7 @@ struct Engine {
   // ISA; it is then formed eagerly (an ISA-only second pass of the round-0
   // re-rank) or, when few suffixes survive, lazily.
   bool defer_round0_isa = false;
+  bool fused = false;          // round 0 ran fused (split_batch0)
   bool lazy = false;           // the ISA holds the survivors' names only (live bitmap)
   const u64* keys0 = nullptr;  // lazy: round-0 sorted keys
   Bufs later{};                // lazy: later rounds' buffers, carved from the spare keys
@@ -263,8 +264,15 @@ struct Engine {
           launch_multi_pack_pairs(c->act_ti, c->act_rank, active, tab, B, idshift, c->isa,
                                   c->keysA + A0, c->valsA + A0, s);
       }
+      fused = defer_round0_isa && m && !active && split_usable(c, total);
       if (total) {
-        run_sort(c, bufs, total, npass_for(c, 64), 1, slot_info, s, true);
+        if (fused) {
+          const sa_status fs =
+              split_batch0(c, total, npass_for(c, 64), tab.base, round0_shift, sa_arena, s);
+          if (fs != SA_OK) return fs;
+        } else {
+          run_sort(c, bufs, total, npass_for(c, 64), 1, slot_info, s, true);
+        }
         RerankArgs a{};
         a.count = total;
         a.n = 0;
@@ -277,7 +285,7 @@ struct Engine {
         a.tlen = tab.len;
         a.tround0 = tab.round0;
         a.tstart = tab.start;
-        run_rerank(c, bufs, a, sa_arena, total, total, s);
+        if (!fused) run_rerank(c, bufs, a, sa_arena, total, total, s);
         last_args = a;
         // Survivors per text; their number is read on the device.
         Tracer tr(c, s, SA_KERNEL_OTHER, 0);
@@ -316,7 +324,7 @@ struct Engine {
   // ISA eagerly (every name), or lazily (survivors only) when at most
   // 1/lazy_ratio of the n suffixes survive and the later rounds' buffers fit in
   // the spare keys (the context's ISA mode may force either form).
-  sa_status form_isa_after_round0(u64 n, hipStream_t s) {
+  sa_status form_isa_after_round0(u64 n, u32* d_sa, hipStream_t s) {
     const u32 f0 = final_buf_of(c, 0);
     const u64* k0 = f0 ? c->keysB : c->keysA;
     u64* spare = f0 ? c->keysA : c->keysB;
@@ -343,7 +351,10 @@ struct Engine {
       // writing only the ISA.
       RerankArgs a = last_args;
       a.mode = kRerankScatterIsa | kRerankIsaOnly;
-      run_rerank(c, full_bufs(c), a, nullptr, a.count, a.count, s);
+      // (After a fused round 0 the sorted positions are in the SA.)
+      Bufs sorted = full_bufs(c);
+      if (fused) sorted.vA = sorted.vB = d_sa;
+      run_rerank(c, sorted, a, nullptr, a.count, a.count, s);
     }
     return SA_OK;
   }
@@ -427,7 +438,7 @@ sa_status build_batch_impl(sa_ctx* c, const u8* text, const u64* h_off, u32 T, u
     info.rounds = u32(r + 1);
     in_round = eng.active;
     if (r == 0) {
-      st = eng.form_isa_after_round0(N, s);
+      st = eng.form_isa_after_round0(N, d_sa, s);
       if (st != SA_OK) return st;
       eng.defer_round0_isa = false;
       info.lazy_isa = eng.lazy ? 1u : 0u;

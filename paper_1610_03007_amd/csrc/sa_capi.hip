@@ -500,13 +500,21 @@ sa_status build_rounds(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_
     launch_byte_presence(text, n, c->present, s);
     launch_alphabet_codes(c->present, c->code, c->counters, c->round0_trim, 0, c->radix_bits, s);
   }
-  {
-    Tracer t(c, s, SA_KERNEL_PACK_TEXT, double(n) * 9.0);
-    launch_pack_text(text, n, c->code, c->counters, c->keysA, s);
-  }
   const int npass0 = npass_for(c, 64);
-  run_sort(c, full, n, npass0, 0, 0, s, true);
-  run_rerank(c, full, single_args(n, n, 0, 0), d_sa, n, n, s);
+  // The fused round 0 writes every place of the SA, so a build that may stop early
+  // (whose unfinished places the caller keeps) does not take it.
+  const bool fused = max_rounds == 0 && split_usable(c, n);
+  if (fused) {
+    st = split_round0(c, text, n, npass0, d_sa, s);
+    if (st != SA_OK) return st;
+  } else {
+    {
+      Tracer t(c, s, SA_KERNEL_PACK_TEXT, double(n) * 9.0);
+      launch_pack_text(text, n, c->code, c->counters, c->keysA, s);
+    }
+    run_sort(c, full, n, npass0, 0, 0, s, true);
+    run_rerank(c, full, single_args(n, n, 0, 0), d_sa, n, n, s);
+  }
   st = readback(c, s);
   if (st != SA_OK) return st;
 
@@ -548,7 +556,10 @@ sa_status build_rounds(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_
       launch_isa_scatter_list(c->act_idx, c->act_rank, active, n, c->isa, c->live, s);
       launch_lazy_sample(keys0, n, c->sample, s);
     } else {
-      run_rerank(c, full, single_args(n, n, 0, kRerankScatterIsa | kRerankIsaOnly), d_sa, n, n,
+      // (After a fused round 0 the sorted positions are in the SA.)
+      Bufs sorted = full;
+      if (fused) sorted.vA = sorted.vB = d_sa;
+      run_rerank(c, sorted, single_args(n, n, 0, kRerankScatterIsa | kRerankIsaOnly), d_sa, n, n,
                  s);
     }
   }

@@ -20,9 +20,9 @@
 //      part by counting the smaller keys.
 //
 // Measured on MI355X for the 2^28 round-0 keys of a Markov text (7 varying bytes):
-// 8.0 ms (sample 0.4, histograms 0.5 + 0.5, sweeps 1.8 + 1.6, LDS 3.3) against
-// 12.1 ms for seven LSD sweeps of 1.68 ms and their histogram. For 2^20 DNA keys
-// 0.11 ms against 0.22, for 2^16 keys 0.05 against 0.11.
+// 6.8 ms from the text to the SA and the survivors (sample 0.4, histograms 0.5 + 0.5,
+// sweeps 1.8 + 1.7, LDS 3.0) against 14.2 ms for packing, histogram, seven LSD sweeps
+// of 1.68 ms and the re-rank.
 //
 // Bucket counts come from a histogram before each sweep; a tile reserves its
 // part of each bucket with one atomic add per bucket, so the order among equal
@@ -51,6 +51,9 @@ constexpr u32 kSplitOne = 3840;       // pairs of an input sorted as one bucket
 constexpr u32 kSplitCap = 9216;       // pairs of a bucket sorted in LDS at most
 constexpr u32 kSplitRankMax = 8192;   // samples sorted by counting
 constexpr u32 kSplitXcds = 8;
+// Pairs per thread of a sweep over a large input: two workgroups a CU with 1024
+// buckets. (8 and 10 give three and two, and 2-5% longer builds: shorter runs.)
+constexpr int kSweepItems = 12;
 constexpr int kPosBits = 14;          // a place in a bucket
 static_assert(kSplitCap <= 1u << kPosBits, "places");
 constexpr int kSearchGang = 4;        // searches of a thread side by side
@@ -144,6 +147,13 @@ struct SplitShape {
   u32 nb() const { return 1u << (log1 + log2); }
 };
 
+// An equality bucket of a round 0 (see split_equal_list_kernel).
+constexpr u32 kEqualPiece = 4096;
+struct SplitEqual {
+  u32 bucket, piece0;
+  u64 out;  // first slot of the active list
+};
+
 // Device arrays of one split sort.
 struct SplitArrays {
   u64* splitters;  // [F], ascending, the last all ones
@@ -156,7 +166,73 @@ struct SplitArrays {
   u32* start1;     // [D1 + 1] first pair of each group of buckets
   u32* tile0;      // [D1 + 1] first tile of the second sweep of each group
   u32* start;      // [F + 1] first pair of each bucket
-  u32* big;        // number of buckets left to the large local sort, then those
+  u32 *big, *big2;  // number of buckets left to the larger local sorts, then those
+  unsigned long long* equal_head;  // round 0: the listed equality buckets
+  SplitEqual* equal;               // [F]
+};
+
+// Round-0 keys read straight from a text (text == nullptr: from memory): key i is
+// the codes of text[i, i + c), w bits each, 0 past the end.
+struct SplitText {
+  const u8* text;
+  const u16* code;
+  const u64* counters;  // kCtrCodeBits, kCtrChars
+  int words;            // the text is 4-byte aligned
+};
+constexpr int kKeyHalo = 64;  // c <= 64
+
+// The keys of positions base + ITEMS tid .. + ITEMS - 1 of a tile of ITEMS per
+// thread, rolled from the tile's codes in LDS. (Every thread calls; s_sym holds the
+// codes of the tile and of kKeyHalo positions more.)
+template <int ITEMS>
+__device__ inline void text_keys(const SplitText& T, u32 base, u32 count, u16* s_code, u16* s_sym,
+                                 u64 (&key)[ITEMS]) {
+  constexpr u32 SPAN = u32(ITEMS) * kSplitBlock + kKeyHalo;
+  const u32 tid = threadIdx.x;
+  const u32 w = u32(T.counters[kCtrCodeBits]);
+  const u32 c = u32(T.counters[kCtrChars]);
+  if (tid < 256) s_code[tid] = T.code[tid];
+  __syncthreads();
+  if (T.words && u64(base) + SPAN <= count) {
+    const u32* tw = reinterpret_cast<const u32*>(T.text + base);
+    for (u32 q = tid; q < SPAN / 4; q += kSplitBlock) {
+      const u32 v = tw[q];
+      s_sym[4 * q] = s_code[v & 0xFFu];
+      s_sym[4 * q + 1] = s_code[(v >> 8) & 0xFFu];
+      s_sym[4 * q + 2] = s_code[(v >> 16) & 0xFFu];
+      s_sym[4 * q + 3] = s_code[v >> 24];
+    }
+  } else {
+    for (u32 i = tid; i < SPAN; i += kSplitBlock) {
+      const u64 p = u64(base) + i;
+      s_sym[i] = p < count ? s_code[T.text[p]] : u16(0);
+    }
+  }
+  __syncthreads();
+  const u64 mask = c * w >= 64 ? ~u64(0) : (u64(1) << (c * w)) - 1;
+  const u32 first = tid * ITEMS;
+  u64 k = 0;
+  for (u32 j = 0; j < c; ++j) k = (k << w) | s_sym[first + j];
+  key[0] = k;
+#pragma unroll
+  for (int j = 1; j < ITEMS; ++j) {
+    k = ((k << w) | s_sym[first + j + c - 1]) & mask;
+    key[j] = k;
+  }
+}
+
+// What the bucket sorts of a round 0 write besides the sorted keys: SA[place] =
+// position for every suffix (a survivor's entry is overwritten when its name
+// becomes unique), and the suffixes whose key is not unique as the active list.
+// In a batch (tbase set) the key's top bits name the text, positions and names are
+// local to it, and the texts' suffixes fill the sorted array in slot order.
+struct SplitFinal {
+  u32* sa;  // nullptr: a plain sort
+  u32* act_idx;
+  u64* act_ti;  // batch: (text << 32) | position
+  u32* act_rank;
+  const u64* tbase;
+  int idshift;
 };
 
 // First kernel: control words of the sort and cleared counts.
@@ -174,15 +250,31 @@ __global__ __launch_bounds__(256) void split_begin_kernel(SortCtl* __restrict__ 
 }
 
 // Sample i: the key of a position drawn in the i-th of `samples` equal stretches.
-__global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict__ keys, u32 count,
-                                                           u32 samples, u64* __restrict__ out) {
+__global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict__ keys,
+                                                           SplitText T, u32 count, u32 samples,
+                                                           u64* __restrict__ out) {
+  __shared__ u16 s_code[256];
+  if (T.text) {
+    s_code[threadIdx.x] = T.code[threadIdx.x];
+    __syncthreads();
+  }
   const u32 i = blockIdx.x * 256 + threadIdx.x;
   if (i >= samples) return;
   const u32 lo = u32(u64(i) * count / samples), hi = u32(u64(i + 1) * count / samples);
   const u32 w = hi > lo ? hi - lo : 1;
   u32 p = lo + mix32(i + 0x9e3779b9u) % w;
   if (p >= count) p = count - 1;
-  out[i] = keys[p];
+  if (!T.text) {
+    out[i] = keys[p];
+    return;
+  }
+  const u32 cw = u32(T.counters[kCtrCodeBits]), c = u32(T.counters[kCtrChars]);
+  u64 k = 0;
+  for (u32 q = 0; q < c; ++q) {
+    const u64 x = u64(p) + q;
+    k = (k << cw) | (x < count ? s_code[T.text[x]] : u16(0));
+  }
+  out[i] = k;
 }
 
 // Sorts up to kSplitRankMax samples by counting, for each, the smaller ones
@@ -225,6 +317,7 @@ __global__ __launch_bounds__(256) void split_pick_kernel(const u64* __restrict__
     return i + 1 < f && q < samples ? sorted[q] : ~u64(0);
   };
   const u32 i = blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) A.big[0] = A.big2[0] = 0;
   if (i < f) A.splitters[i] = at(i);
   const u32 d1 = 1u << log1;
   if (blockIdx.x * 256 < d1) {
@@ -294,11 +387,15 @@ __device__ inline void load_splitters(const SplitArrays& A, u32 row, int logd, u
 }
 
 // Counts per bucket. Bound by the key reads (8 bytes a pair) and the search:
-// log2(D) LDS reads a pair. Level 1 also ORs the keys and their complements.
-template <int ITEMS, bool SECOND>
+// log2(D) LDS reads a pair; from a text, by one byte a pair and the search. Level 1
+// also ORs the keys and their complements.
+template <int ITEMS, bool SECOND, bool TEXT>
 __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __restrict__ keys,
-                                                                 SplitShape S, SplitArrays A,
+                                                                 SplitText T, SplitShape S,
+                                                                 SplitArrays A,
                                                                  u64* __restrict__ counters) {
+  __shared__ u16 s_code[TEXT ? 256 : 1];
+  __shared__ u16 s_sym[TEXT ? ITEMS * kSplitBlock + kKeyHalo : 1];
   __shared__ u64 s_sp[kSplitMaxD];
   __shared__ u32 s_cnt[kSplitMaxD];
   __shared__ u32 s_fl[kSplitMaxD / 32];
@@ -336,16 +433,21 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
       n = S.count - base < TILE ? S.count - base : TILE;
     }
     u64 key[ITEMS];
+    if constexpr (TEXT) {
+      text_keys<ITEMS>(T, base, S.count, s_code, s_sym, key);
+      __syncthreads();  // the next tile's codes go to the same place
+    } else {
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      const u32 e = u32(j) * kSplitBlock + tid;
-      key[j] = e < n ? keys[u64(base) + e] : 0;
+      for (int j = 0; j < ITEMS; ++j) {
+        const u32 e = u32(j) * kSplitBlock + tid;
+        key[j] = e < n ? keys[u64(base) + e] : 0;
+      }
     }
     u32 bk[ITEMS];
     buckets_of<ITEMS>(s_sp, s_fl, logd, key, bk);
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
-      const u32 e = u32(j) * kSplitBlock + tid;
+      const u32 e = TEXT ? tid * ITEMS + j : u32(j) * kSplitBlock + tid;
       if (e < n) {
         atomicAdd(&s_cnt[bk[j]], 1u);
         if (!SECOND) {
@@ -389,15 +491,18 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
 // generated), each bucket's run of a tile written contiguously from LDS. A pair's
 // place in its run is its LDS fetch-add on the bucket's count (no order among
 // equal keys is kept, which saves the LSD sweep's ballots).
-// ITEMS = 12 fills 78 KB of LDS at 1024 buckets (two workgroups a CU).
-template <int ITEMS, bool SECOND>
+// 2^28 suffixes: 1.8 ms from the text (13 bytes a suffix), 1.7 ms the second sweep
+// (24 bytes, 3.8 TB/s).
+template <int ITEMS, bool SECOND, bool TEXT>
 __global__ __launch_bounds__(kSplitBlock) __attribute__((amdgpu_waves_per_eu(4)))
 void split_sweep_kernel(
-    const u64* __restrict__ kin, const u32* __restrict__ vin, u64* __restrict__ kout,
+    const u64* __restrict__ kin, const u32* __restrict__ vin, SplitText T, u64* __restrict__ kout,
     u32* __restrict__ vout, SplitShape S, SplitArrays A, int iota, u64* __restrict__ counters) {
   constexpr u32 TILE = u32(ITEMS) * kSplitBlock;
   static_assert(kSplitMaxD <= 2 * kSplitBlock, "two buckets per thread");
-  __shared__ u64 s_buf[TILE];       // keys, then values
+  __shared__ u64 s_buf[TILE];       // codes of a text, then keys, then values
+  static_assert(2 * (TILE + kKeyHalo) <= 8 * TILE, "the tile's codes fit");
+  __shared__ u16 s_code[TEXT ? 256 : 1];
   __shared__ u16 s_dig[TILE];
   __shared__ u64 s_sp[kSplitMaxD];  // splitters, then (as u32) the output offsets
   __shared__ u32 s_cnt[kSplitMaxD];
@@ -420,18 +525,27 @@ void split_sweep_kernel(
     t.base = u32(b);
     t.n = S.count - t.base < TILE ? S.count - t.base : TILE;
   }
-  // The tile's pairs are requested first.
+  // The tile's pairs are requested first. Item j of a thread: striped over the
+  // threads, or (from a text) consecutive.
+  auto item = [&](int j) { return TEXT ? tid * ITEMS + j : u32(j) * kSplitBlock + tid; };
   u64 key[ITEMS];
   u32 val[ITEMS];
+  if constexpr (TEXT) {
+    text_keys<ITEMS>(T, t.base, S.count, s_code, reinterpret_cast<u16*>(s_buf), key);
 #pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    const u32 e = u32(j) * kSplitBlock + tid;
-    key[j] = e < t.n ? __builtin_nontemporal_load(kin + t.base + e) : 0;
-  }
+    for (int j = 0; j < ITEMS; ++j) val[j] = t.base + item(j);
+  } else {
 #pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    const u32 e = u32(j) * kSplitBlock + tid;
-    val[j] = iota ? t.base + e : (vin && e < t.n) ? __builtin_nontemporal_load(vin + t.base + e) : 0;
+    for (int j = 0; j < ITEMS; ++j) {
+      const u32 e = item(j);
+      key[j] = e < t.n ? __builtin_nontemporal_load(kin + t.base + e) : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const u32 e = item(j);
+      val[j] =
+          iota ? t.base + e : (vin && e < t.n) ? __builtin_nontemporal_load(vin + t.base + e) : 0;
+    }
   }
   load_splitters<SECOND>(A, t.row, logd, s_sp, s_fl);
   for (u32 i = tid; i < d; i += kSplitBlock) s_cnt[i] = 0;
@@ -480,8 +594,7 @@ void split_sweep_kernel(
   buckets_of<ITEMS>(s_sp, s_fl, logd, key, place);
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j) {
-    const u32 e = u32(j) * kSplitBlock + tid;
-    rank[j] = e < t.n ? atomicAdd(&s_cnt[place[j]], 1u) : 0u;
+    rank[j] = item(j) < t.n ? atomicAdd(&s_cnt[place[j]], 1u) : 0u;
   }
   __syncthreads();
   u32 cnt[2] = {0, 0}, off[2] = {0, 0};
@@ -508,8 +621,7 @@ void split_sweep_kernel(
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j) {
-    const u32 e = u32(j) * kSplitBlock + tid;
-    if (e < t.n) {
+    if (item(j) < t.n) {
       const u32 b = place[j];
       const u32 p = s_cnt[b] + rank[j];  // < t.n: the counts of the tile sum to t.n
       place[j] = p;
@@ -536,8 +648,7 @@ void split_sweep_kernel(
   u32* s_val = reinterpret_cast<u32*>(s_buf);
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j) {
-    const u32 e = u32(j) * kSplitBlock + tid;
-    if (e < t.n) s_val[place[j]] = val[j];
+    if (item(j) < t.n) s_val[place[j]] = val[j];
   }
   __syncthreads();
 #pragma unroll
@@ -596,17 +707,24 @@ __device__ inline u64 wave_sort(u64 v) {
 // are requested as soon as this one's are in LDS, and a workgroup is small (two
 // waves and ten workgroups a CU for buckets of 512, four and five for 1024) so
 // that others work while one waits.
-// A bucket of more than CAP pairs goes to the list `big` for a launch of the
-// larger shape (which takes its buckets from there: from_list), or if there is no
-// list raises kCtrSplitOver. start == nullptr: the whole input (count <= CAP) is
+// A bucket of more than CAP pairs goes to the list `big` for a launch of a larger
+// shape (which takes its buckets from there: `from`), or if there is no list raises
+// kCtrSplitOver. start == nullptr: the whole input (count <= CAP) is
 // the one bucket, with generated values when iota is set and the key ORs left in
 // the counters.
-template <int CAP, int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5)))
+// (2^28 suffixes: 3.0 ms with FINAL, 24 bytes a suffix at 2.1 TB/s; 4.2 ms at 96
+// registers, which spills.)
+// FINAL (a round 0): the sorted pairs leave through LDS in order, which gives every
+// pair its neighbours' keys: its name if it is not unique, as the re-rank would
+// find it, without another pass over the pairs. The name is 1 + the first place of
+// its run of equal keys, which lies in this bucket.
+template <int CAP, int BLOCK, bool FINAL>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
 void split_local_kernel(
     u64* __restrict__ keys, u32* __restrict__ vals, u32 count, u32 nbuckets,
-    const u32* __restrict__ start, const u64* __restrict__ splitters, u32* __restrict__ big,
-    int from_list, int iota, u64* __restrict__ counters) {
+    const u32* __restrict__ start, const u64* __restrict__ splitters,
+    const u32* __restrict__ from, u32* __restrict__ big, int iota, SplitFinal fin,
+    u64* __restrict__ counters) {
   constexpr int IT = (CAP + BLOCK * kSearchGang - 1) / (BLOCK * kSearchGang) * kSearchGang;
   constexpr int P = BLOCK;          // parts, and samples
   constexpr int NW = BLOCK / kWave;
@@ -623,10 +741,12 @@ void split_local_kernel(
   __shared__ u32 s_cnt[P];
   __shared__ u32 s_off[P + 1];
   __shared__ u32 s_fl[P / 32];
+  __shared__ u32 s_left, s_taken;  // FINAL: survivors of the bucket
+  __shared__ u64 s_out;
   const u32 tid = threadIdx.x;
-  if (from_list) {
-    nbuckets = big[0];
-    if (nbuckets == 0) return;
+  if (from) {
+    nbuckets = from[0];
+    if (blockIdx.x >= nbuckets) return;
   }
   // Bucket w of the launch: its first pair, its size (0: nothing to sort), the
   // key below it and whether its keys, less that one, leave the low kPosBits
@@ -641,7 +761,7 @@ void split_local_kernel(
       m = count;
       return;
     }
-    const u32 f = from_list ? big[1 + w] : w;
+    const u32 f = from ? from[1 + w] : w;
     a = start[f];
     const u32 z = start[f + 1];
     low = f > 0 ? splitters[f - 1] : 0;
@@ -652,11 +772,12 @@ void split_local_kernel(
       if (tid == 0) flag(counters, kErrBounds);
       return;
     }
-    // An equality bucket is in order already, and so is a single pair.
-    if (z - a <= 1 || same) return;
+    // An equality bucket is in order already, and so is a single pair. (FINAL:
+    // split_equal_kernel takes the equality buckets, this kernel every other.)
+    if (z == a || same || (!FINAL && z - a == 1)) return;
     if (z - a > u32(CAP)) {
       if (tid == 0) {
-        if (big && !from_list)
+        if (big)
           big[1 + atomicAdd(&big[0], 1u)] = f;
         else
           counters[kCtrSplitOver] = 1;
@@ -675,7 +796,7 @@ void split_local_kernel(
       val[j] = 0;
       if (e < m) {
         key[j] = keys[u64(a) + e];
-        val[j] = iota ? e : vals ? vals[u64(a) + e] : 0;
+        val[j] = !start && iota ? e : vals ? vals[u64(a) + e] : 0;
       }
     }
   };
@@ -793,10 +914,12 @@ void split_local_kernel(
     }
     if (tid < 4u) s_key[m + tid] = ~u64(0);  // read, never counted, by the last part
     __syncthreads();
-    load(na, nm);
+    if (!FINAL) load(na, nm);
     // Pair q: its place is its part's start plus the smaller keys of the part.
     // (Parts are ordered: keys read past the part's end are larger.) A part of
     // equal keys is in order already.
+    u64 kk[FINAL ? IT : 1];
+    u32 place[FINAL ? IT : 1];
 #pragma unroll
     for (int j = 0; j < IT; j += GANG) {
       if (u32(j) * BLOCK >= m) break;  // uniform
@@ -842,9 +965,78 @@ void split_local_kernel(
 #pragma unroll
       for (int y = 0; y < GANG; ++y) {
         const u32 q = u32(j + y) * BLOCK + tid;
-        if (q < m) {
+        if constexpr (FINAL) {
+          kk[j + y] = k[y];
+          place[j + y] = at[y];
+        } else if (q < m) {
           keys[u64(a) + at[y]] = narrow ? (k[y] >> kPosBits) + low : k[y];
           if (vals) vals[u64(a) + at[y]] = s_val[q];
+        }
+      }
+    }
+    if constexpr (FINAL) {
+      if (tid == 0) s_left = s_taken = 0;
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < IT; ++j) {
+        const u32 q = u32(j) * BLOCK + tid;
+        if (q < m) s_key[place[j]] = kk[j];
+        if (!narrow && q < m) kk[j] = s_val[q];
+      }
+      __syncthreads();
+      if (!narrow) {  // (a narrow key names its value's place)
+#pragma unroll
+        for (int j = 0; j < IT; ++j)
+          if (u32(j) * BLOCK + tid < m) s_val[place[j]] = u32(kk[j]);
+        __syncthreads();
+      }
+      load(na, nm);
+      constexpr u32 PMASK = (1u << kPosBits) - 1;
+      const int sh = narrow ? kPosBits : 0;
+      u32 same = 0;  // bit j: item j shares its key with a neighbour
+#pragma unroll
+      for (int j = 0; j < IT; ++j) {
+        const u32 q = u32(j) * BLOCK + tid;
+        if (q < m) {
+          const u64 x = s_key[q], k = x >> sh;
+          const bool dup =
+              (q > 0 && s_key[q - 1] >> sh == k) || (q + 1 < m && s_key[q + 1] >> sh == k);
+          same |= dup ? 1u << j : 0u;
+          keys[u64(a) + q] = narrow ? k + low : k;
+          fin.sa[u64(a) + q] = s_val[narrow ? u32(x) & PMASK : q];
+        }
+      }
+      if (same) atomicAdd(&s_left, u32(__popc(same)));
+      __syncthreads();
+      const u32 left = s_left;
+      if (left) {  // uniform
+        if (tid == 0)
+          s_out = atomicAdd(reinterpret_cast<unsigned long long*>(counters + kCtrActive),
+                            (unsigned long long)left);
+        __syncthreads();
+        if (s_out + left > count) {
+          if (tid == 0) flag(counters, kErrBounds);
+        } else {
+#pragma unroll
+          for (int j = 0; j < IT; ++j) {
+            const u32 q = u32(j) * BLOCK + tid;
+            if ((same >> j) & 1u) {
+              const u64 x = s_key[q], k = x >> sh;
+              const u32 v = s_val[narrow ? u32(x) & PMASK : q];
+              u32 h = q;
+              while (h > 0 && s_key[h - 1] >> sh == k) --h;
+              const u64 o = s_out + atomicAdd(&s_taken, 1u);
+              u64 name = u64(a) + h + 1;
+              if (fin.tbase) {
+                const u64 t = (narrow ? k + low : k) >> fin.idshift;
+                name -= fin.tbase[t];
+                fin.act_ti[o] = (t << 32) | v;
+              } else {
+                fin.act_idx[o] = v;
+              }
+              fin.act_rank[o] = u32(name);
+            }
+          }
         }
       }
     }
@@ -854,6 +1046,94 @@ void split_local_kernel(
     low = nlow;
     narrow = nnarrow;
   }
+}
+
+// Round 0, the equality buckets: their pairs are in order, and every suffix of one
+// (unless it is alone) survives under the name of the bucket's first place. First
+// they are listed, with their slots in the active list and their pieces of
+// kEqualPiece pairs numbered in list order; then workgroups take pieces, so that a
+// bucket of any size (a text of one character is one bucket) is spread over all.
+__global__ __launch_bounds__(256) void split_equal_list_kernel(
+    u32 nbuckets, u32 count, const u32* __restrict__ start, const u64* __restrict__ splitters,
+    unsigned long long* __restrict__ head,  // entries << 32 | pieces
+    SplitEqual* __restrict__ list, u64* __restrict__ counters) {
+  const u32 stride = gridDim.x * 256;
+  for (u32 f0 = blockIdx.x * 256; f0 < nbuckets; f0 += stride) {  // uniform trip count
+    const u32 f = f0 + threadIdx.x;
+    u32 m = 0;
+    if (f > 0 && f < nbuckets && splitters[f - 1] == splitters[f]) {
+      const u32 a = start[f], z = start[f + 1];
+      if (z > a && z <= count) m = z - a;
+    }
+    // One pair of atomics per wave.
+    const u64 any = __ballot(m != 0);
+    if (any == 0) continue;  // wave-uniform
+    const u32 pieces = (m + kEqualPiece - 1) / kEqualPiece;
+    const u32 left = m > 1 ? m : 0;
+    const u32 pinc = wave_inclusive_sum(pieces);
+    u64 linc = left;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const u64 t = __shfl_up(linc, off, kWave);
+      if (lane_id() >= off) linc += t;
+    }
+    unsigned long long h = 0, o = 0;
+    if (lane_id() == kWave - 1) {
+      h = atomicAdd(head, ((unsigned long long)__popcll(any) << 32) | pinc);
+      o = atomicAdd(reinterpret_cast<unsigned long long*>(counters + kCtrActive),
+                    (unsigned long long)linc);
+    }
+    h = __shfl(h, kWave - 1, kWave);
+    o = __shfl(o, kWave - 1, kWave);
+    if (m) {
+      const u32 e = u32(h >> 32) + u32(__popcll(any & ((u64(1) << lane_id()) - 1)));
+      list[e] = SplitEqual{f, u32(h) + pinc - pieces, o + linc - left};
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void split_equal_kernel(
+    const u64* __restrict__ keys, const u32* __restrict__ vals, u32 count,
+    const u32* __restrict__ start, const unsigned long long* __restrict__ head,
+    const SplitEqual* __restrict__ list, SplitFinal fin, u64* __restrict__ counters) {
+  const unsigned long long h = *head;
+  const u32 entries = u32(h >> 32), pieces = u32(h);
+  bool bad = false;
+  for (u32 w = blockIdx.x; w < pieces; w += gridDim.x) {
+    u32 lo = 0, hi = entries;  // the last entry whose pieces start at or before w
+    while (hi - lo > 1) {
+      const u32 mid = (lo + hi) >> 1;
+      if (list[mid].piece0 <= w)
+        lo = mid;
+      else
+        hi = mid;
+    }
+    const SplitEqual e = list[lo];
+    const u32 a = start[e.bucket], m = start[e.bucket + 1] - a;
+    const u32 i0 = (w - e.piece0) * kEqualPiece;
+    const u32 i1 = m - i0 < kEqualPiece ? m : i0 + kEqualPiece;
+    u64 name = u64(a) + 1, t = 0;
+    if (fin.tbase) {
+      t = keys[a] >> fin.idshift;
+      name -= fin.tbase[t];
+    }
+    for (u32 i = i0 + threadIdx.x; i < i1; i += 256) {
+      const u32 v = vals[u64(a) + i];
+      fin.sa[u64(a) + i] = v;
+      if (m == 1) continue;
+      const u64 o = e.out + i;
+      if (o >= count) {
+        bad = true;
+        continue;
+      }
+      if (fin.tbase)
+        fin.act_ti[o] = (t << 32) | v;
+      else
+        fin.act_idx[o] = v;
+      fin.act_rank[o] = u32(name);
+    }
+  }
+  if (bad) flag(counters, kErrBounds);
 }
 
 // The sort's plan as the re-rank and the round log read it: the buffer that
@@ -891,18 +1171,19 @@ SplitShape split_shape(u64 count) {
     // Small inputs: buckets of 256, so that more CUs take part.
     while (lf < kSplitMaxLogD && (count >> 8) > (u64(1) << lf)) ++lf;
   }
-  // One sweep up to 1024 buckets (2^20 pairs); above, two of about equal width.
+  // One sweep up to 1024 buckets; above, two, the second as wide as it can be (its
+  // output stays within one group of buckets, the first one's is all over).
   if (lf <= kSplitMaxLogD) {
     S.log1 = lf;
     S.log2 = 0;
   } else {
-    S.log2 = lf / 2;
+    S.log2 = std::min(kSplitMaxLogD, lf - 3);
     S.log1 = lf - S.log2;
   }
   S.over = lf > kSplitMaxLogD ? 12 : count > (u64(512) << lf) ? 8 : 4;
   S.samples = S.over << lf;
   // Small inputs: small tiles, so that more CUs take part.
-  S.tile = count < (u64(1) << 22) ? 4 * kSplitBlock : 12 * kSplitBlock;
+  S.tile = count < (u64(1) << 22) ? 4 * kSplitBlock : kSweepItems * kSplitBlock;
   S.tiles = u32(ceil_div(count, S.tile));
   S.groups = S.tiles >= 16 * kSplitXcds ? kSplitXcds : 1;
   S.per = (S.tiles + S.groups - 1) / S.groups;
@@ -929,24 +1210,27 @@ struct Carver {
 };
 
 // Arrays of one sort; the counts to clear come first, in one piece.
-SplitArrays carve(Carver& cv, const SplitShape& S, u32** clear, u64* clear_words) {
+SplitArrays carve(Carver& cv, const SplitShape& S, bool final, u32** clear, u64* clear_words) {
   SplitArrays A{};
   const u64 d1 = u64(1) << S.log1, f = S.nb(), rows1 = u64(S.groups) * d1;
-  const u64 words = 2 * rows1 + (S.log2 ? 2 * f : 0) + 1;
-  u32* p = cv.get<u32>(words + f);
+  const u64 words = 4 + 2 * rows1 + (S.log2 ? 2 * f : 0);
+  u32* p = cv.get<u32>(words);
   *clear = p;
   *clear_words = words;
-  A.tot1 = p;
-  A.cur1 = p + rows1;
-  A.tot2 = p + 2 * rows1;
-  A.cur2 = p + 2 * rows1 + f;
-  A.big = p + words - 1;
+  A.equal_head = reinterpret_cast<unsigned long long*>(p);
+  A.tot1 = p + 4;
+  A.cur1 = A.tot1 + rows1;
+  A.tot2 = A.cur1 + rows1;
+  A.cur2 = A.tot2 + f;
   A.splitters = cv.get<u64>(f);
   A.top = cv.get<u64>(d1);
   A.top_flag = cv.get<u32>(ceil_div(d1, 32));
   A.start1 = cv.get<u32>(d1 + 1);
   A.tile0 = cv.get<u32>(d1 + 1);
   A.start = cv.get<u32>(f + 1);
+  A.big = cv.get<u32>(f + 1);
+  A.big2 = cv.get<u32>(f + 1);
+  if (final) A.equal = cv.get<SplitEqual>(f);
   return A;
 }
 
@@ -957,42 +1241,50 @@ namespace drv {
 
 // Sorts `count` pairs in (kA, vA) (values optional) within `cv`'s scratch; the
 // result ends in buffer A or B (*fin). top: the build's own sort, whose control
-// words and plan row are set; otherwise a sort of samples inside one.
-static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, int iota, Carver cv, bool top,
-                           int npass, int log_row, u32* fin, hipStream_t s) {
+// words and plan row are set; otherwise a sort of samples inside one. T.text: the
+// keys are the text's, values the positions; out.sa: a round 0 (see SplitFinal;
+// values generated, or in vA for a batch).
+static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText& T,
+                           const SplitFinal& out, int iota, Carver cv, bool top, int npass,
+                           int log_row, u32* fin, hipStream_t s) {
   const SplitShape S = split_shape(count);
+  const bool final = out.sa != nullptr;
   u32* clear = nullptr;
   u64 words = 0;
-  const SplitArrays A = carve(cv, S, &clear, &words);
-  const bool sweeps = S.log1 > 0;
+  const SplitArrays A = carve(cv, S, final, &clear, &words);
   u64 *sk = nullptr, *sk2 = nullptr;
-  if (sweeps) {
+  if (S.log1) {
     sk = cv.get<u64>(S.samples);
     sk2 = cv.get<u64>(S.samples);
   }
-  if (!cv.ok) return SA_EDEVICE;  // split_fits() has checked this
+  if (!cv.ok) return SA_EDEVICE;  // split_usable() has checked this
   u64* ctr = c->counters;
   u64* const ctr_top = top ? ctr : nullptr;
   *fin = 0;
   {
     Tracer t(c, s, SA_KERNEL_OTHER, 0);
     const u32 g = u32(std::min<u64>(std::max<u64>(1, ceil_div(words, 1024)), 1024));
-    if (top || words)
-      hipLaunchKernelGGL(split_begin_kernel, dim3(g), dim3(256), 0, s, top ? c->ctl : nullptr,
-                         count, clear, words, ctr);
+    hipLaunchKernelGGL(split_begin_kernel, dim3(g), dim3(256), 0, s, top ? c->ctl : nullptr, count,
+                       clear, words, ctr);
   }
-  u64* kout = bf.kA;
-  u32* vout = bf.vA;
-  if (!sweeps) {
+#define SA_LOCAL(CAP, BL, GRID, KEYS, VALS, NB, START, SPL, FROM, BIG)                             \
+  do {                                                                                           \
+    if (final)                                                                                   \
+      hipLaunchKernelGGL((split_local_kernel<CAP, BL, true>), dim3(GRID), dim3(BL), 0, s, KEYS,  \
+                         VALS, u32(count), NB, START, SPL, FROM, BIG, iota, out, ctr);           \
+    else                                                                                         \
+      hipLaunchKernelGGL((split_local_kernel<CAP, BL, false>), dim3(GRID), dim3(BL), 0, s, KEYS, \
+                         VALS, u32(count), NB, START, SPL, FROM, BIG, iota, out, ctr);           \
+  } while (0)
+  if (!S.log1) {
+    if (T.text) launch_pack_text(T.text, count, T.code, T.counters, bf.kA, s);
     Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (iota ? 20.0 : 24.0));
-    hipLaunchKernelGGL((split_local_kernel<int(kSplitOne), kSplitBlock>), dim3(1),
-                       dim3(kSplitBlock), 0, s, bf.kA, bf.vA, u32(count), 1u, nullptr, nullptr,
-                       nullptr, 0, iota, ctr);
+    SA_LOCAL(int(kSplitOne), 512, 1, bf.kA, bf.vA, 1u, nullptr, nullptr, nullptr, nullptr);
   } else {
     {
       Tracer t(c, s, SA_KERNEL_OTHER, 0);
       hipLaunchKernelGGL(split_sample_kernel, dim3(u32(ceil_div(S.samples, 256))), dim3(256), 0, s,
-                         bf.kA, S.count, S.samples, sk);
+                         bf.kA, T, S.count, S.samples, sk);
       u64* sorted = sk2;
       if (S.samples <= kSplitRankMax) {
         hipLaunchKernelGGL(split_rank_kernel, dim3(u32(ceil_div(S.samples, 16))),
@@ -1000,7 +1292,8 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, int iota, Carve
       } else {
         u32 sf = 0;
         const Bufs sb{sk, sk2, nullptr, nullptr};
-        const sa_status st = split_run(c, sb, S.samples, 0, cv, false, 0, 0, &sf, s);
+        const sa_status st = split_run(c, sb, S.samples, SplitText{}, SplitFinal{}, 0, cv, false, 0,
+                                       0, &sf, s);
         if (st != SA_OK) return st;
         sorted = sf ? sk2 : sk;
       }
@@ -1009,67 +1302,82 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, int iota, Carve
     }
     const bool small = S.tile == 4 * kSplitBlock;
     const u32 hgrid = S.groups * std::min<u32>(S.per, 2048 / S.groups);
-    {
-      Tracer t(c, s, SA_KERNEL_HISTOGRAM, double(count) * 8.0);
-      if (small)
-        hipLaunchKernelGGL((split_hist_kernel<4, false>), dim3(hgrid), dim3(kSplitBlock), 0, s,
-                           bf.kA, S, A, ctr_top);
-      else
-        hipLaunchKernelGGL((split_hist_kernel<12, false>), dim3(hgrid), dim3(kSplitBlock), 0, s,
-                           bf.kA, S, A, ctr_top);
-    }
     const u32* vin = iota ? nullptr : bf.vA;
+#define SA_HIST(IT, SECOND, TEXT, GRID, KEYS, CTR)                                              \
+  hipLaunchKernelGGL((split_hist_kernel<IT, SECOND, TEXT>), dim3(GRID), dim3(kSplitBlock), 0, s, \
+                     KEYS, T, S, A, CTR)
+#define SA_SWEEP(IT, SECOND, TEXT, GRID, KIN, VIN, KOUT, VOUT, IOTA)                              \
+  hipLaunchKernelGGL((split_sweep_kernel<IT, SECOND, TEXT>), dim3(GRID), dim3(kSplitBlock), 0, s, \
+                     KIN, VIN, T, KOUT, VOUT, S, A, IOTA, ctr)
     {
-      Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (iota ? 20.0 : 24.0));
-      if (small)
-        hipLaunchKernelGGL((split_sweep_kernel<4, false>), dim3(S.groups * S.per),
-                           dim3(kSplitBlock), 0, s, bf.kA, vin, bf.kB, bf.vB, S, A, iota, ctr);
-      else
-        hipLaunchKernelGGL((split_sweep_kernel<12, false>), dim3(S.groups * S.per),
-                           dim3(kSplitBlock), 0, s, bf.kA, vin, bf.kB, bf.vB, S, A, iota, ctr);
+      Tracer t(c, s, SA_KERNEL_HISTOGRAM, double(count) * (T.text ? 1.0 : 8.0));
+      if (T.text) {
+        if (small) SA_HIST(4, false, true, hgrid, bf.kA, ctr_top);
+        else SA_HIST(kSweepItems, false, true, hgrid, bf.kA, ctr_top);
+      } else {
+        if (small) SA_HIST(4, false, false, hgrid, bf.kA, ctr_top);
+        else SA_HIST(kSweepItems, false, false, hgrid, bf.kA, ctr_top);
+      }
     }
-    kout = bf.kB;
-    vout = bf.vB;
+    {
+      Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (T.text ? 13.0 : iota ? 20.0 : 24.0));
+      const u32 grid = S.groups * S.per;
+      if (T.text) {
+        if (small) SA_SWEEP(4, false, true, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+        else SA_SWEEP(kSweepItems, false, true, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+      } else {
+        if (small) SA_SWEEP(4, false, false, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+        else SA_SWEEP(kSweepItems, false, false, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+      }
+    }
+    u64* kout = bf.kB;
+    u32* vout = bf.vB;
     *fin = 1;
     if (S.log2) {
       // At most one partly filled tile per group; a multiple of the XCDs.
       const u32 grid = u32(ceil_div(u64(S.tiles) + (u64(1) << S.log1), kSplitXcds) * kSplitXcds);
       {
         Tracer t(c, s, SA_KERNEL_HISTOGRAM, double(count) * 8.0);
-        if (small)
-          hipLaunchKernelGGL((split_hist_kernel<4, true>), dim3(grid), dim3(kSplitBlock), 0, s,
-                             bf.kB, S, A, nullptr);
-        else
-          hipLaunchKernelGGL((split_hist_kernel<12, true>), dim3(grid), dim3(kSplitBlock), 0, s,
-                             bf.kB, S, A, nullptr);
+        if (small) SA_HIST(4, true, false, grid, bf.kB, nullptr);
+        else SA_HIST(kSweepItems, true, false, grid, bf.kB, nullptr);
       }
       {
         Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * 24.0);
-        if (small)
-          hipLaunchKernelGGL((split_sweep_kernel<4, true>), dim3(grid), dim3(kSplitBlock), 0, s,
-                             bf.kB, bf.vB, bf.kA, bf.vA, S, A, 0, ctr);
-        else
-          hipLaunchKernelGGL((split_sweep_kernel<12, true>), dim3(grid), dim3(kSplitBlock), 0, s,
-                             bf.kB, bf.vB, bf.kA, bf.vA, S, A, 0, ctr);
+        if (small) SA_SWEEP(4, true, false, grid, bf.kB, bf.vB, bf.kA, bf.vA, 0);
+        else SA_SWEEP(kSweepItems, true, false, grid, bf.kB, bf.vB, bf.kA, bf.vA, 0);
       }
       kout = bf.kA;
       vout = bf.vA;
       *fin = 0;
     }
+#undef SA_HIST
+#undef SA_SWEEP
     Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * 24.0);
+    // Most buckets fit the first, smallest local sort; what it lists goes on to the
+    // next (which is short of work, not of room: two lists).
     const u32 nb = S.nb();
     if ((count >> 9) <= nb)
-      hipLaunchKernelGGL((split_local_kernel<1016, 128>),
-                         dim3(std::min<u32>(nb, u32(c->num_cus) * 10)), dim3(128), 0, s, kout, vout,
-                         u32(count), nb, A.start, A.splitters, A.big, 0, 0, ctr);
+      SA_LOCAL(1016, 128, std::min<u32>(nb, u32(c->num_cus) * 8), kout, vout, nb, A.start,
+               A.splitters, nullptr, A.big);
     else
-      hipLaunchKernelGGL((split_local_kernel<2032, 256>),
-                         dim3(std::min<u32>(nb, u32(c->num_cus) * 5)), dim3(256), 0, s, kout, vout,
-                         u32(count), nb, A.start, A.splitters, A.big, 0, 0, ctr);
-    hipLaunchKernelGGL((split_local_kernel<int(kSplitCap), 1024>),
-                       dim3(std::min<u32>(nb, u32(c->num_cus))), dim3(1024), 0, s,
-                       kout, vout, u32(count), nb, A.start, A.splitters, A.big, 1, 0, ctr);
+      SA_LOCAL(2032, 256, std::min<u32>(nb, u32(c->num_cus) * 4), kout, vout, nb, A.start,
+               A.splitters, nullptr, A.big);
+    SA_LOCAL(int(kSplitOne), 512, std::min<u32>(nb, u32(c->num_cus)), kout, vout, nb, A.start,
+             A.splitters, A.big, A.big2);
+    SA_LOCAL(int(kSplitCap), 1024, std::min<u32>(nb, u32(c->num_cus)), kout, vout, nb, A.start,
+             A.splitters, A.big2, nullptr);
+    if (final) {
+      hipLaunchKernelGGL(split_equal_list_kernel, dim3(u32(std::min<u64>(ceil_div(nb, 256), 256))),
+                         dim3(256), 0, s, nb, u32(count), A.start, A.splitters, A.equal_head,
+                         A.equal, ctr);
+      hipLaunchKernelGGL(split_equal_kernel,
+                         dim3(u32(std::min<u64>(std::max<u64>(1, count / kEqualPiece),
+                                                u64(c->num_cus) * 8))),
+                         dim3(256), 0, s, kout, vout, u32(count), A.start, A.equal_head, A.equal,
+                         out, ctr);
+    }
   }
+#undef SA_LOCAL
   if (top) {
     Tracer t(c, s, SA_KERNEL_OTHER, 0);
     hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(kWave), 0, s, ctr, npass, *fin, c->plan,
@@ -1080,9 +1388,11 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, int iota, Carve
 
 // Whether a sort of `count` pairs may take the split sort. An explicit tuning
 // asks for the LSD sweeps it describes. Above 1280 * 2^20 pairs a bucket's mean
-// comes too close to kSplitCap. The scratch is the active list's position
-// array (4 bytes a suffix; no sort's input needs it any more and no sort's output
-// yet). The ranks beside it stay: a multi-text round can be repeated.
+// comes too close to what the local sorts hold. The scratch is the active list's
+// position array (4 bytes a suffix; no sort's input needs it any more and no
+// sort's output yet). The ranks beside it stay: a multi-text round can be repeated.
+// A round 0 writes the active list while it still reads the scratch, so its scratch
+// is the ISA instead, which is formed after it.
 bool split_usable(const sa_ctx* c, u64 count) {
   if (c->tuning_explicit || c->force_lsd || count == 0 || count > (u64(1280) << 20)) return false;
   // Arrays and samples of the sort and of the sorts of samples inside it.
@@ -1092,7 +1402,7 @@ bool split_usable(const sa_ctx* c, u64 count) {
     Carver cv{nullptr, ~size_t(0)};
     u32* clear;
     u64 words;
-    carve(cv, S, &clear, &words);
+    carve(cv, S, true, &clear, &words);
     if (S.log1) {
       cv.get<u64>(S.samples);
       cv.get<u64>(S.samples);
@@ -1108,7 +1418,24 @@ sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_p
                      hipStream_t s) {
   u32 fin = 0;
   const Carver cv{reinterpret_cast<char*>(c->act_idx), size_t(c->cap) * 4};
-  return split_run(c, bf, count, vals_present ? 0 : 1, cv, true, npass, slot, &fin, s);
+  return split_run(c, bf, count, SplitText{}, SplitFinal{}, vals_present ? 0 : 1, cv, true, npass,
+                   slot, &fin, s);
+}
+
+sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, hipStream_t s) {
+  u32 fin = 0;
+  const Carver cv{reinterpret_cast<char*>(c->isa), size_t(c->cap) * 4};
+  const SplitText T{text, c->code, c->counters, (reinterpret_cast<uintptr_t>(text) & 3) == 0};
+  const SplitFinal out{d_sa, c->act_idx, nullptr, c->act_rank, nullptr, 0};
+  return split_run(c, full_bufs(c), n, T, out, 1, cv, true, npass, 0, &fin, s);
+}
+
+sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u64* tbase, int idshift, u32* d_sa,
+                       hipStream_t s) {
+  u32 fin = 0;
+  const Carver cv{reinterpret_cast<char*>(c->isa), size_t(c->cap) * 4};
+  const SplitFinal out{d_sa, nullptr, c->act_ti, c->act_rank, tbase, idshift};
+  return split_run(c, full_bufs(c), n, SplitText{}, out, 0, cv, true, npass, 0, &fin, s);
 }
 
 }  // namespace drv

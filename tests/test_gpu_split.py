@@ -55,6 +55,28 @@ def test_equal_keys(builder, n):
     check(builder, np.tile(rng.integers(0, 96, 997), n // 997 + 1)[:n])
 
 
+@pytest.mark.parametrize("mode", ["eager", "lazy"])
+@pytest.mark.parametrize("n", [2000, 70001, 3000001])
+def test_isa_after_fused_round0(builder, mode, n):
+    """Both forms of the ISA after a round 0 that left its positions in the SA, with
+    survivors from ordinary and from equality buckets; the text at every alignment."""
+    rng = np.random.default_rng(n)
+    t = rng.integers(0, 60, n + 3).astype(np.uint8)
+    t[n // 5:n // 5 + n // 50] = 9
+    t[n // 2:n // 2 + n // 100] = t[n // 3:n // 3 + n // 100]
+    d = torch.from_numpy(t).to("cuda:0")
+    builder.set_isa_mode(mode)
+    try:
+        for k in range(4):
+            sa = builder.build(d[k:k + n])
+            torch.cuda.synchronize()
+            assert np.array_equal(sa.cpu().numpy().view(np.uint32),
+                                  oracle.sa(t[k:k + n], parallel=True)), (mode, n, k)
+            assert builder.last_info()["rounds"] > 1
+    finally:
+        builder.set_isa_mode("auto")
+
+
 def mix32(x):
     x = x ^ (x >> 16)
     x = (x * 0x7feb352d) & 0xFFFFFFFF
