@@ -96,6 +96,7 @@ struct sa_ctx {
   u32* stage_hist = nullptr;  // staged ISA writes: counts per (bucket, re-rank workgroup)
   // Pinned mirror of counters | rc | plan_log, refreshed by every readback.
   void* h_mirror = nullptr;
+  u64* d_mirror = nullptr;  // its device address
   u64* h_counters = nullptr;
   RoundCtl* h_rc = nullptr;
   u32* h_plans = nullptr;  // [kPlanLogRows][kPlanLogWords]
@@ -283,6 +284,9 @@ sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_p
 // sorted keys in the plan's final buffer, their positions in d_sa (in place of a
 // value buffer), the suffixes whose key is not unique in the active list. The ISA's
 // memory is scratch. Only where split_usable().
+// A text that split_small_text() names also has its control words and alphabet made
+// by split_round0 (c->present zero on entry and exit), others before it.
+bool split_small_text(u64 n);
 sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, hipStream_t s);
 sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u64* tbase, int idshift, u32* d_sa,
                        hipStream_t s);

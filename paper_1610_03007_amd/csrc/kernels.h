@@ -197,6 +197,9 @@ void launch_isa_complete(u32* isa, u64 n, const u8* text, const u16* code, const
                          const u64* keys0, const u64* sample, const u32* live, hipStream_t s);
 void launch_fill_u32(u32* p, u64 count, u32 value, hipStream_t s);
 
+// to[i] = from[i] for `words` 64-bit words (to: pinned host memory).
+void launch_mirror(const u64* from, u64* to, u32 words, hipStream_t s);
+
 __host__ __device__ inline u64 ceil_div(u64 a, u64 b) { return (a + b - 1) / b; }
 
 // ---------------------------------------------------------------------------

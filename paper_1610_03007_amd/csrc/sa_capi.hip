@@ -292,10 +292,9 @@ RerankArgs single_args(u64 count, u64 n, int b, int mode) {
 }
 
 sa_status readback(sa_ctx* c, hipStream_t s) {
-  // counters | rc | plan log in one copy.
-  if (hipMemcpyAsync(c->h_mirror, c->counters, kMirrorBytes, hipMemcpyDeviceToHost, s) !=
-      hipSuccess)
-    return SA_EDEVICE;
+  // counters | rc | plan log in one go.
+  static_assert(kMirrorBytes % 8 == 0, "whole words");
+  launch_mirror(c->counters, c->d_mirror, u32(kMirrorBytes / 8), s);
   if (hipStreamSynchronize(s) != hipSuccess) return SA_EDEVICE;
   if (hipGetLastError() != hipSuccess) return SA_EDEVICE;
   if (c->h_counters[kCtrSplitOver] != 0) {
@@ -489,21 +488,23 @@ sa_status build_rounds(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_
   // Round 0: alphabet, packed keys, full sort, names, discard. The ISA is not
   // written yet; every sorted position's rank goes to the spare value buffer.
   const Bufs full = full_bufs(c);
-  {
-    Tracer t(c, s, SA_KERNEL_OTHER, 0);
-    launch_fill_u64(c->counters, kCtrCount, 0, s);
-    launch_fill_u64(reinterpret_cast<u64*>(c->rc), sizeof(RoundCtl) / 8, 0, s);
-    launch_fill_u64(reinterpret_cast<u64*>(c->present), 256 / 2, 0, s);
-  }
-  {
-    Tracer t(c, s, SA_KERNEL_OTHER, double(n));
-    launch_byte_presence(text, n, c->present, s);
-    launch_alphabet_codes(c->present, c->code, c->counters, c->round0_trim, 0, c->radix_bits, s);
-  }
-  const int npass0 = npass_for(c, 64);
   // The fused round 0 writes every place of the SA, so a build that may stop early
   // (whose unfinished places the caller keeps) does not take it.
   const bool fused = max_rounds == 0 && split_usable(c, n);
+  if (!(fused && split_small_text(n))) {
+    {
+      Tracer t(c, s, SA_KERNEL_OTHER, 0);
+      launch_fill_u64(c->counters, kCtrCount, 0, s);
+      launch_fill_u64(reinterpret_cast<u64*>(c->rc), sizeof(RoundCtl) / 8, 0, s);
+      launch_fill_u64(reinterpret_cast<u64*>(c->present), 256 / 2, 0, s);
+    }
+    Tracer t(c, s, SA_KERNEL_OTHER, double(n));
+    launch_byte_presence(text, n, c->present, s);
+    launch_alphabet_codes(c->present, c->code, c->counters, c->round0_trim, 0, c->radix_bits, s);
+    // (Builds of short texts expect it clear.)
+    launch_fill_u64(reinterpret_cast<u64*>(c->present), 256 / 2, 0, s);
+  }
+  const int npass0 = npass_for(c, 64);
   if (fused) {
     st = split_round0(c, text, n, npass0, d_sa, s);
     if (st != SA_OK) return st;
@@ -874,6 +875,12 @@ sa_status sa_ctx_create(sa_ctx** out, int device, const char* tune_cache_json) {
     sa_ctx_destroy(c);
     return SA_ENOMEM;
   }
+  void* dm = nullptr;
+  if (hipHostGetDevicePointer(&dm, c->h_mirror, 0) != hipSuccess || !dm) {
+    sa_ctx_destroy(c);
+    return SA_EDEVICE;
+  }
+  c->d_mirror = static_cast<u64*>(dm);
   c->h_counters = static_cast<u64*>(c->h_mirror);
   c->h_rc = reinterpret_cast<RoundCtl*>(static_cast<char*>(c->h_mirror) + kSmallCounters);
   c->h_plans = reinterpret_cast<u32*>(static_cast<char*>(c->h_mirror) + kSmallCounters +

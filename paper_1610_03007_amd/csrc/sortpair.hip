@@ -158,6 +158,8 @@ sa_status build_sortpair(sa_ctx* c, const u8* text, u64 n, u32* d_sa, u64* h_cou
     Tracer t(c, s, SA_KERNEL_OTHER, double(n));
     launch_byte_presence(text, n, c->present, s);
     launch_alphabet_codes(c->present, c->code, c->counters, c->round0_trim, 0, c->radix_bits, s);
+    // (Builds of short texts expect it clear.)
+    launch_fill_u64(reinterpret_cast<u64*>(c->present), 256 / 2, 0, s);
   }
   {
     Tracer t(c, s, SA_KERNEL_PACK_TEXT, double(n) * 9.0);

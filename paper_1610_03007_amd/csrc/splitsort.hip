@@ -47,7 +47,7 @@ namespace {
 constexpr int kSplitBlock = 512;
 constexpr int kSplitMaxLogD = 10;
 constexpr u32 kSplitMaxD = 1u << kSplitMaxLogD;
-constexpr u32 kSplitOne = 3840;       // pairs of an input sorted as one bucket
+constexpr u32 kSplitOne = 4608;       // pairs of an input sorted as one bucket
 constexpr u32 kSplitCap = 9216;       // pairs of a bucket sorted in LDS at most
 constexpr u32 kSplitRankMax = 8192;   // samples sorted by counting
 constexpr u32 kSplitXcds = 8;
@@ -147,6 +147,15 @@ struct SplitShape {
   u32 nb() const { return 1u << (log1 + log2); }
 };
 
+// What a round 0 in one workgroup needs besides the sort's own arguments.
+struct SplitTiny {
+  const u8* text;
+  u16* code;
+  SortCtl* ctl;
+  u64* rc;
+  int trim;
+};
+
 // An equality bucket of a round 0 (see split_equal_list_kernel).
 constexpr u32 kEqualPiece = 4096;
 struct SplitEqual {
@@ -235,6 +244,59 @@ struct SplitFinal {
   int idshift;
 };
 
+// Code width w and characters per round-0 key c of an alphabet of sigma bytes, as
+// alphabet_codes_kernel has them for one text.
+__device__ inline void key_shape(u32 sigma, int trim, u32 rb, u32* w, u32* c) {
+  *w = sigma ? 32 - __clz(sigma) : 1;
+  *c = 64 / *w;
+  const u32 used = *c * *w;
+  if (trim && used % rb != 0 && used > rb) {
+    const u32 full = (used / rb) * rb;
+    if (full / *w >= 1) *c = full / *w;
+  }
+}
+
+// Code of byte value threadIdx.x (of the first 256 threads) from its presence flag:
+// 1 + the present bytes below it, 0 if absent; *sigma gets their number. Every
+// thread of the workgroup calls; s_w holds four words.
+__device__ inline u16 byte_code(bool present, u32* s_w, u32* sigma) {
+  const u32 t = threadIdx.x;
+  const u32 p = t < 256 && present ? 1u : 0u;
+  const u32 inc = wave_inclusive_sum(p);
+  if (t < 256 && lane_id() == kWave - 1) s_w[t / kWave] = inc;
+  __syncthreads();
+  u32 off = 0;
+  *sigma = 0;
+  for (u32 w = 0; w < 4; ++w) {
+    if (w < t / kWave) off += s_w[w];
+    *sigma += s_w[w];
+  }
+  return p ? u16(off + inc) : u16(0);
+}
+
+// The sort's plan as the re-rank and the round log read it: the buffer that holds
+// the output, and which digits vary (skip flags). One lane per pass.
+struct SplitPlanOut {
+  SortPlan* plan;  // nullptr: none (a sort of samples)
+  u32* log;        // the plan log's row
+  int npass, rb;
+  u32 final_buf;
+};
+__device__ inline void write_plan(const SplitPlanOut& o, u64 varying) {
+  const int p = threadIdx.x;
+  if (p >= kMaxPasses) return;
+  u32 skip = !(p < o.npass && ((varying >> (p * o.rb)) & ((u64(1) << o.rb) - 1)) != 0);
+  if (varying == 0) skip = p != o.npass - 1;  // all keys equal: the LSD sort's one copy pass
+  o.plan->skip[p] = skip;
+  o.log[p] = skip;
+  o.log[kMaxPasses + p] = 0;
+  o.log[2 * kMaxPasses + p] = 0;
+  if (p == 0) {
+    o.plan->final_buf = o.final_buf;
+    o.log[3 * kMaxPasses] = o.final_buf;
+  }
+}
+
 // First kernel: control words of the sort and cleared counts.
 __global__ __launch_bounds__(256) void split_begin_kernel(SortCtl* __restrict__ ctl, u64 count,
                                                           u32* __restrict__ clear, u64 words,
@@ -249,7 +311,14 @@ __global__ __launch_bounds__(256) void split_begin_kernel(SortCtl* __restrict__ 
   for (u32 i = threadIdx.x; i <= u32(kCtrActive); i += blockDim.x) counters[i] = 0;
 }
 
-// Sample i: the key of a position drawn in the i-th of `samples` equal stretches.
+// Position of sample i: drawn in the i-th of `samples` equal stretches.
+__device__ inline u32 sample_position(u32 i, u32 count, u32 samples) {
+  const u32 lo = u32(u64(i) * count / samples), hi = u32(u64(i + 1) * count / samples);
+  const u32 w = hi > lo ? hi - lo : 1;
+  const u32 p = lo + mix32(i + 0x9e3779b9u) % w;
+  return p < count ? p : count - 1;
+}
+
 __global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict__ keys,
                                                            SplitText T, u32 count, u32 samples,
                                                            u64* __restrict__ out) {
@@ -260,10 +329,7 @@ __global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict
   }
   const u32 i = blockIdx.x * 256 + threadIdx.x;
   if (i >= samples) return;
-  const u32 lo = u32(u64(i) * count / samples), hi = u32(u64(i + 1) * count / samples);
-  const u32 w = hi > lo ? hi - lo : 1;
-  u32 p = lo + mix32(i + 0x9e3779b9u) % w;
-  if (p >= count) p = count - 1;
+  const u32 p = sample_position(i, count, samples);
   if (!T.text) {
     out[i] = keys[p];
     return;
@@ -280,9 +346,12 @@ __global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict
 // Sorts up to kSplitRankMax samples by counting, for each, the smaller ones
 // (ties by index): 16 samples per workgroup, each counted by 32 threads that
 // read neighbouring samples, so that 8192 samples occupy every CU.
-__global__ __launch_bounds__(kSplitBlock) void split_rank_kernel(const u64* __restrict__ in,
-                                                                 u32 samples,
-                                                                 u64* __restrict__ out) {
+// over != 0 (an input of one sweep): every over-th sorted sample is a splitter of
+// the f buckets, written to `out` by itself (and the last, all ones); the lists of
+// larger buckets start empty and `present`, if any, is cleared for the next build.
+__global__ __launch_bounds__(kSplitBlock) void split_rank_kernel(
+    const u64* __restrict__ in, u32 samples, u64* __restrict__ out, u32 over, u32 f,
+    u32* __restrict__ big, u32* __restrict__ big2, u32* __restrict__ present) {
   constexpr u32 PER = 16, PARTS = kSplitBlock / PER;
   __shared__ u64 s_k[kSplitRankMax];
   __shared__ u32 s_r[PER];
@@ -303,7 +372,20 @@ __global__ __launch_bounds__(kSplitBlock) void split_rank_kernel(const u64* __re
     atomicAdd(&s_r[threadIdx.x % PER], r);
   }
   __syncthreads();
-  if (p == 0 && i < samples) out[s_r[threadIdx.x]] = s_k[i];
+  if (p == 0 && i < samples) {
+    const u32 r = s_r[threadIdx.x];
+    if (!over)
+      out[r] = s_k[i];
+    else if (r > 0 && r % over == 0 && r / over < f)
+      out[r / over - 1] = s_k[i];
+  }
+  if (over && blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      out[f - 1] = ~u64(0);
+      big[0] = big2[0] = 0;
+    }
+    if (present && threadIdx.x < 256) present[threadIdx.x] = 0;
+  }
 }
 
 // Splitters from the sorted samples: every over-th, and the table of the first
@@ -328,6 +410,80 @@ __global__ __launch_bounds__(256) void split_pick_kernel(const u64* __restrict__
     const u64 m = __ballot(same);
     if ((lane_id() & 31) == 0 && i < d1) A.top_flag[i >> 5] = u32(m >> lane_id());
   }
+}
+
+// Round 0 of a text of one sweep, where the launches themselves are most of the
+// time: three kernels in place of the clears, the alphabet, the sample and the
+// splitters (nine kernels; 2^16 bytes: 108 -> 84 us a build with the plan written
+// by the sweep and the counters mirrored by a kernel).
+//
+// 1. The bytes present (`present` is zero between builds: kernel 3 clears it), and
+// every cleared or initial control word.
+__global__ __launch_bounds__(256) void small_begin_kernel(const u8* __restrict__ text, u32 n,
+                                                          int vec_ok, u32* __restrict__ present,
+                                                          SortCtl* __restrict__ ctl,
+                                                          u64* __restrict__ counters,
+                                                          u64* __restrict__ rc,
+                                                          u32* __restrict__ clear, u32 words) {
+  __shared__ u32 seen[256];
+  seen[threadIdx.x] = 0;
+  const u32 stride = gridDim.x * 256, t = blockIdx.x * 256 + threadIdx.x;
+  for (u32 i = t; i < words; i += stride) clear[i] = 0;
+  if (t < u32(kCtrCount)) counters[t] = 0;
+  if (t < u32(sizeof(RoundCtl) / 8)) rc[t] = 0;
+  if (t == 0) {
+    ctl->count = n;
+    ctl->dense = 0;
+  }
+  __syncthreads();
+  const u32 nvec = vec_ok ? n / 16 : 0;
+  const uint4* v = reinterpret_cast<const uint4*>(text);
+  for (u32 i = t; i < nvec; i += stride) {
+    const uint4 x = v[i];
+    const u32 ws[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) seen[(ws[q] >> (8 * b)) & 0xFFu] = 1;
+    }
+  }
+  for (u32 i = nvec * 16 + t; i < n; i += stride) seen[text[i]] = 1;
+  __syncthreads();
+  if (seen[threadIdx.x]) atomicOr(&present[threadIdx.x], 1u);
+}
+
+// 2. The alphabet (every workgroup for itself, the first one for the kernels after
+// it) and the sample.
+__global__ __launch_bounds__(256) void small_sample_kernel(const u8* __restrict__ text, u32 n,
+                                                           const u32* __restrict__ present,
+                                                           int trim, int rb, u32 samples,
+                                                           u16* __restrict__ code,
+                                                           u64* __restrict__ counters,
+                                                           u64* __restrict__ out) {
+  __shared__ u16 s_code[256];
+  __shared__ u32 s_w[4];
+  u32 sigma, w, c;
+  const u16 mine = byte_code(present[threadIdx.x] != 0, s_w, &sigma);
+  key_shape(sigma, trim, u32(rb), &w, &c);
+  s_code[threadIdx.x] = mine;
+  if (blockIdx.x == 0) {
+    code[threadIdx.x] = mine;
+    if (threadIdx.x == 0) {
+      counters[kCtrSigma] = sigma;
+      counters[kCtrCodeBits] = w;
+      counters[kCtrChars] = c;
+    }
+  }
+  __syncthreads();
+  const u32 i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= samples) return;
+  const u32 p = sample_position(i, n, samples);
+  u64 k = 0;
+  for (u32 q = 0; q < c; ++q) {
+    const u64 x = u64(p) + q;
+    k = (k << w) | (x < n ? s_code[text[x]] : u16(0));
+  }
+  out[i] = k;
 }
 
 // The pairs [base, base + n) and tables of one tile, for the kernels below.
@@ -364,17 +520,17 @@ __device__ inline SplitTile split_tile2(const SplitArrays& A, u32 d1, u32 tile, 
   return t;
 }
 
-// Splitter tree of a sweep into LDS: level 1 the `top` table and its flags, level 2
-// the row's own splitters. (Bit D - 1 of the flags is never set.)
+// Splitter tree of a sweep into LDS: the first of two sweeps the `top` table and its
+// flags, the second the row's own splitters, a single sweep all of them. (Bit D - 1 of the flags is never set.)
 template <bool SECOND>
-__device__ inline void load_splitters(const SplitArrays& A, u32 row, int logd, u64* s_sp,
+__device__ inline void load_splitters(const SplitArrays& A, u32 row, int logd, bool two, u64* s_sp,
                                       u32* s_fl) {
   const u32 d = 1u << logd;
-  if (!SECOND) {
+  if (!SECOND && two) {
     for (u32 i = threadIdx.x; i + 1 < d; i += kSplitBlock) s_sp[tree_node(i, logd)] = A.top[i];
     for (u32 i = threadIdx.x; i < (d + 31) / 32; i += kSplitBlock) s_fl[i] = A.top_flag[i];
   } else {
-    const u64* sp = A.splitters + (u64(row) << logd);
+    const u64* sp = A.splitters + (SECOND ? u64(row) << logd : 0);
     for (u32 i0 = 0; i0 < d; i0 += kSplitBlock) {
       const u32 i = i0 + threadIdx.x;
       const u64 k = i < d ? sp[i] : 0;
@@ -417,7 +573,7 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
     kstep = gridDim.x / S.groups;
     kend = S.per;
   }
-  load_splitters<SECOND>(A, row, logd, s_sp, s_fl);
+  load_splitters<SECOND>(A, row, logd, S.log2 != 0, s_sp, s_fl);
   for (u32 i = tid; i < d; i += kSplitBlock) s_cnt[i] = 0;
   __syncthreads();
   u64 kor = 0, knot = 0;
@@ -497,7 +653,8 @@ template <int ITEMS, bool SECOND, bool TEXT>
 __global__ __launch_bounds__(kSplitBlock) __attribute__((amdgpu_waves_per_eu(4)))
 void split_sweep_kernel(
     const u64* __restrict__ kin, const u32* __restrict__ vin, SplitText T, u64* __restrict__ kout,
-    u32* __restrict__ vout, SplitShape S, SplitArrays A, int iota, u64* __restrict__ counters) {
+    u32* __restrict__ vout, SplitShape S, SplitArrays A, int iota, SplitPlanOut plan,
+    u64* __restrict__ counters) {
   constexpr u32 TILE = u32(ITEMS) * kSplitBlock;
   static_assert(kSplitMaxD <= 2 * kSplitBlock, "two buckets per thread");
   __shared__ u64 s_buf[TILE];       // codes of a text, then keys, then values
@@ -547,7 +704,7 @@ void split_sweep_kernel(
           iota ? t.base + e : (vin && e < t.n) ? __builtin_nontemporal_load(vin + t.base + e) : 0;
     }
   }
-  load_splitters<SECOND>(A, t.row, logd, s_sp, s_fl);
+  load_splitters<SECOND>(A, t.row, logd, S.log2 != 0, s_sp, s_fl);
   for (u32 i = tid; i < d; i += kSplitBlock) s_cnt[i] = 0;
   // Where the buckets 2 tid and 2 tid + 1 of this row start: their totals
   // scanned, plus (level 1) what earlier groups put there.
@@ -572,6 +729,7 @@ void split_sweep_kernel(
   if (t.first) {
     // What the next kernels read: the start of every bucket and, after the
     // first of two sweeps, the tiles of the second (at least one per group).
+    if (!SECOND && plan.plan) write_plan(plan, counters[kCtrKeyOr] & counters[kCtrKeyNot]);
     u32* start = SECOND ? A.start + (u64(t.row) << logd) : S.log2 ? A.start1 : A.start;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
@@ -718,13 +876,15 @@ __device__ inline u64 wave_sort(u64 v) {
 // pair its neighbours' keys: its name if it is not unique, as the re-rank would
 // find it, without another pass over the pairs. The name is 1 + the first place of
 // its run of equal keys, which lies in this bucket.
-template <int CAP, int BLOCK, bool FINAL>
+// TINY: the whole round 0 of a text of at most CAP bytes in one workgroup, from the
+// control words and the alphabet on (n, text and tables in `tiny`).
+template <int CAP, int BLOCK, bool FINAL, bool TINY>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
 void split_local_kernel(
     u64* __restrict__ keys, u32* __restrict__ vals, u32 count, u32 nbuckets,
     const u32* __restrict__ start, const u64* __restrict__ splitters,
     const u32* __restrict__ from, u32* __restrict__ big, int iota, SplitFinal fin,
-    u64* __restrict__ counters) {
+    SplitPlanOut plan, SplitTiny tiny, u64* __restrict__ counters) {
   constexpr int IT = (CAP + BLOCK * kSearchGang - 1) / (BLOCK * kSearchGang) * kSearchGang;
   constexpr int P = BLOCK;          // parts, and samples
   constexpr int NW = BLOCK / kWave;
@@ -804,13 +964,77 @@ void split_local_kernel(
   u64 low;
   bool narrow;
   bucket(blockIdx.x, a, m, low, narrow);
-  load(a, m);
+  if constexpr (TINY) {
+    // The text in LDS (over the values), the bytes seen, the codes (over the tree).
+    static_assert(BLOCK >= 256 && P >= 256, "a thread per byte value");
+    u8* const s_txt = reinterpret_cast<u8*>(s_val);
+    u16* const s_code = reinterpret_cast<u16*>(s_sp);
+    for (u32 i = tid; i < 256; i += BLOCK) s_cnt[i] = 0;
+    if (tid < u32(kCtrCount) && tid != u32(kCtrActive)) counters[tid] = 0;
+    for (u32 i = tid; i < u32(sizeof(RoundCtl) / 8); i += BLOCK) tiny.rc[i] = 0;
+    __syncthreads();
+    for (u32 i = tid; i < count; i += BLOCK) {
+      const u8 x = tiny.text[i];
+      s_txt[i] = x;
+      s_cnt[x] = 1;
+    }
+    __syncthreads();
+    u32 sigma, cw, c;
+    const u16 mine = byte_code(tid < 256 && s_cnt[tid & 255u] != 0, s_off, &sigma);
+    key_shape(sigma, tiny.trim, u32(plan.rb), &cw, &c);
+    if (tid < 256) {
+      s_code[tid] = mine;
+      tiny.code[tid] = mine;
+    }
+    if (tid == 0) {
+      // (The clear of these words above is this wave's: the stores stay in order.)
+      static_assert(kCtrCount <= kWave, "cleared by the first wave");
+      counters[kCtrSigma] = sigma;
+      counters[kCtrCodeBits] = cw;
+      counters[kCtrChars] = c;
+      tiny.ctl->count = count;
+      tiny.ctl->dense = 0;
+    }
+    __syncthreads();
+    u64 o = 0, n = 0;
+#pragma unroll
+    for (int j = 0; j < IT; ++j) {
+      const u32 e = u32(j) * BLOCK + tid;
+      u64 k = 0;
+      if (e < count) {
+        for (u32 q = 0; q < c; ++q) k = (k << cw) | (e + q < count ? s_code[s_txt[e + q]] : u16(0));
+        o |= k;
+        n |= ~k;
+      }
+      key[j] = k;
+      val[j] = e;
+    }
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) {
+      o |= __shfl_xor(o, off, kWave);
+      n |= __shfl_xor(n, off, kWave);
+    }
+    if (lane_id() == 0) {
+      s_raw[tid / kWave] = o;
+      s_raw[NW + tid / kWave] = n;
+    }
+    __syncthreads();
+    o = n = 0;
+    for (int w = 0; w < NW; ++w) {
+      o |= s_raw[w];
+      n |= s_raw[NW + w];
+    }
+    write_plan(plan, o & n);
+    __syncthreads();  // the arrays are reused below
+  } else {
+    load(a, m);
+  }
   for (u32 w = blockIdx.x; w < nbuckets; w += gridDim.x) {
     u32 na, nm;
     u64 nlow;
     bool nnarrow;
     bucket(w + gridDim.x, na, nm, nlow, nnarrow);
-    if (!start && counters) {
+    if (!TINY && !start) {
       // The whole input: the bits that vary, for the plan.
       u64 o = 0, n = 0;
 #pragma unroll
@@ -824,11 +1048,18 @@ void split_local_kernel(
         o |= __shfl_xor(o, off, kWave);
         n |= __shfl_xor(n, off, kWave);
       }
-      if (lane_id() != 0) o = n = 0;
-      if (o) atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyOr),
-                      (unsigned long long)o);
-      if (n) atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyNot),
-                      (unsigned long long)n);
+      if (lane_id() == 0) {
+        s_raw[tid / kWave] = o;
+        s_raw[NW + tid / kWave] = n;
+      }
+      __syncthreads();
+      o = n = 0;
+      for (int w = 0; w < NW; ++w) {
+        o |= s_raw[w];
+        n |= s_raw[NW + w];
+      }
+      if (plan.plan) write_plan(plan, o & n);
+      __syncthreads();
     }
     const bool split = m >= u32(P);  // fewer pairs: one part
     s_cnt[tid] = 0;
@@ -1009,10 +1240,12 @@ void split_local_kernel(
       if (same) atomicAdd(&s_left, u32(__popc(same)));
       __syncthreads();
       const u32 left = s_left;
+      if (TINY && tid == 0) counters[kCtrActive] = left;
       if (left) {  // uniform
         if (tid == 0)
-          s_out = atomicAdd(reinterpret_cast<unsigned long long*>(counters + kCtrActive),
-                            (unsigned long long)left);
+          s_out = TINY ? 0
+                       : atomicAdd(reinterpret_cast<unsigned long long*>(counters + kCtrActive),
+                                   (unsigned long long)left);
         __syncthreads();
         if (s_out + left > count) {
           if (tid == 0) flag(counters, kErrBounds);
@@ -1136,25 +1369,16 @@ __global__ __launch_bounds__(256) void split_equal_kernel(
   if (bad) flag(counters, kErrBounds);
 }
 
-// The sort's plan as the re-rank and the round log read it: the buffer that
-// holds the output, and which digits vary (skip flags).
-__global__ void split_plan_kernel(const u64* __restrict__ counters, int npass, u32 final_buf,
-                                  SortPlan* __restrict__ plan, u32* __restrict__ plan_log,
-                                  int log_row, int rb) {
-  const int p = threadIdx.x;
-  if (p >= kMaxPasses) return;
-  const u64 varying = counters[kCtrKeyOr] & counters[kCtrKeyNot];
-  u32 skip = !(p < npass && ((varying >> (p * rb)) & ((u64(1) << rb) - 1)) != 0);
-  if (varying == 0) skip = p != npass - 1;  // all keys equal: the LSD sort's one copy pass
-  plan->skip[p] = skip;
-  u32* f = plan_log + size_t(log_row) * kPlanLogWords;
-  f[p] = skip;
-  f[kMaxPasses + p] = 0;
-  f[2 * kMaxPasses + p] = 0;
-  if (p == 0) {
-    plan->final_buf = final_buf;
-    f[3 * kMaxPasses] = final_buf;
-  }
+// Control words of a build to their pinned host mirror: a kernel's writes reach it
+// sooner than a copy command does.
+__global__ __launch_bounds__(256) void mirror_kernel(const u64* __restrict__ from, u32 words,
+                                                     u64* __restrict__ to) {
+  for (u32 i = blockIdx.x * 256 + threadIdx.x; i < words; i += gridDim.x * 256) to[i] = from[i];
+}
+
+void launch_mirror(const u64* from, u64* to, u32 words, hipStream_t s) {
+  hipLaunchKernelGGL(mirror_kernel, dim3(u32(ceil_div(words, 256))), dim3(256), 0, s, from, words,
+                     to);
 }
 
 namespace {
@@ -1180,7 +1404,7 @@ SplitShape split_shape(u64 count) {
     S.log2 = std::min(kSplitMaxLogD, lf - 3);
     S.log1 = lf - S.log2;
   }
-  S.over = lf > kSplitMaxLogD ? 12 : count > (u64(512) << lf) ? 8 : 4;
+  S.over = lf > kSplitMaxLogD ? 12 : count > (u64(512) << lf) ? 6 : 4;
   S.samples = S.over << lf;
   // Small inputs: small tiles, so that more CUs take part.
   S.tile = count < (u64(1) << 22) ? 4 * kSplitBlock : kSweepItems * kSplitBlock;
@@ -1261,34 +1485,62 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
   u64* ctr = c->counters;
   u64* const ctr_top = top ? ctr : nullptr;
   *fin = 0;
-  {
+  // Round 0 of a text short enough for one sweep or none starts with its own
+  // kernels (see small_begin_kernel).
+  const bool small_text = T.text && !S.log2;
+  if (small_text && S.log1) {
+    Tracer t(c, s, SA_KERNEL_OTHER, double(count));
+    const u8* text = T.text;
+    hipLaunchKernelGGL(small_begin_kernel,
+                       dim3(u32(std::min<u64>(std::max<u64>(1, ceil_div(count, 256 * 32)), 256))),
+                       dim3(256), 0, s, text, S.count, (reinterpret_cast<uintptr_t>(text) & 15) == 0,
+                       c->present, c->ctl, ctr, reinterpret_cast<u64*>(c->rc), clear, u32(words));
+  } else if (!small_text) {
     Tracer t(c, s, SA_KERNEL_OTHER, 0);
     const u32 g = u32(std::min<u64>(std::max<u64>(1, ceil_div(words, 1024)), 1024));
     hipLaunchKernelGGL(split_begin_kernel, dim3(g), dim3(256), 0, s, top ? c->ctl : nullptr, count,
                        clear, words, ctr);
   }
-#define SA_LOCAL(CAP, BL, GRID, KEYS, VALS, NB, START, SPL, FROM, BIG)                             \
+  const SplitPlanOut plan{top ? c->plan : nullptr, c->plan_log + size_t(log_row) * kPlanLogWords,
+                          npass, c->radix_bits, S.log1 && !S.log2 ? 1u : 0u};
+#define SA_LOCAL(CAP, BL, GRID, KEYS, VALS, NB, START, SPL, FROM, BIG)                           \
   do {                                                                                           \
     if (final)                                                                                   \
-      hipLaunchKernelGGL((split_local_kernel<CAP, BL, true>), dim3(GRID), dim3(BL), 0, s, KEYS,  \
-                         VALS, u32(count), NB, START, SPL, FROM, BIG, iota, out, ctr);           \
+      hipLaunchKernelGGL((split_local_kernel<CAP, BL, true, false>), dim3(GRID), dim3(BL), 0, s, \
+                         KEYS, VALS, u32(count), NB, START, SPL, FROM, BIG, iota, out, plan,     \
+                         SplitTiny{}, ctr);                                                      \
     else                                                                                         \
-      hipLaunchKernelGGL((split_local_kernel<CAP, BL, false>), dim3(GRID), dim3(BL), 0, s, KEYS, \
-                         VALS, u32(count), NB, START, SPL, FROM, BIG, iota, out, ctr);           \
+      hipLaunchKernelGGL((split_local_kernel<CAP, BL, false, false>), dim3(GRID), dim3(BL), 0, s, \
+                         KEYS, VALS, u32(count), NB, START, SPL, FROM, BIG, iota, out, plan,     \
+                         SplitTiny{}, ctr);                                                      \
   } while (0)
   if (!S.log1) {
-    if (T.text) launch_pack_text(T.text, count, T.code, T.counters, bf.kA, s);
-    Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (iota ? 20.0 : 24.0));
-    SA_LOCAL(int(kSplitOne), 512, 1, bf.kA, bf.vA, 1u, nullptr, nullptr, nullptr, nullptr);
+    Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (T.text ? 13.0 : iota ? 20.0 : 24.0));
+    if (T.text) {
+      const SplitTiny tiny{T.text, c->code, c->ctl, reinterpret_cast<u64*>(c->rc), c->round0_trim};
+      hipLaunchKernelGGL((split_local_kernel<int(kSplitOne), 1024, true, true>), dim3(1),
+                         dim3(1024), 0, s, bf.kA, nullptr, u32(count), 1u, nullptr, nullptr,
+                         nullptr, nullptr, 1, out, plan, tiny, ctr);
+      return SA_OK;
+    }
+    SA_LOCAL(int(kSplitOne), 1024, 1, bf.kA, bf.vA, 1u, nullptr, nullptr, nullptr, nullptr);
   } else {
     {
       Tracer t(c, s, SA_KERNEL_OTHER, 0);
-      hipLaunchKernelGGL(split_sample_kernel, dim3(u32(ceil_div(S.samples, 256))), dim3(256), 0, s,
-                         bf.kA, T, S.count, S.samples, sk);
+      if (small_text)
+        hipLaunchKernelGGL(small_sample_kernel, dim3(u32(ceil_div(S.samples, 256))), dim3(256), 0,
+                           s, T.text, S.count, c->present, c->round0_trim, c->radix_bits, S.samples,
+                           c->code, ctr, sk);
+      else
+        hipLaunchKernelGGL(split_sample_kernel, dim3(u32(ceil_div(S.samples, 256))), dim3(256), 0,
+                           s, bf.kA, T, S.count, S.samples, sk);
       u64* sorted = sk2;
       if (S.samples <= kSplitRankMax) {
+        const bool direct = S.log2 == 0;
         hipLaunchKernelGGL(split_rank_kernel, dim3(u32(ceil_div(S.samples, 16))),
-                           dim3(kSplitBlock), 0, s, sk, S.samples, sk2);
+                           dim3(kSplitBlock), 0, s, sk, S.samples, direct ? A.splitters : sk2,
+                           direct ? S.over : 0u, S.nb(), A.big, A.big2,
+                           small_text ? c->present : nullptr);
       } else {
         u32 sf = 0;
         const Bufs sb{sk, sk2, nullptr, nullptr};
@@ -1297,7 +1549,8 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
         if (st != SA_OK) return st;
         sorted = sf ? sk2 : sk;
       }
-      hipLaunchKernelGGL(split_pick_kernel, dim3(u32(ceil_div(S.nb(), 256))), dim3(256), 0, s,
+      if (S.log2)
+        hipLaunchKernelGGL(split_pick_kernel, dim3(u32(ceil_div(S.nb(), 256))), dim3(256), 0, s,
                          sorted, S.log1, S.log2, S.over, S.samples, A);
     }
     const bool small = S.tile == 4 * kSplitBlock;
@@ -1308,7 +1561,7 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
                      KEYS, T, S, A, CTR)
 #define SA_SWEEP(IT, SECOND, TEXT, GRID, KIN, VIN, KOUT, VOUT, IOTA)                              \
   hipLaunchKernelGGL((split_sweep_kernel<IT, SECOND, TEXT>), dim3(GRID), dim3(kSplitBlock), 0, s, \
-                     KIN, VIN, T, KOUT, VOUT, S, A, IOTA, ctr)
+                     KIN, VIN, T, KOUT, VOUT, S, A, IOTA, plan, ctr)
     {
       Tracer t(c, s, SA_KERNEL_HISTOGRAM, double(count) * (T.text ? 1.0 : 8.0));
       if (T.text) {
@@ -1362,10 +1615,13 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
     else
       SA_LOCAL(2032, 256, std::min<u32>(nb, u32(c->num_cus) * 4), kout, vout, nb, A.start,
                A.splitters, nullptr, A.big);
-    SA_LOCAL(int(kSplitOne), 512, std::min<u32>(nb, u32(c->num_cus)), kout, vout, nb, A.start,
-             A.splitters, A.big, A.big2);
+    // (Buckets of 512 pairs on average in a single sweep: one larger shape does.)
+    const bool one_tier = !S.log2 && (count >> 9) <= nb;
+    if (!one_tier)
+      SA_LOCAL(int(kSplitOne), 1024, std::min<u32>(nb, u32(c->num_cus)), kout, vout, nb, A.start,
+               A.splitters, A.big, A.big2);
     SA_LOCAL(int(kSplitCap), 1024, std::min<u32>(nb, u32(c->num_cus)), kout, vout, nb, A.start,
-             A.splitters, A.big2, nullptr);
+             A.splitters, one_tier ? A.big : A.big2, nullptr);
     if (final) {
       hipLaunchKernelGGL(split_equal_list_kernel, dim3(u32(std::min<u64>(ceil_div(nb, 256), 256))),
                          dim3(256), 0, s, nb, u32(count), A.start, A.splitters, A.equal_head,
@@ -1378,11 +1634,6 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
     }
   }
 #undef SA_LOCAL
-  if (top) {
-    Tracer t(c, s, SA_KERNEL_OTHER, 0);
-    hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(kWave), 0, s, ctr, npass, *fin, c->plan,
-                       c->plan_log, log_row, c->radix_bits);
-  }
   return SA_OK;
 }
 
@@ -1421,6 +1672,8 @@ sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_p
   return split_run(c, bf, count, SplitText{}, SplitFinal{}, vals_present ? 0 : 1, cv, true, npass,
                    slot, &fin, s);
 }
+
+bool split_small_text(u64 n) { return split_shape(n).log2 == 0; }
 
 sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, hipStream_t s) {
   u32 fin = 0;
