@@ -83,33 +83,99 @@ __device__ inline u32 common_prefix(const u8* __restrict__ text, u64 n, u64 x, u
   return m;
 }
 
+// The first 16 bytes of suffix x, little-endian, 0 past the end of the text.
+struct Head {
+  u64 lo, hi;
+};
+__device__ inline Head suffix_head(const u8* __restrict__ text, u64 n, u64 x) {
+  const uintptr_t t0 = reinterpret_cast<uintptr_t>(text);
+  const uintptr_t ax = (t0 + x) & ~uintptr_t(7);
+  Head h{0, 0};
+  if (ax >= t0 && ax + 24 <= t0 + n) {
+    const u64* p = reinterpret_cast<const u64*>(ax);
+    const u64 w0 = p[0], w1 = p[1], w2 = p[2];
+    const u32 s = u32(t0 + x - ax) * 8;
+    h.lo = s ? (w0 >> s) | (w1 << (64 - s)) : w0;
+    h.hi = s ? (w1 >> s) | (w2 << (64 - s)) : w1;
+  } else if (x < n) {
+    for (u32 q = 0; q < 16 && x + q < n; ++q) {
+      if (q < 8)
+        h.lo |= u64(text[x + q]) << (8 * q);
+      else
+        h.hi |= u64(text[x + q]) << (8 * (q - 8));
+    }
+  }
+  return h;
+}
+
 // LCP in suffix array order up to kLcpCap; a long entry marks its position in
-// `long_bits` and records Phi there.
+// `long_bits`, records Phi there and sets *any_long.
+// Bound by the random reads of the text (a line per suffix): each suffix's first
+// 16 bytes are read once, by one lane, and its successor takes them from that lane
+// (neighbours used to read both suffixes of every pair: two lines per entry, 2^26
+// suffixes of a Markov text in 1.62 ms). A wave goes through kLcpRows rows of 64
+// consecutive entries, kLcpGang of them at a time so that their reads overlap.
+constexpr int kLcpRows = 16;
+constexpr int kLcpGang = 4;
 __global__ __launch_bounds__(256) void lcp_direct_kernel(const u8* __restrict__ text, u64 n,
                                                          const u32* __restrict__ sa,
                                                          u32* __restrict__ lcp,
                                                          u32* __restrict__ phi,
                                                          u32* __restrict__ long_bits,
+                                                         u64* __restrict__ any_long,
                                                          u64* __restrict__ err) {
-  const u64 stride = u64(gridDim.x) * blockDim.x;
-  for (u64 j = u64(blockIdx.x) * blockDim.x + threadIdx.x; j < n; j += stride) {
-    if (j == 0) {
-      lcp[0] = 0;
-      continue;
+  const int lane = lane_id();
+  const u64 wave = (u64(blockIdx.x) * blockDim.x + threadIdx.x) / kWave;
+  const u64 first = wave * (u64(kLcpRows) * kWave);
+  if (first >= n) return;  // wave-uniform
+  // The suffix before the wave's first entry.
+  u32 carry_s = first > 0 ? sa[first - 1] : 0;
+  Head carry = first > 0 ? suffix_head(text, n, carry_s) : Head{0, 0};
+  for (int r0 = 0; r0 < kLcpRows; r0 += kLcpGang) {
+    u32 b[kLcpGang];
+    Head h[kLcpGang];
+#pragma unroll
+    for (int g = 0; g < kLcpGang; ++g) {
+      const u64 j = first + u64(r0 + g) * kWave + lane;
+      b[g] = j < n ? sa[j] : 0;
     }
-    const u32 a = sa[j - 1], b = sa[j];
-    if (a >= n || b >= n || a == b) {
-      flag_error(err);
-      lcp[j] = 0;
-      continue;
-    }
-    const u32 m = common_prefix(text, n, a, b, kLcpCap);
-    if (m < kLcpCap) {
-      lcp[j] = m;
-    } else {
-      lcp[j] = kLcpLong;
-      phi[b] = a;
-      atomicOr(&long_bits[b >> 5], 1u << (b & 31u));
+#pragma unroll
+    for (int g = 0; g < kLcpGang; ++g) h[g] = suffix_head(text, n, b[g]);
+#pragma unroll
+    for (int g = 0; g < kLcpGang; ++g) {
+      const u64 j = first + u64(r0 + g) * kWave + lane;
+      u32 a = __shfl_up(b[g], 1, kWave);
+      Head p{__shfl_up(h[g].lo, 1, kWave), __shfl_up(h[g].hi, 1, kWave)};
+      if (lane == 0) {
+        a = carry_s;
+        p = carry;
+      }
+      carry_s = __shfl(b[g], kWave - 1, kWave);
+      carry.lo = __shfl(h[g].lo, kWave - 1, kWave);
+      carry.hi = __shfl(h[g].hi, kWave - 1, kWave);
+      if (j >= n) continue;
+      if (j == 0) {
+        lcp[0] = 0;
+        continue;
+      }
+      if (a >= n || b[g] >= n || a == b[g]) {
+        flag_error(err);
+        lcp[j] = 0;
+        continue;
+      }
+      const u64 room = n - (a > b[g] ? a : b[g]);
+      const u64 dl = p.lo ^ h[g].lo, dh = p.hi ^ h[g].hi;
+      u32 m = dl ? u32(__builtin_ctzll(dl) / 8) : dh ? 8 + u32(__builtin_ctzll(dh) / 8) : 16u;
+      if (m > room) m = u32(room);
+      if (m == 16) m += common_prefix(text, n, u64(a) + 16, u64(b[g]) + 16, kLcpCap - 16);
+      if (m < kLcpCap) {
+        lcp[j] = m;
+      } else {
+        lcp[j] = kLcpLong;
+        phi[b[g]] = a;
+        atomicOr(&long_bits[b[g] >> 5], 1u << (b[g] & 31u));
+        *any_long = 1;
+      }
     }
   }
 }
@@ -119,8 +185,10 @@ __global__ __launch_bounds__(256) void lcp_direct_kernel(const u8* __restrict__ 
 // least the previous position's minus one when that one was long too.
 __global__ __launch_bounds__(256) void plcp_long_kernel(const u8* __restrict__ text, u64 n,
                                                         const u32* __restrict__ long_bits,
+                                                        const u64* __restrict__ any_long,
                                                         u32* __restrict__ phi_plcp) {
   static_assert(kLcpStretch % 32 == 0, "whole bitmap words per stretch");
+  if (*any_long == 0) return;
   const u64 t = u64(blockIdx.x) * blockDim.x + threadIdx.x;
   const u64 lo = t * kLcpStretch;
   if (lo >= n) return;
@@ -157,7 +225,9 @@ __global__ __launch_bounds__(256) void plcp_long_kernel(const u8* __restrict__ t
 // LCP[j] = PLCP[SA[j]] for the long entries.
 __global__ __launch_bounds__(256) void lcp_long_gather_kernel(const u32* __restrict__ sa, u64 n,
                                                               const u32* __restrict__ plcp,
+                                                              const u64* __restrict__ any_long,
                                                               u32* __restrict__ lcp) {
+  if (*any_long == 0) return;
   const u64 stride = u64(gridDim.x) * blockDim.x;
   for (u64 j = u64(blockIdx.x) * blockDim.x + threadIdx.x; j < n; j += stride) {
     if (lcp[j] != kLcpLong) continue;
@@ -168,55 +238,88 @@ __global__ __launch_bounds__(256) void lcp_long_gather_kernel(const u32* __restr
 
 // The row of $ (1 + the j with SA[j] = 0) into *dollar.
 __global__ __launch_bounds__(256) void find_dollar_kernel(const u32* __restrict__ sa, u64 n,
-                                                          u64* __restrict__ dollar) {
+                                                          int vec_ok, u64* __restrict__ dollar) {
   const u64 stride = u64(gridDim.x) * blockDim.x;
-  for (u64 j = u64(blockIdx.x) * blockDim.x + threadIdx.x; j < n; j += stride)
+  const u64 t = u64(blockIdx.x) * blockDim.x + threadIdx.x;
+  const u64 nvec = vec_ok ? n / 4 : 0;
+  const uint4* v = reinterpret_cast<const uint4*>(sa);
+  for (u64 i = t; i < nvec; i += stride) {
+    const uint4 x = v[i];
+    if (x.x == 0 || x.y == 0 || x.z == 0 || x.w == 0)
+      *dollar = 4 * i + 1 + (x.x == 0 ? 0 : x.y == 0 ? 1 : x.z == 0 ? 2 : 3);
+  }
+  for (u64 j = nvec * 4 + t; j < n; j += stride)
     if (sa[j] == 0) *dollar = j + 1;
 }
 
 // Transform rows r = 0 .. n: B[r] = T[n - 1] for r = 0, T[SA[r - 1] - 1]
 // otherwise; the $ row either is left out (compact: rows after it move down by
-// one) or holds the byte 0 (the FM index keeps every row and corrects its
-// counts at the $ row).
+// one, *dollar known) or holds the byte 0 (the FM index keeps every row and
+// corrects its counts at the $ row, which goes to *dollar here).
+// Bound by the random reads of the text (a line per row). A thread makes four
+// neighbouring output bytes, so that four reads are in flight and they leave as one
+// word (one byte a thread: 1.21 ms for 2^26 rows of a Markov text). `out` is
+// 4-byte aligned when `words` is set.
 __global__ __launch_bounds__(256) void bwt_kernel(const u8* __restrict__ text, u64 n,
                                                   const u32* __restrict__ sa,
-                                                  const u64* __restrict__ dollar, int compact,
-                                                  u8* __restrict__ out, u64* __restrict__ err) {
-  const u64 d = *dollar;
-  const u64 stride = u64(gridDim.x) * blockDim.x;
-  for (u64 r = u64(blockIdx.x) * blockDim.x + threadIdx.x; r <= n; r += stride) {
-    u8 ch = 0;
-    if (r == 0) {
-      ch = text[n - 1];
-    } else {
-      const u32 s = sa[r - 1];
-      if (s >= n) {
-        flag_error(err);
-        continue;
-      }
-      if (s == 0) {
-        if (!compact) out[r] = 0;
-        continue;
-      }
-      ch = text[s - 1];
+                                                  u64* __restrict__ dollar, int compact,
+                                                  int words, u8* __restrict__ out,
+                                                  u64* __restrict__ err) {
+  const u64 d = compact ? *dollar : ~u64(0);
+  const u64 outs = compact ? n : n + 1;
+  const u64 stride = u64(gridDim.x) * blockDim.x * 4;
+  for (u64 o = (u64(blockIdx.x) * blockDim.x + threadIdx.x) * 4; o < outs; o += stride) {
+    u32 s[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const u64 r = o + q + (o + q >= d ? 1 : 0);  // (n + 1 past the last row of a compact one)
+      s[q] = r == 0 ? u32(n) : r <= n ? sa[r - 1] : 1u;
+      if (r > 0 && s[q] >= n) s[q] = 0xFFFFFFFFu;  // not a position
     }
-    out[compact && r > d ? r - 1 : r] = ch;
+    u32 word = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool in = o + q < outs;
+      if (in && s[q] > n) flag_error(err);
+      if (in && s[q] == 0 && !compact) *dollar = o + q;
+      const u8 ch = in && s[q] != 0 && s[q] <= n ? text[s[q] - 1] : u8(0);
+      word |= u32(ch) << (8 * q);
+    }
+    if (words && o + 4 <= outs) {
+      *reinterpret_cast<u32*>(out + o) = word;
+    } else {
+      for (int q = 0; q < 4; ++q)
+        if (o + q < outs) out[o + q] = u8(word >> (8 * q));
+    }
   }
 }
 
-// Byte counts of the text (for C) in LDS, then one atomic per byte value.
+// Byte counts of the text (for C) in LDS, a copy per wave, then one atomic per
+// byte value. The text is read as 16-byte words where it is 16-byte aligned.
 __global__ __launch_bounds__(256) void byte_count_kernel(const u8* __restrict__ text, u64 n,
-                                                         u64* __restrict__ counts) {
-  __shared__ u32 h[256];
-  h[threadIdx.x] = 0;
+                                                         int vec_ok, u64* __restrict__ counts) {
+  __shared__ u32 h[4][256];
+  for (int i = threadIdx.x; i < 4 * 256; i += 256) (&h[0][0])[i] = 0;
   __syncthreads();
+  u32* mine = h[threadIdx.x / kWave];
   const u64 stride = u64(gridDim.x) * blockDim.x;
-  for (u64 i = u64(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride)
-    atomicAdd(&h[text[i]], 1u);
+  const u64 t = u64(blockIdx.x) * blockDim.x + threadIdx.x;
+  const u64 nvec = vec_ok ? n / 16 : 0;
+  const uint4* v = reinterpret_cast<const uint4*>(text);
+  for (u64 i = t; i < nvec; i += stride) {
+    const uint4 x = v[i];
+    const u32 ws[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int by = 0; by < 4; ++by) atomicAdd(&mine[(ws[k] >> (8 * by)) & 0xFFu], 1u);
+    }
+  }
+  for (u64 i = nvec * 16 + t; i < n; i += stride) atomicAdd(&mine[text[i]], 1u);
   __syncthreads();
-  if (h[threadIdx.x])
-    atomicAdd(reinterpret_cast<unsigned long long*>(counts + threadIdx.x),
-              (unsigned long long)h[threadIdx.x]);
+  const u32 c = h[0][threadIdx.x] + h[1][threadIdx.x] + h[2][threadIdx.x] + h[3][threadIdx.x];
+  if (c)
+    atomicAdd(reinterpret_cast<unsigned long long*>(counts + threadIdx.x), (unsigned long long)c);
 }
 
 // Per sample block b (rows [b * kOccBlock, (b + 1) * kOccBlock) of B): the
@@ -224,25 +327,44 @@ __global__ __launch_bounds__(256) void byte_count_kernel(const u8* __restrict__ 
 // counts into prefix sums). A workgroup takes kOccGroup consecutive blocks so
 // that each byte's row of counts is written in runs. The $ row (byte 0 in B)
 // is not counted.
+// Counts are 16-bit halves, two blocks a word (a block has 256 rows), and only the
+// present bytes have them: 128 * sigma bytes of LDS, which is what each workgroup
+// clears and reads again (64 KB of it took twice the time of the counting).
 __global__ __launch_bounds__(256) void occ_count_kernel(const u8* __restrict__ B, u64 rows,
-                                                        u64 nblocks, u64 dollar,
-                                                        const u8* __restrict__ sym, u32 sigma,
+                                                        u64 nblocks,
+                                                        const u64* __restrict__ dollar_ptr,
+                                                        const u16* __restrict__ code, u32 sigma,
                                                         u64 stride_b, u32* __restrict__ occ) {
-  __shared__ u32 cnt[256][kOccGroup];
-  for (int i = threadIdx.x; i < 256 * kOccGroup; i += 256) (&cnt[0][0])[i] = 0;
+  extern __shared__ u32 cnt[];  // [sigma][kOccGroup / 2]
+  constexpr u32 HW = kOccGroup / 2;
+  __shared__ u16 s_code[256];
+  s_code[threadIdx.x] = code[threadIdx.x];
+  const u64 dollar = dollar_ptr ? *dollar_ptr : ~u64(0);
+  for (u32 i = threadIdx.x; i < sigma * HW; i += 256) cnt[i] = 0;
   __syncthreads();
   const u64 b0 = u64(blockIdx.x) * kOccGroup;
   const u64 r0 = b0 * kOccBlock;
-  constexpr int kBytes = kOccGroup * kOccBlock;  // rows of the group
-  for (int q = threadIdx.x; q < kBytes; q += 256) {
-    const u64 r = r0 + u64(q);
-    if (r < rows && r != dollar) atomicAdd(&cnt[B[r]][q / kOccBlock], 1u);
+  constexpr u32 kWords = kOccGroup * kOccBlock / 4;  // words of the group
+  // (B is padded to whole blocks.)
+  const u64 padded = nblocks * kOccBlock;
+  for (u32 q = threadIdx.x; q < kWords; q += 256) {
+    const u64 r = r0 + u64(q) * 4;
+    if (r >= padded) continue;
+    const u32 w = *reinterpret_cast<const u32*>(B + r);
+    const u32 g = q * 4 / kOccBlock;
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const u32 c = s_code[(w >> (8 * y)) & 0xFFu];
+      if (r + y < rows && r + y != dollar && c < sigma)
+        atomicAdd(&cnt[c * HW + g / 2], 1u << (16 * (g & 1u)));
+    }
   }
   __syncthreads();
   for (u32 idx = threadIdx.x; idx < sigma * kOccGroup; idx += 256) {
     const u32 c = idx / kOccGroup, g = idx % kOccGroup;
     const u64 b = b0 + g;
-    if (b < nblocks) occ[u64(c) * stride_b + b] = cnt[sym[c]][g];
+    if (b < nblocks)
+      occ[u64(c) * stride_b + b] = (cnt[c * HW + g / 2] >> (16 * (g & 1u))) & 0xFFFFu;
   }
 }
 
@@ -258,12 +380,18 @@ __global__ __launch_bounds__(256) void occ_scan_chunks_kernel(u32* __restrict__ 
   u32* row = occ + c * stride_b;
   const u64 base = ch * kScanChunk;
   constexpr int IT = kScanChunk / 256;
+  // (stride_b is a multiple of 64 entries: a row is padded to whole 16-byte words.)
   u32 v[IT];
   u32 sum = 0;
-  for (int k = 0; k < IT; ++k) {
+#pragma unroll
+  for (int k = 0; k < IT; k += 4) {
     const u64 e = base + u64(threadIdx.x) * IT + k;
-    v[k] = e < entries ? row[e] : 0u;
-    sum += v[k];
+    const uint4 x = e < stride_b ? *reinterpret_cast<const uint4*>(row + e) : uint4{0, 0, 0, 0};
+    v[k] = e < entries ? x.x : 0u;
+    v[k + 1] = e + 1 < entries ? x.y : 0u;
+    v[k + 2] = e + 2 < entries ? x.z : 0u;
+    v[k + 3] = e + 3 < entries ? x.w : 0u;
+    sum += v[k] + v[k + 1] + v[k + 2] + v[k + 3];
   }
   // Exclusive scan of the per-thread sums.
   u32 inc = sum;
@@ -279,10 +407,16 @@ __global__ __launch_bounds__(256) void occ_scan_chunks_kernel(u32* __restrict__ 
     total += wsum[w];
   }
   u32 run = woff + inc - sum;
-  for (int k = 0; k < IT; ++k) {
+#pragma unroll
+  for (int k = 0; k < IT; k += 4) {
     const u64 e = base + u64(threadIdx.x) * IT + k;
-    if (e < entries) row[e] = run;
-    run += v[k];
+    uint4 x;
+    x.x = run;
+    x.y = x.x + v[k];
+    x.z = x.y + v[k + 1];
+    x.w = x.z + v[k + 2];
+    run = x.w + v[k + 3];
+    if (e < stride_b) *reinterpret_cast<uint4*>(row + e) = x;
   }
   if (threadIdx.x == 0) totals[c * chunks + ch] = total;
 }
@@ -313,60 +447,83 @@ __global__ __launch_bounds__(256) void occ_scan_add_kernel(u32* __restrict__ occ
   }
 }
 
-// Occ(c, r) for one wave: the sample at r's block plus the matches of byte c
-// among the block's rows before r (a wave reads the 256-row block as one
-// 4-byte word per lane and counts with four ballots), minus the $ row when
-// c is the byte 0 that stands in for it.
-__device__ inline u64 occ_wave(const u8* __restrict__ B, const u32* __restrict__ occ_row,
-                               u64 dollar, u32 c, u64 r) {
-  const u64 b = r / kOccBlock;
-  const u64 start = b * kOccBlock;
-  const int lane = lane_id();
-  const u32 word = reinterpret_cast<const u32*>(B + start)[lane];
-  u64 part = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const u64 pos = start + u64(lane) * 4 + k;
-    const bool hit = pos < r && ((word >> (8 * k)) & 0xFFu) == c;
-    part += __popcll(__ballot(hit));
-  }
-  if (c == 0 && dollar >= start && dollar < r) part -= 1;
-  return u64(occ_row[b]) + part;
-}
-
-// One wave per pattern; patterns concatenated with offsets[num + 1].
+// Backward search. Occ(c, r) is the sample at r's block plus the matches of byte c
+// among the block's rows before r (minus the $ row when c is the byte 0 that stands
+// in for it). Bound by the latency of a chain of dependent random reads, one step
+// per pattern byte, so what counts is how many chains are in flight: a bound of a
+// pattern takes 16 lanes (a 256-row block is 16 bytes a lane), a wave two patterns
+// (one pattern a wave: 200 us for 2^16 patterns of 16 bytes in a 2^26-byte text).
+// Patterns are concatenated with offsets[num + 1].
 __global__ __launch_bounds__(256) void fm_count_kernel(
     const u8* __restrict__ B, u64 n, u64 dollar, const u32* __restrict__ occ, u64 stride_b,
     const u64* __restrict__ C, const u16* __restrict__ code, const u8* __restrict__ pats,
     const u64* __restrict__ offs, u32 num, u64* __restrict__ ranges) {
+  static_assert(kOccBlock == 256, "16 lanes of 16 bytes");
+  __shared__ u64 s_C[256];
+  __shared__ u16 s_code[256];
+  s_C[threadIdx.x] = C[threadIdx.x];
+  s_code[threadIdx.x] = code[threadIdx.x];
+  __syncthreads();
+  const int lane = lane_id();
+  const bool upper = (lane >> 4) & 1;  // this quarter of the wave holds ep, else sp
+  const u32 l = u32(lane & 15);
+  const u64 pairs = (u64(num) + 1) / 2;
   const u64 waves = (u64(gridDim.x) * blockDim.x) / kWave;
-  for (u64 q = (u64(blockIdx.x) * blockDim.x + threadIdx.x) / kWave; q < num; q += waves) {
-    const u64 a = offs[q], z = offs[q + 1];
-    u64 sp = 0, ep = n + 1;
-    if (z > a) {
-      for (u64 k = z; k-- > a;) {
+  for (u64 w = (u64(blockIdx.x) * blockDim.x + threadIdx.x) / kWave; w < pairs; w += waves) {
+    const u64 q = 2 * w + u64(lane >> 5);
+    const bool have = q < num;
+    const u64 a = have ? offs[q] : 0, z = have ? offs[q + 1] : 0;
+    u64 pos = upper ? n + 1 : 0;
+    u64 k = z;
+    while (__any(k > a)) {  // wave-uniform: the shuffles below see every lane
+      const bool on = k > a;
+      u32 part = 0;
+      u64 base = 0, sample = 0;
+      bool absent = false;
+      if (on) {
+        --k;
         const u32 c = pats[k];
-        const u32 cc = code[c];
-        const u64 base = C[c];
-        if (cc == 0xFFFFu) {
-          sp = ep = base;  // the byte does not occur: no row starts with it
-        } else {
-          const u32* row = occ + u64(cc) * stride_b;
-          sp = base + occ_wave(B, row, dollar, c, sp);
-          ep = base + occ_wave(B, row, dollar, c, ep);
+        const u32 cc = s_code[c];
+        base = s_C[c];
+        absent = cc == 0xFFFFu;  // the byte does not occur: no row starts with it
+        if (!absent) {
+          const u64 start = pos & ~u64(kOccBlock - 1);
+          const uint4 x = reinterpret_cast<const uint4*>(B + start)[l];
+          sample = occ[u64(cc) * stride_b + start / kOccBlock];
+          const u32 before = u32(pos - start);  // rows of the block before pos
+          const u32 mine = before > 16 * l ? before - 16 * l : 0u;
+          const u32 cw = c * 0x01010101u;
+          const u32 ws[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+          for (u32 i = 0; i < 4; ++i) {
+            const u32 d = ws[i] ^ cw;
+            const u32 nz = ((d & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | d | 0x7F7F7F7Fu;  // 0x7F: zero byte
+            const u32 take = mine > 4 * i ? mine - 4 * i : 0u;
+            const u32 keep = take >= 4 ? ~0u : (1u << (8 * take)) - 1u;
+            part += u32(__popc(~nz & keep));
+          }
+          if (l == 0 && c == 0 && dollar >= start && dollar < pos) part -= 1;
         }
       }
-      // Rows 1.. are suffixes SA[0..]: the $ row never starts with a byte.
-      sp -= 1;
-      ep -= 1;
-    } else {
-      ep = n;  // the empty pattern: every suffix
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) part += u32(__shfl_xor(int(part), off, kWave));
+      if (on) pos = absent ? base : base + sample + u64(int(part));
     }
-    if (lane_id() == 0) {
-      ranges[2 * q] = sp;
-      ranges[2 * q + 1] = ep;
+    if (have && l == 0) {
+      // Rows 1.. are suffixes SA[0..]: the $ row never starts with a byte. The
+      // empty pattern: every suffix.
+      const u64 v = z > a ? pos - 1 : upper ? n : 0;
+      ranges[2 * q + (upper ? 1 : 0)] = v;
     }
   }
+}
+
+__global__ __launch_bounds__(256) void fill_tail_kernel(u8* __restrict__ p, u64 from, u64 to) {
+  for (u64 i = from + threadIdx.x; i < to; i += 256) p[i] = 0;
+}
+
+void launch_fill_tail(u8* p, u64 from, u64 to, hipStream_t s) {
+  hipLaunchKernelGGL(fill_tail_kernel, dim3(1), dim3(256), 0, s, p, from, to);
 }
 
 u32 grid_for(u64 items, u32 per_block, u32 cap) {
@@ -410,12 +567,16 @@ sa_status sa_lcp(sa_ctx* ctx, const uint8_t* d_text, uint64_t n, const uint32_t*
   u32* long_bits = ctx->live;  // the long positions
   launch_fill_u32(long_bits, ceil_div(n, 32), 0, s);
   const u32 g = grid_for(n, 256, 8192);
-  hipLaunchKernelGGL(lcp_direct_kernel, dim3(g), dim3(256), 0, s, d_text, n, d_sa, d_lcp, phi,
-                     long_bits, ctx->counters + kCtrError);
+  u64* any_long = ctx->counters + kCtrIndexAux;
+  hipLaunchKernelGGL(lcp_direct_kernel,
+                     dim3(u32(ceil_div(ceil_div(n, u64(kLcpRows) * kWave), 256 / kWave))),
+                     dim3(256), 0, s, d_text, n, d_sa, d_lcp, phi, long_bits, any_long,
+                     ctx->counters + kCtrError);
   const u64 threads = ceil_div(n, kLcpStretch);
   hipLaunchKernelGGL(plcp_long_kernel, dim3(u32(ceil_div(threads, 256))), dim3(256), 0, s,
-                     d_text, n, long_bits, phi);
-  hipLaunchKernelGGL(lcp_long_gather_kernel, dim3(g), dim3(256), 0, s, d_sa, n, phi, d_lcp);
+                     d_text, n, long_bits, any_long, phi);
+  hipLaunchKernelGGL(lcp_long_gather_kernel, dim3(g), dim3(256), 0, s, d_sa, n, phi, any_long,
+                     d_lcp);
   return finish(ctx, s);
 }
 
@@ -430,9 +591,10 @@ sa_status sa_bwt(sa_ctx* ctx, const uint8_t* d_text, uint64_t n, const uint32_t*
   if (hipSetDevice(ctx->device) != hipSuccess) return SA_EDEVICE;
   launch_fill_u64(ctx->counters, kCtrCount, 0, s);
   u64* d_dollar = ctx->counters + kCtrIndexAux;
-  const u32 g = grid_for(n + 1, 256, 8192);
-  hipLaunchKernelGGL(find_dollar_kernel, dim3(g), dim3(256), 0, s, d_sa, n, d_dollar);
-  hipLaunchKernelGGL(bwt_kernel, dim3(g), dim3(256), 0, s, d_text, n, d_sa, d_dollar, 1, d_bwt,
+  hipLaunchKernelGGL(find_dollar_kernel, dim3(grid_for(n, 256 * 16, 4096)), dim3(256), 0, s, d_sa,
+                     n, (reinterpret_cast<uintptr_t>(d_sa) & 15) == 0, d_dollar);
+  hipLaunchKernelGGL(bwt_kernel, dim3(grid_for(n, 1024, 65536)), dim3(256), 0, s, d_text, n, d_sa,
+                     d_dollar, 1, (reinterpret_cast<uintptr_t>(d_bwt) & 3) == 0, d_bwt,
                      ctx->counters + kCtrError);
   const sa_status st = finish(ctx, s);
   if (st != SA_OK) return st;
@@ -457,19 +619,16 @@ sa_status sa_fm_create(sa_fm** out, sa_ctx* ctx, const uint8_t* d_text, uint64_t
   fm->nblocks = ceil_div(rows, kOccBlock) + 1;  // one more: Occ(c, rows) when rows % 256 == 0
   // Byte counts -> C, the present bytes and their codes (on the host: 256 values).
   std::vector<u64> counts(256, 0);
-  u64* tmp = nullptr;
-  if (!dev_alloc(&tmp, 256)) {
-    delete fm;
-    return SA_ENOMEM;
-  }
-  (void)hipMemsetAsync(tmp, 0, 256 * sizeof(u64), s);
+  // (In the context's sample array, which only a build's rounds use.)
+  u64* tmp = ctx->sample;
+  static_assert(kLazySamples >= 256, "the byte counts fit");
+  launch_fill_u64(tmp, 256, 0, s);
   if (n)
-    hipLaunchKernelGGL(byte_count_kernel, dim3(grid_for(n, 256 * 16, 2048)), dim3(256), 0, s,
-                       d_text, n, tmp);
+    hipLaunchKernelGGL(byte_count_kernel, dim3(grid_for(n, 256 * 16 * 4, 1024)), dim3(256), 0, s,
+                       d_text, n, (reinterpret_cast<uintptr_t>(d_text) & 15) == 0, tmp);
   if (hipMemcpyAsync(counts.data(), tmp, 256 * sizeof(u64), hipMemcpyDeviceToHost, s) !=
           hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess) {
-    (void)hipFree(tmp);
     delete fm;
     return SA_EDEVICE;
   }
@@ -492,11 +651,10 @@ sa_status sa_fm_create(sa_fm** out, sa_ctx* ctx, const uint8_t* d_text, uint64_t
   const size_t b_bytes = (fm->nblocks * kOccBlock + 255) / 256 * 256;
   const size_t occ_bytes = size_t(std::max<u32>(fm->sigma, 1)) * fm->stride_b * 4;
   const size_t off_occ = b_bytes, off_C = off_occ + occ_bytes, off_code = off_C + 256 * 8,
-               off_sym = off_code + 512, off_tot = off_sym + 256,
+               off_tot = off_code + 512 + 256,
                total = off_tot + size_t(std::max<u32>(fm->sigma, 1)) * chunks * 8;
   if (hipMalloc(&fm->dev, total) != hipSuccess) {
     (void)hipGetLastError();
-    (void)hipFree(tmp);
     delete fm;
     return SA_ENOMEM;
   }
@@ -505,40 +663,37 @@ sa_status sa_fm_create(sa_fm** out, sa_ctx* ctx, const uint8_t* d_text, uint64_t
   fm->occ = reinterpret_cast<u32*>(p + off_occ);
   fm->C = reinterpret_cast<u64*>(p + off_C);
   fm->code = reinterpret_cast<u16*>(p + off_code);
-  u8* d_sym = reinterpret_cast<u8*>(p + off_sym);
   u64* totals = reinterpret_cast<u64*>(p + off_tot);
   sa_status st = SA_OK;
-  if (hipMemsetAsync(fm->B, 0, b_bytes, s) != hipSuccess ||
-      hipMemcpyAsync(fm->C, C.data(), 256 * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-      hipMemcpyAsync(fm->code, code.data(), 512, hipMemcpyHostToDevice, s) != hipSuccess ||
-      (fm->sigma && hipMemcpyAsync(d_sym, sym.data(), fm->sigma, hipMemcpyHostToDevice, s) !=
-                        hipSuccess))
+  // The rows past the last one (the pad of its block and the last, empty block).
+  launch_fill_tail(fm->B, rows, b_bytes, s);
+  if (hipMemcpyAsync(fm->C, C.data(), 256 * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
+      hipMemcpyAsync(fm->code, code.data(), 512, hipMemcpyHostToDevice, s) != hipSuccess)
     st = SA_EDEVICE;
-  if (st == SA_OK && n) {
+  u64* d_dollar = ctx->counters + kCtrIndexAux;
+  if (st == SA_OK) {
     launch_fill_u64(ctx->counters, kCtrCount, 0, s);
-    u64* d_dollar = ctx->counters + kCtrIndexAux;
-    const u32 g = grid_for(rows, 256, 8192);
-    hipLaunchKernelGGL(find_dollar_kernel, dim3(g), dim3(256), 0, s, d_sa, n, d_dollar);
-    hipLaunchKernelGGL(bwt_kernel, dim3(g), dim3(256), 0, s, d_text, n, d_sa, d_dollar, 0, fm->B,
-                       ctx->counters + kCtrError);
-    st = finish(ctx, s);
-    if (st == SA_OK) {
-      fm->dollar = ctx->h_counters[kCtrIndexAux];
-      if (fm->dollar == 0 || fm->dollar > n) st = SA_EDEVICE;
-    }
+    if (n)
+      hipLaunchKernelGGL(bwt_kernel, dim3(grid_for(rows, 1024, 65536)), dim3(256), 0, s, d_text, n,
+                         d_sa, d_dollar, 0, 1, fm->B, ctx->counters + kCtrError);
   }
   if (st == SA_OK && fm->sigma) {
     hipLaunchKernelGGL(occ_count_kernel, dim3(u32(ceil_div(fm->nblocks, kOccGroup))), dim3(256),
-                       0, s, fm->B, rows, fm->nblocks, n ? fm->dollar : ~u64(0), d_sym,
+                       fm->sigma * kOccGroup * 2, s, fm->B, rows, fm->nblocks, d_dollar, fm->code,
                        fm->sigma, fm->stride_b, fm->occ);
     hipLaunchKernelGGL(occ_scan_chunks_kernel, dim3(u32(chunks), fm->sigma), dim3(256), 0, s,
                        fm->occ, fm->nblocks, fm->stride_b, chunks, totals);
     hipLaunchKernelGGL(occ_scan_totals_kernel, dim3(fm->sigma), dim3(64), 0, s, totals, chunks);
     hipLaunchKernelGGL(occ_scan_add_kernel, dim3(u32(chunks), fm->sigma), dim3(256), 0, s,
                        fm->occ, fm->nblocks, fm->stride_b, chunks, totals);
-    if (hipStreamSynchronize(s) != hipSuccess || hipGetLastError() != hipSuccess) st = SA_EDEVICE;
   }
-  (void)hipFree(tmp);
+  if (st == SA_OK) {
+    st = finish(ctx, s);  // waits for the index and reports the kernels' errors
+    if (st == SA_OK && n) {
+      fm->dollar = ctx->h_counters[kCtrIndexAux];
+      if (fm->dollar == 0 || fm->dollar > n) st = SA_EDEVICE;
+    }
+  }
   if (st != SA_OK) {
     sa_fm_destroy(fm);
     return st;
@@ -554,8 +709,7 @@ sa_status sa_fm_count(sa_fm* fm, const uint8_t* d_patterns, const uint64_t* d_of
   if (!d_offsets || !d_ranges) return SA_EINVAL;
   if (hipSetDevice(fm->device) != hipSuccess) return SA_EDEVICE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const u64 waves_per_block = 256 / kWave;
-  const u32 g = grid_for(num_patterns, u32(waves_per_block), 16384);
+  const u32 g = grid_for(num_patterns, 2 * (256 / kWave), 16384);
   hipLaunchKernelGGL(fm_count_kernel, dim3(g), dim3(256), 0, s, fm->B, fm->n, fm->dollar,
                      fm->occ, fm->stride_b, fm->C, fm->code, d_patterns, d_offsets, num_patterns,
                      d_ranges);
