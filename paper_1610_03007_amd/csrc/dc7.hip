@@ -117,31 +117,75 @@ __global__ __launch_bounds__(256) void d7_pack_rest_kernel(D7Text txt, u64 nns,
   }
 }
 
+// The position's class p mod 7 sits in the top bits of the ranks (which stay below
+// 2^31: the sample is 3/7 of fewer than 2^32 suffixes).
 struct D7Rec {
   u64 chars;   // characters p .. p + 6
   u32 rk[3];   // ranks of the sample positions in p .. p + 6, by cover class
   u32 pos;
 };
+constexpr u32 kD7RankBits = 31;
+constexpr u32 kD7RankMask = (1u << kD7RankBits) - 1;
 
+// rankp is zero from n to n + 7.
 __device__ inline D7Rec d7_rec(const D7Text& txt, const u32* __restrict__ rankp, u64 p) {
   D7Rec r;
-  r.chars = txt.chars(p, 7);
-  const u32 a = u32(p % 7);
-  r.rk[0] = u32(d7_rank(rankp, txt.n, p + (7 - a) % 7));
-  r.rk[1] = u32(d7_rank(rankp, txt.n, p + (8 - a) % 7));
-  r.rk[2] = u32(d7_rank(rankp, txt.n, p + (10 - a) % 7));
+  if (p >= txt.n) p = 0;  // (not a position: only after an error that is reported later)
+  // One read of eight bytes and two of four ranks, at the position's own alignment:
+  // a random read costs per instruction and lane, not per byte (seven byte reads
+  // and three rank reads: 15.4 ms for 2^27 records).
+  u32 w[8];
+  __builtin_memcpy(w, rankp + p, 16);
+  if (p + 8 <= txt.n) {
+    u64 c;
+    __builtin_memcpy(&c, txt.t + p, 8);
+    u64 v = 0;
+#pragma unroll
+    for (int q = 0; q < 7; ++q) v = (v << 9) | (((c >> (8 * q)) & 0xFFu) + 1);
+    r.chars = v;
+  } else {
+    r.chars = txt.chars(p, 7);
+  }
+  __builtin_memcpy(w + 4, rankp + p + 4, 16);
+  const u32 a = u32(p) % 7u;
+  // Offset of the next position of class 0, 1 and 3.
+  const u32 off[3] = {a == 0 ? 0u : 7u - a, a <= 1 ? 1u - a : 8u - a, a <= 3 ? 3u - a : 10u - a};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    u32 v = w[0];
+#pragma unroll
+    for (u32 q = 1; q < 7; ++q) v = off[k] == q ? w[q] : v;
+    r.rk[k] = v | (((a >> k) & 1u) << kD7RankBits);
+  }
   r.pos = u32(p);
   return r;
 }
 
-__device__ inline bool d7_less(const D7Rec& x, const D7Rec& y) {
-  const u32 a = x.pos % 7, b = y.pos % 7;
-  const u32 k = d7_offset(a, b);
-  if (k > 0) {
-    const u64 cx = x.chars >> (9 * (7 - k)), cy = y.chars >> (9 * (7 - k));
-    if (cx != cy) return cx < cy;
+// Per pair of classes (a, b): the offset k, and the slots of the ranks that decide
+// for the first and the second suffix: k | slot << 3 | slot << 5, in LDS.
+__device__ inline void d7_load_table(u8* s_tab) {
+  for (u32 i = threadIdx.x; i < 64; i += blockDim.x) {
+    const u32 a = i >> 3, b = i & 7u;
+    const u32 k = a < 7 && b < 7 ? d7_offset(a, b) : 0;
+    s_tab[i] = u8(k | (d7_slot((a + k) % 7) << 3) | (d7_slot((b + k) % 7) << 5));
   }
-  return x.rk[d7_slot((a + k) % 7)] < y.rk[d7_slot((b + k) % 7)];
+  __syncthreads();
+}
+
+__device__ inline u32 d7_class(const D7Rec& r) {
+  return (r.rk[0] >> kD7RankBits) | ((r.rk[1] >> kD7RankBits) << 1) |
+         ((r.rk[2] >> kD7RankBits) << 2);
+}
+
+__device__ inline bool d7_less(const D7Rec& x, const D7Rec& y, const u8* s_tab) {
+  const u32 e = s_tab[d7_class(x) * 8 + d7_class(y)];
+  const u32 sh = 9 * (7 - (e & 7u));  // (63: no characters)
+  const u64 cx = x.chars >> sh, cy = y.chars >> sh;
+  if (cx != cy) return cx < cy;
+  const u32 sx = (e >> 3) & 3u, sy = e >> 5;
+  const u32 rx = sx == 0 ? x.rk[0] : sx == 1 ? x.rk[1] : x.rk[2];
+  const u32 ry = sy == 0 ? y.rk[0] : sy == 1 ? y.rk[1] : y.rk[2];
+  return (rx & kD7RankMask) < (ry & kD7RankMask);
 }
 
 // Records of the sorted non-sample suffixes (the sort's final value buffer)
@@ -163,6 +207,8 @@ constexpr int kD7Tile = 256 * kD7Items;
 __global__ __launch_bounds__(256) void d7_partition_kernel(const D7Rec* __restrict__ a, u64 na,
                                                           const D7Rec* __restrict__ b, u64 nb,
                                                           u64 ntiles, u64* __restrict__ split) {
+  __shared__ u8 s_tab[64];
+  d7_load_table(s_tab);
   const u64 m = na + nb;
   for (u64 t = u64(blockIdx.x) * blockDim.x + threadIdx.x; t <= ntiles;
        t += u64(gridDim.x) * blockDim.x) {
@@ -170,7 +216,7 @@ __global__ __launch_bounds__(256) void d7_partition_kernel(const D7Rec* __restri
     u64 lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
     while (lo < hi) {
       const u64 mid = (lo + hi) >> 1;
-      if (d7_less(a[mid], b[d - 1 - mid]))
+      if (d7_less(a[mid], b[d - 1 - mid], s_tab))
         lo = mid + 1;
       else
         hi = mid;
@@ -186,7 +232,10 @@ __global__ __launch_bounds__(256) void d7_merge_tile_kernel(
     const D7Rec* __restrict__ a, u64 na, const D7Rec* __restrict__ b, u64 nb,
     const u64* __restrict__ split, D7Rec* __restrict__ out, u32* __restrict__ out_pos,
     u64* __restrict__ counters) {
-  __shared__ D7Rec s_a[kD7Tile], s_b[kD7Tile];
+  // The two runs one after the other: together at most a tile.
+  __shared__ D7Rec s_rec[kD7Tile];
+  __shared__ u8 s_tab[64];
+  d7_load_table(s_tab);
   const u64 m = na + nb;
   const u64 t = blockIdx.x;
   const u64 d0 = t * kD7Tile;
@@ -200,15 +249,17 @@ __global__ __launch_bounds__(256) void d7_merge_tile_kernel(
                (unsigned long long)kErrBounds);
     return;
   }
-  for (u32 k = threadIdx.x; k < ka; k += blockDim.x) s_a[k] = a[a0 + k];
-  for (u32 k = threadIdx.x; k < kb; k += blockDim.x) s_b[k] = b[b0 + k];
+  const D7Rec* const s_a = s_rec;
+  const D7Rec* const s_b = s_rec + ka;
+  for (u32 k = threadIdx.x; k < nt; k += blockDim.x)
+    s_rec[k] = k < ka ? a[a0 + k] : b[b0 + (k - ka)];
   __syncthreads();
   const u32 dd = threadIdx.x * kD7Items;
   if (dd >= nt) return;
   u32 lo = dd > kb ? dd - kb : 0, hi = dd < ka ? dd : ka;
   while (lo < hi) {
     const u32 mid = (lo + hi) >> 1;
-    if (d7_less(s_a[mid], s_b[dd - 1 - mid]))
+    if (d7_less(s_a[mid], s_b[dd - 1 - mid], s_tab))
       lo = mid + 1;
     else
       hi = mid;
@@ -217,7 +268,7 @@ __global__ __launch_bounds__(256) void d7_merge_tile_kernel(
 #pragma unroll
   for (int k = 0; k < kD7Items; ++k) {
     if (dd + k >= nt) break;
-    const bool take_a = ib >= kb || (ia < ka && d7_less(s_a[ia], s_b[ib]));
+    const bool take_a = ib >= kb || (ia < ka && d7_less(s_a[ia], s_b[ib], s_tab));
     const D7Rec& r = take_a ? s_a[ia++] : s_b[ib++];
     if (out_pos)
       out_pos[d0 + dd + k] = r.pos;
