@@ -171,14 +171,19 @@ constexpr int kSortBlockDefault = 512;   // default sweep shape: 512 threads x 8
 constexpr int kSortItemsDefault = 8;
 constexpr int kSortTileMin = 2048;       // smallest tile (512 x 4); status arrays are sized for it
 constexpr int kHistBlock = 256;
-// Staged ISA writes of a re-rank over a large active set: (position, name)
-// pairs grouped by position bucket (kStageBuckets equal ranges of the text)
-// and then written one bucket after the other, so that the writes in flight
-// fall in one bucket's stretch of the ISA instead of all of it.
-constexpr int kStageBuckets = 256;
-constexpr u32 kStageMaxWgs = 1024;               // re-rank workgroups with a count row
+// Staged ISA writes of a re-rank over a large active set: (position, name) pairs
+// grouped by stretches of kStageSpan positions (in two steps above
+// kStageMaxDigits stretches), each stretch then filled in LDS and written in order.
+// A position has at most one pair, so the pairs of a stretch are given its own range
+// [first position, last position] of a buffer of n pairs and need no counting.
+constexpr int kStageShift = 14;
+constexpr u32 kStageSpan = 1u << kStageShift;    // 64 KiB of the ISA
+constexpr u32 kStageMaxDigits = 1024;            // of a grouping step
+constexpr u32 kStageFirstDigits = 256;           // of the first of two
+constexpr u32 kStageMaxSpans = u32((u64(1) << 32) >> kStageShift);
 constexpr u64 kStageMinCount = u64(1) << 22;     // active elements (read on the device)
-constexpr u64 kStageMinN = u64(1) << 26;         // text length (ISA of 256 MiB)
+constexpr u64 kStageMinN = u64(1) << 26;         // text length (below, direct writes into an
+                                                 // ISA of up to 256 MiB are faster)
 constexpr u64 kStageSkip = ~u64(0);              // staged entry: name unchanged
 
 constexpr int kRerankBlock = 256;
@@ -198,9 +203,8 @@ enum CounterSlot : int {
   kCtrIndexAux = kMaxPasses + 7,     // index builds: the row of $ in the transform
   kCtrPairI = kMaxPasses + 8,        // sort-based pairing: non-unique items paired this round
   kCtrPairU = kMaxPasses + 9,        // sort-based pairing: unique items kept for the next round
-  kCtrStage = kMaxPasses + 10,       // staged ISA writes of the last re-rank
-  kCtrSplitOver = kMaxPasses + 11,   // a bucket of the split sort overflowed: keys unsorted
-  kCtrCount = kMaxPasses + 12,
+  kCtrSplitOver = kMaxPasses + 10,   // a bucket of the split sort overflowed: keys unsorted
+  kCtrCount = kMaxPasses + 11,
 };
 
 }  // namespace sa

@@ -93,7 +93,7 @@ struct sa_ctx {
   u32* present = nullptr;
   u16* code = nullptr;
   u64* sample = nullptr;  // lazy ISA: sampled round-0 sorted keys
-  u32* stage_hist = nullptr;  // staged ISA writes: counts per (bucket, re-rank workgroup)
+  u32* stage_cur = nullptr;  // staged ISA writes: pairs placed so far per digit
   // Pinned mirror of counters | rc | plan_log, refreshed by every readback.
   void* h_mirror = nullptr;
   u64* d_mirror = nullptr;  // its device address
@@ -171,7 +171,7 @@ constexpr size_t kSmallPlan = (sizeof(SortPlan) + 255) / 256 * 256;
 constexpr size_t kSmallPresent = 256 * sizeof(u32);
 constexpr size_t kSmallCode = 256 * sizeof(u16);
 constexpr size_t kSmallSample = size_t(kLazySamples) * sizeof(u64);
-constexpr size_t kSmallStage = size_t(kStageBuckets) * kStageMaxWgs * sizeof(u32);
+constexpr size_t kSmallStage = size_t(kStageFirstDigits + kStageMaxSpans) * sizeof(u32);
 constexpr size_t kSmallBytes = kSmallHist + kMirrorBytes + kSmallCtl + kSmallPlan + kSmallPresent +
                                kSmallCode + kSmallSample + kSmallStage;
 static_assert(kSmallCounters % 8 == 0 && kSmallRoundCtl % 8 == 0, "mirror alignment");

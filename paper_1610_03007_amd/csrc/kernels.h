@@ -147,17 +147,13 @@ struct RerankArgs {
   u32* emit_vals;
   const u64* emit_base;
   u64 emit_h, emit_q;
-  // Staged ISA writes (kRerankScatterIsa, one text, stage_w != 0): when the
-  // set has at least kStageMinCount elements, element e of the sorted set
-  // leaves (position << 32 | new name), or kStageSkip for an unchanged name,
-  // at e of the key buffer the sort did not end in (stage_a or stage_b, the
-  // sort's two key buffers), and each workgroup its count per bucket
-  // (position / stage_w) at stage_hist[bucket * grid + workgroup];
-  // launch_stage_isa then writes the names.
+  // Staged ISA writes (kRerankScatterIsa, one text, stage_a set): when the set has
+  // at least kStageMinCount elements, element e of the sorted set leaves
+  // (position << 32 | new name), or kStageSkip for an unchanged name, at e of the
+  // key buffer the sort did not end in (stage_a or stage_b, the sort's two key
+  // buffers, of at least n elements); launch_stage_isa then writes the names.
   u64* stage_a;
   u64* stage_b;
-  u32* stage_hist;
-  u32 stage_w;
 };
 // The sorted set has ctl->count elements (args.count is ignored); `grid`
 // workgroups stride over its tiles of kRerankTile elements.
@@ -169,14 +165,12 @@ void launch_rerank_compact(const u64* keysA, const u64* keysB, const u32* valsA,
                            const u32* valsB, const SortPlan* plan, const RerankArgs& args,
                            const SortCtl* ctl, u32* isa, u32* sa_out, u32* act_idx, u64* act_ti,
                            u32* act_rank, u64* counters, u32 grid, hipStream_t s);
-// The ISA writes a staged re-rank of `grid` workgroups left: the per-bucket
-// counts scanned (their total to counters[kCtrStage]), the pairs grouped by
-// bucket into the key buffer the sort ended in, then written to isa. Every
-// kernel returns at once when the re-rank did not stage (fewer than
+// The ISA writes a staged re-rank left: the pairs grouped by position and written
+// to isa (through both key buffers). cur: kStageFirstDigits + kStageMaxSpans words.
+// Every kernel returns at once when the re-rank did not stage (fewer than
 // kStageMinCount elements).
-void launch_stage_isa(u64* keysA, u64* keysB, const SortPlan* plan, const SortCtl* ctl,
-                      u32* stage_hist, u32 grid, u32 stage_w, u64 n, u32* isa, u64* counters,
-                      u32 apply_grid, hipStream_t s);
+void launch_stage_isa(u64* keysA, u64* keysB, const SortPlan* plan, const SortCtl* ctl, u32* cur,
+                      u64 n, u32* isa, u64* counters, hipStream_t s);
 
 // ISA after round 0. Eager: the round-0 re-rank again, with kRerankIsaOnly.
 // Lazy: survivors scattered from the active list and marked in the live-position

@@ -255,23 +255,22 @@ void run_rerank(sa_ctx* c, const Bufs& bf, const RerankArgs& args, u32* d_sa, u6
   Tracer t(c, s, (args.mode & kRerankIsaOnly) ? SA_KERNEL_ISA_SCATTER : SA_KERNEL_RERANK, bytes);
   const u32 grid = u32(std::min<u64>(std::max<u64>(1, ceil_div(bound, kRerankTile)),
                                      u64(c->num_cus) * rerank_wgs_per_cu(args.tie != 0)));
-  // Names of one long text go through the staged writes (when the device
-  // count turns out large enough): its ISA is far larger than the caches.
+  // Names of one long text go through the staged writes (when the device count
+  // turns out large enough), if both key buffers hold n pairs. (Those carved for the
+  // rounds of a lazy ISA do not: both lie in one of the context's, kA at its start.)
   RerankArgs a = args;
   const bool stage = (a.mode & kRerankScatterIsa) && !(a.mode & (kRerankPairOut | kRerankEmit)) &&
-                     !a.tbase && a.n >= kStageMinN && grid <= kStageMaxWgs && c->stage_isa;
+                     !a.tbase && a.n >= kStageMinN && a.n <= c->cap && bf.kA == c->keysA &&
+                     bf.kB == c->keysB && c->stage_isa;
   if (stage) {
     a.stage_a = bf.kA;
     a.stage_b = bf.kB;
-    a.stage_hist = c->stage_hist;
-    a.stage_w = u32(ceil_div(a.n, u64(kStageBuckets)));
   }
   launch_rerank_compact(bf.kA, bf.kB, bf.vA, bf.vB, c->plan, a, c->ctl, c->isa, d_sa,
                         a.tbase ? nullptr : c->act_idx, a.tbase ? c->act_ti : nullptr,
                         c->act_rank, c->counters, grid, s);
   if (stage)
-    launch_stage_isa(bf.kA, bf.kB, c->plan, c->ctl, c->stage_hist, grid, a.stage_w, a.n, c->isa,
-                     c->counters, u32(c->num_cus) * 4, s);
+    launch_stage_isa(bf.kA, bf.kB, c->plan, c->ctl, c->stage_cur, a.n, c->isa, c->counters, s);
 }
 
 // Re-rank arguments of a single text: round 0 (one group, every rank 1) or a
@@ -687,7 +686,7 @@ void bind_small(sa_ctx* c, char* p) {
   p += kSmallCode;
   c->sample = reinterpret_cast<u64*>(p);
   p += kSmallSample;
-  c->stage_hist = reinterpret_cast<u32*>(p);
+  c->stage_cur = reinterpret_cast<u32*>(p);
 }
 
 // ---------------------------------------------------------------------------
@@ -777,6 +776,7 @@ struct WorkspaceView {
   u32* present;
   u16* code;
   u64* sample;
+  u32* stage_cur;
   u32 gen;
   bool trace;
   bool graphs_blocked;
@@ -787,7 +787,7 @@ WorkspaceView save_view(const sa_ctx* c) {
                        c->isa,      c->live,     c->act_idx,      c->act_rank, c->status,
                        c->hist_in,  c->hist_run, c->tickets,      c->counters, c->rc,
                        c->plan_log, c->ctl,      c->plan,         c->present,  c->code,
-                       c->sample,   c->gen,      c->trace,        c->graphs_blocked};
+                       c->sample,   c->stage_cur, c->gen,         c->trace,    c->graphs_blocked};
 }
 
 void restore_view(sa_ctx* c, const WorkspaceView& v) {
@@ -812,6 +812,7 @@ void restore_view(sa_ctx* c, const WorkspaceView& v) {
   c->present = v.present;
   c->code = v.code;
   c->sample = v.sample;
+  c->stage_cur = v.stage_cur;
   c->gen = v.gen;
   c->trace = v.trace;
   c->graphs_blocked = v.graphs_blocked;

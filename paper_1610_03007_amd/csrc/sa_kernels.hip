@@ -1291,7 +1291,6 @@ void rerank_compact_kernel(
   __shared__ u32 s_svr[T];  // new name
   __shared__ u32 s_fill, s_tile_at, s_flush_n;
   __shared__ u64 s_flush_at;
-  __shared__ u32 s_bh[kStageBuckets];  // staged ISA writes per position bucket
 
   const u32 fb = plan->final_buf;
   const u64* keys = fb ? keysB : keysA;
@@ -1309,10 +1308,8 @@ void rerank_compact_kernel(
   const u64 lt_mask = (u64(1) << lane) - 1;
   const u64 tiles = ceil_div(count, u64(T));
   if (tid == 0) s_fill = 0;  // ordered before its use by the tile's first barrier
-  const bool staged = scatter && a.stage_w != 0 && count >= kStageMinCount;
+  const bool staged = scatter && a.stage_a && count >= kStageMinCount;
   u64* const stage = fb ? a.stage_a : a.stage_b;  // the key buffer the sort did not end in
-  if (staged)
-    for (int b = tid; b < kStageBuckets; b += kRerankBlock) s_bh[b] = 0;
   bool bad = false;
   // Writes buffer entries [0, s_flush_n) at s_flush_at (every thread).
   auto flush = [&]() {
@@ -1563,13 +1560,7 @@ void rerank_compact_kernel(
     // that did not change (a group that did not split, or the first sub-group
     // of one that did) is not written again.
     if (staged) {
-      u64 w = kStageSkip;
-      if (first_round || nr != r0) {
-        const u32 pos = u32(gb + v[r]);
-        w = (u64(pos) << 32) | u64(u32(nr));
-        atomicAdd(&s_bh[pos / a.stage_w], 1u);
-      }
-      stage[e] = w;
+      stage[e] = first_round || nr != r0 ? (u64(u32(gb + v[r])) << 32) | u64(u32(nr)) : kStageSkip;
     } else if (scatter && (first_round || nr != r0)) {
       isa[gb + v[r]] = u32(nr);
     }
@@ -1593,9 +1584,6 @@ void rerank_compact_kernel(
   }
   __syncthreads();
   if (s_flush_n) flush();
-  if (staged)
-    for (int b = tid; b < kStageBuckets; b += kRerankBlock)
-      a.stage_hist[size_t(b) * gridDim.x + blockIdx.x] = s_bh[b];
   if (bad)
     atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrError),
              (unsigned long long)kErrBounds);
@@ -1633,126 +1621,198 @@ void launch_rerank_compact(const u64* keysA, const u64* keysB, const u32* valsA,
 }
 
 // ---------------------------------------------------------------------------
-// Staged ISA writes of a re-rank (see RerankArgs::stage_w). A random 4-byte
-// write costs a memory transaction of its own; with the pairs grouped by
-// position bucket, the writes a wave of the last kernel issues fall in one
-// 1/kStageBuckets stretch of the ISA, whose lines the caches then combine.
+// Staged ISA writes of a re-rank (see RerankArgs::stage_a). A random 4-byte write
+// costs a request of its own wherever its line is (about 85e9 lanes a second, the
+// same into 2 MiB that stay in an L2 as into 4 GiB), so the pairs are grouped until
+// a stretch of the ISA fits LDS, where random writes are cheap, and leave in order.
 
-// Exclusive scan, in place, of the per-(bucket, workgroup) counts in
-// bucket-major order (one workgroup); the total to counters[kCtrStage].
-__global__ __launch_bounds__(1024) void stage_scan_kernel(const SortCtl* __restrict__ ctl,
-                                                          u32* __restrict__ hist, u32 entries,
-                                                          u64* __restrict__ counters) {
-  if (ctl->count < kStageMinCount) return;
-  __shared__ u32 s_w[1024 / kWave];
+constexpr int kStageItems = 12;  // pairs per thread of a grouping step
+
+// One grouping step: pairs of positions with the digit pos >> shift (below a parent
+// of positions [parent << pshift, ...), FIRST: of all) into that digit's range of
+// `out`. Bound by memory: 16 bytes a pair, each digit's run of a tile written from
+// LDS; a tile reserves its runs with one atomic add per digit.
+// FIRST: the staged pairs (tile blockIdx); else the pairs of parent
+// blockIdx / per_parent, cur_parent[parent] of them.
+// 2^30 pairs: 4.6 ms the first step (1024 threads; 7.0 with 512, whose tiles reserve
+// twice as often on the same 256 cursors), 3.7 ms the second (512; 4.6 with 1024, one
+// workgroup a CU).
+template <bool FIRST, int BLOCK>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
+void stage_group_kernel(u64* __restrict__ keysA, u64* __restrict__ keysB,
+                        const SortPlan* __restrict__ plan, const SortCtl* __restrict__ ctl,
+                        const u32* __restrict__ cur_parent, int pshift, u32 per_parent,
+                        u32* __restrict__ cur, int shift, u64 n, u64* __restrict__ counters) {
+  constexpr u32 TILE = BLOCK * kStageItems;
+  constexpr int DPT = kStageMaxDigits / BLOCK;  // digits per thread
+  static_assert(DPT * BLOCK == int(kStageMaxDigits), "whole digits");
+  const u64 count = ctl->count;
+  if (count < kStageMinCount || counters[kCtrSplitOver]) return;
+  // The re-rank staged into the buffer the sort did not end in.
+  const u32 fb = plan->final_buf;
+  const u64* in = (fb != 0) == FIRST ? keysA : keysB;
+  u64* out = (fb != 0) == FIRST ? keysB : keysA;
+  __shared__ u64 s_buf[TILE];
+  __shared__ u32 s_cnt[kStageMaxDigits];
+  __shared__ u32 s_delta[kStageMaxDigits];
+  __shared__ u32 s_w[BLOCK / kWave];
   const u32 tid = threadIdx.x;
-  const u32 per = (entries + 1023) / 1024;
-  const u32 lo = tid * per < entries ? tid * per : entries;
-  const u32 hi = lo + per < entries ? lo + per : entries;
-  u32 sum = 0;
-  for (u32 i = lo; i < hi; ++i) sum += hist[i];
+  u64 base, left, first = 0;  // first: first position of the parent
+  if (FIRST) {
+    base = u64(blockIdx.x) * TILE;
+    if (base >= count) return;
+    left = count - base;
+  } else {
+    const u32 parent = blockIdx.x / per_parent;
+    const u64 off = u64(blockIdx.x % per_parent) * TILE;
+    first = u64(parent) << pshift;
+    // (At most the parent's positions: a pair each.)
+    u64 size = u64(1) << pshift;
+    if (size > n - first) size = n - first;
+    if (cur_parent[parent] < size) size = cur_parent[parent];
+    if (off >= size) return;
+    base = first + off;
+    left = size - off;
+  }
+  const u32 d0 = u32(first >> shift);  // digit of the parent's first position
+  u64 w[kStageItems];
+#pragma unroll
+  for (int j = 0; j < kStageItems; ++j) {
+    const u32 q = u32(j) * BLOCK + tid;
+    w[j] = q < left ? __builtin_nontemporal_load(in + base + q) : kStageSkip;
+  }
+  for (u32 b = tid; b < kStageMaxDigits; b += BLOCK) s_cnt[b] = 0;
+  __syncthreads();
+  bool bad = false;
+  u32 rank[kStageItems];
+#pragma unroll
+  for (int j = 0; j < kStageItems; ++j) {
+    rank[j] = 0;
+    if (w[j] == kStageSkip) continue;
+    const u64 pos = w[j] >> 32;
+    const u32 d = u32(pos >> shift) - d0;
+    if (pos >= n || d >= kStageMaxDigits) {
+      bad = true;
+      w[j] = kStageSkip;
+      continue;
+    }
+    rank[j] = atomicAdd(&s_cnt[d], 1u);
+  }
+  __syncthreads();
+  // Digits DPT * tid + y: their starts in the tile and in the output.
+  u32 c[DPT], sum = 0;
+#pragma unroll
+  for (int y = 0; y < DPT; ++y) {
+    c[y] = s_cnt[DPT * tid + y];
+    sum += c[y];
+  }
   const u32 inc = wave_inclusive_sum(sum);
   if (lane_id() == kWave - 1) s_w[tid / kWave] = inc;
   __syncthreads();
-  u32 run = inc - sum;
-  for (u32 w = 0; w < tid / kWave; ++w) run += s_w[w];
-  for (u32 i = lo; i < hi; ++i) {
-    const u32 x = hist[i];
-    hist[i] = run;
-    run += x;
+  u32 off = 0, pairs = 0;
+#pragma unroll
+  for (u32 v = 0; v < BLOCK / kWave; ++v) {
+    if (v < tid / kWave) off += s_w[v];
+    pairs += s_w[v];
   }
-  if (tid == 1023) counters[kCtrStage] = run;
-}
-
-// Each workgroup takes the tiles its re-rank workgroup took (same grid, same
-// tile order) and moves their staged pairs to the scanned offsets of their
-// buckets in the key buffer the sort ended in.
-__global__ __launch_bounds__(256) void stage_partition_kernel(
-    u64* __restrict__ keysA, u64* __restrict__ keysB, const SortPlan* __restrict__ plan,
-    const SortCtl* __restrict__ ctl, const u32* __restrict__ hist, u32 stage_w, u64 n,
-    u64* __restrict__ counters) {
-  constexpr int T = kRerankTile;
-  constexpr int PER = T / 256;
-  const u64 count = ctl->count;
-  if (count < kStageMinCount) return;
-  const u32 fb = plan->final_buf;
-  const u64* stage = fb ? keysA : keysB;
-  u64* out = fb ? keysB : keysA;
-  __shared__ u32 s_off[kStageBuckets], s_cnt[kStageBuckets];
-  const int tid = threadIdx.x;
-  for (int b = tid; b < kStageBuckets; b += 256) {
-    s_off[b] = hist[size_t(b) * gridDim.x + blockIdx.x];
-    s_cnt[b] = 0;
+  u32 start = off + inc - sum;
+#pragma unroll
+  for (int y = 0; y < DPT; ++y) {
+    const u32 b = DPT * tid + y, dg = d0 + b;  // dg: the digit among all
+    const u32 o = c[y] ? (dg << shift) + atomicAdd(&cur[dg], c[y]) : 0;
+    s_cnt[b] = start;
+    s_delta[b] = o - start;  // modulo 2^32
+    start += c[y];
   }
   __syncthreads();
-  const u64 total = counters[kCtrStage];
-  const u64 tiles = ceil_div(count, u64(T));
-  bool bad = false;
-  for (u64 tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    u64 w[PER];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const u64 e = tile * T + u64(j) * 256 + tid;
-      w[j] = e < count ? stage[e] : kStageSkip;
-    }
+  for (int j = 0; j < kStageItems; ++j)
+    if (w[j] != kStageSkip) s_buf[s_cnt[(u32(w[j] >> 32) >> shift) - d0] + rank[j]] = w[j];
+  __syncthreads();
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      if (w[j] == kStageSkip) continue;
-      const u64 pos = w[j] >> 32;
-      if (pos >= n) {
+  for (int j = 0; j < kStageItems; ++j) {
+    const u32 q = u32(j) * BLOCK + tid;
+    if (q < pairs) {
+      const u64 x = s_buf[q];
+      const u32 g = u32(x >> 32) >> shift;
+      const u32 o = s_delta[g - d0] + q;
+      if (o < n && (o >> shift) == g)
+        out[o] = x;
+      else
         bad = true;
-        continue;
-      }
-      const u32 b = u32(pos) / stage_w;  // < kStageBuckets: stage_w >= n / kStageBuckets
-      const u64 slot = u64(s_off[b]) + atomicAdd(&s_cnt[b], 1u);
-      if (slot >= total) {
-        bad = true;
-        continue;
-      }
-      out[slot] = w[j];
     }
-    __syncthreads();
-    for (int b = tid; b < kStageBuckets; b += 256) {
-      s_off[b] += s_cnt[b];
-      s_cnt[b] = 0;
-    }
-    __syncthreads();
   }
   if (bad)
     atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrError),
              (unsigned long long)kErrBounds);
 }
 
-// ISA[position] = name for the grouped pairs, in order: the threads in flight
-// write into one or two buckets' stretches. Scattered 4-byte writes run
-// fastest with few in flight: about four 256-thread workgroups per CU (twice
-// as many take twice as long).
-__global__ __launch_bounds__(256) void stage_apply_kernel(const u64* __restrict__ keysA,
-                                                          const u64* __restrict__ keysB,
-                                                          const SortPlan* __restrict__ plan,
-                                                          const SortCtl* __restrict__ ctl,
-                                                          const u64* __restrict__ counters, u64 n,
-                                                          u32* __restrict__ isa) {
-  if (ctl->count < kStageMinCount) return;
-  const u64* in = plan->final_buf ? keysB : keysA;
-  const u64 total = counters[kCtrStage];
-  const u64 stride = u64(gridDim.x) * blockDim.x;
-  for (u64 e = u64(blockIdx.x) * blockDim.x + threadIdx.x; e < total; e += stride) {
-    const u64 w = in[e];
-    const u64 pos = w >> 32;
-    if (pos < n) isa[pos] = u32(w);
+// A stretch of the ISA per workgroup: its pairs to LDS, the whole stretch out in
+// order (with the names that stay read first, unless every position has a pair).
+// Few pairs are written one by one. Bound by memory: 8 bytes a pair, 4 or 8 a
+// position.
+constexpr int kFillBlock = 512;
+__global__ __launch_bounds__(kFillBlock) void stage_fill_kernel(
+    const u64* __restrict__ keysA, const u64* __restrict__ keysB,
+    const SortPlan* __restrict__ plan, const SortCtl* __restrict__ ctl,
+    const u32* __restrict__ cur, int two_steps, const u64* __restrict__ counters, u64 n,
+    u32* __restrict__ isa) {
+  const u64 count = ctl->count;
+  if (count < kStageMinCount || counters[kCtrSplitOver]) return;
+  const u32 fb = plan->final_buf;
+  const u64* in = (fb != 0) == (two_steps != 0) ? keysA : keysB;
+  __shared__ u32 s_isa[kStageSpan];
+  const u32 tid = threadIdx.x;
+  const u64 p0 = u64(blockIdx.x) * kStageSpan;
+  const u32 span = n - p0 < kStageSpan ? u32(n - p0) : kStageSpan;
+  u32 m = cur[blockIdx.x];
+  if (m == 0) return;
+  if (m > span) m = span;  // (the grouping has reported it)
+  if (m < span / 16) {
+    for (u32 i = tid; i < m; i += kFillBlock) {
+      const u64 w = in[p0 + i];
+      if ((w >> 32) - p0 < span) isa[w >> 32] = u32(w);
+    }
+    return;
   }
+  if (m < span) {
+    for (u32 i = tid; i < span; i += kFillBlock) s_isa[i] = isa[p0 + i];
+    __syncthreads();
+  }
+  for (u32 i = tid; i < m; i += kFillBlock) {
+    const u64 w = __builtin_nontemporal_load(in + p0 + i);
+    const u64 at = (w >> 32) - p0;
+    if (at < span) s_isa[at] = u32(w);
+  }
+  __syncthreads();
+  for (u32 i = tid; i < span; i += kFillBlock) isa[p0 + i] = s_isa[i];
 }
 
-void launch_stage_isa(u64* keysA, u64* keysB, const SortPlan* plan, const SortCtl* ctl,
-                      u32* stage_hist, u32 grid, u32 stage_w, u64 n, u32* isa, u64* counters,
-                      u32 apply_grid, hipStream_t s) {
-  hipLaunchKernelGGL(stage_scan_kernel, dim3(1), dim3(1024), 0, s, ctl, stage_hist,
-                     u32(kStageBuckets) * grid, counters);
-  hipLaunchKernelGGL(stage_partition_kernel, dim3(grid), dim3(256), 0, s, keysA, keysB, plan, ctl,
-                     stage_hist, stage_w, n, counters);
-  hipLaunchKernelGGL(stage_apply_kernel, dim3(apply_grid), dim3(256), 0, s, keysA, keysB, plan,
-                     ctl, counters, n, isa);
+void launch_stage_isa(u64* keysA, u64* keysB, const SortPlan* plan, const SortCtl* ctl, u32* cur,
+                      u64 n, u32* isa, u64* counters, hipStream_t s) {
+  const u32 spans = u32(ceil_div(n, kStageSpan));
+  u32* cur2 = cur + kStageFirstDigits;
+  launch_fill_u32(cur, kStageFirstDigits + spans, 0, s);
+  // (A dense round ranks all n suffixes, whatever bound its launches have.)
+  constexpr int kFirst = 1024, kSecond = 512;
+  const u32 tiles = u32(ceil_div(n, kFirst * kStageItems));
+  const bool two = spans > kStageMaxDigits;
+  if (!two) {
+    hipLaunchKernelGGL((stage_group_kernel<true, kFirst>), dim3(tiles), dim3(kFirst), 0, s, keysA,
+                       keysB, plan, ctl, nullptr, 0, 0u, cur2, kStageShift, n, counters);
+  } else {
+    int shift = kStageShift;
+    while (ceil_div(n, u64(1) << shift) > kStageFirstDigits) ++shift;
+    const u32 parents = u32(ceil_div(n, u64(1) << shift));
+    const u32 per_parent = u32(ceil_div(u64(1) << shift, kSecond * kStageItems));
+    hipLaunchKernelGGL((stage_group_kernel<true, kFirst>), dim3(tiles), dim3(kFirst), 0, s, keysA,
+                       keysB, plan, ctl, nullptr, 0, 0u, cur, shift, n, counters);
+    hipLaunchKernelGGL((stage_group_kernel<false, kSecond>), dim3(parents * per_parent),
+                       dim3(kSecond), 0, s, keysA, keysB, plan, ctl, cur, shift, per_parent, cur2, kStageShift, n,
+                       counters);
+  }
+  hipLaunchKernelGGL(stage_fill_kernel, dim3(spans), dim3(kFillBlock), 0, s, keysA, keysB, plan,
+                     ctl, cur2, two ? 1 : 0, counters, n, isa);
 }
 
 // ---------------------------------------------------------------------------
