@@ -266,7 +266,7 @@ inline int npass_for(const sa_ctx* c, int bits) { return passes_for(bits, c->rad
 // and the sweeps. `bound` >= the count sizes the launch grids. With
 // reserve == false the caller has reserved the generations already.
 void begin_sort(sa_ctx* c, u64 bound, const u64* dev_count, RoundCtl* rc, int npass, bool reserve,
-                hipStream_t s, u64 dense_n = 0, int log2a = 1);
+                hipStream_t s, u64 dense_n = 0, int log2a = 1, bool lsd = true);
 void sort_passes(sa_ctx* c, const Bufs& bf, u64 bound, int npass, int vals_present, int log_row,
                  u64 trace_count, hipStream_t s);
 // A sort of `count` pairs known on the host. any_order: pairs of equal keys may
@@ -279,6 +279,10 @@ constexpr u64 kSplitRoundMin = u64(1) << 21;  // active suffixes of a later roun
 bool split_usable(const sa_ctx* c, u64 count);
 sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_present, int slot,
                      hipStream_t s);
+// A later round's sort in one workgroup, its count (at most `bound`, which
+// split_one_fits() accepts) read from the control words, so that it can be captured.
+bool split_one_fits(const sa_ctx* c, u64 bound);
+void split_one(sa_ctx* c, const Bufs& bf, int npass, int log_row, u64 trace_count, hipStream_t s);
 // Round 0 of one text, or of a batch whose round-0 keys are packed (text slot at
 // idshift, texts in slot order), from the keys' sort to the active list in one go:
 // sorted keys in the plan's final buffer, their positions in d_sa (in place of a

@@ -192,13 +192,13 @@ int default_wgs_per_cu(int items, int block, bool table, int rb) {
 }
 
 void begin_sort(sa_ctx* c, u64 bound, const u64* dev_count, RoundCtl* rc, int npass, bool reserve,
-                hipStream_t s, u64 dense_n, int log2a) {
+                hipStream_t s, u64 dense_n, int log2a, bool lsd) {
   if (reserve) reserve_gens(c, u32(npass), s);
   Tracer t(c, s, SA_KERNEL_OTHER, 0);
   static_assert(kCtrSortTiles < kCtrActive && kCtrKeyOr < kCtrActive && kCtrKeyNot < kCtrActive,
                 "sort_begin clears the sort's counters");
-  launch_sort_begin(c->ctl, rc, bound, dev_count, npass, dense_n, log2a, c->hist_in, kClearWords,
-                    c->counters, s);
+  launch_sort_begin(c->ctl, rc, bound, dev_count, npass, dense_n, log2a, c->hist_in,
+                    lsd ? kClearWords : 0, c->counters, s);
 }
 
 // Sorts (kA, vA or generated values) by the low 8*npass bits. The sorted pairs
@@ -322,6 +322,7 @@ struct LaterRound {
   u64 dense_n;  // n when dense rounds are allowed (the ISA holds every name), else 0
   int b, npass;
   bool lazy;
+  bool one;     // the sort fits one workgroup (split_one)
   bool quad;    // prefix quadrupling: rank quadruples, two sorts per round (needs the eager ISA)
   Bufs bufs;
   const u8* text;
@@ -382,7 +383,8 @@ void enqueue_later_round(sa_ctx* c, const LaterRound& L, bool reserve, int log_r
     enqueue_quad_round(c, L, reserve, log_row, trace_count, trace_dense, s);
     return;
   }
-  begin_sort(c, L.bound, c->counters + kCtrActive, c->rc, L.npass, reserve, s, L.dense_n, 1);
+  begin_sort(c, L.bound, c->counters + kCtrActive, c->rc, L.npass, reserve, s, L.dense_n, 1,
+             !L.one && !split_count);
   {
     // A dense round reads two names and writes a key per suffix (16 bytes);
     // otherwise index, rank and the gathered name in, key and value out.
@@ -396,7 +398,9 @@ void enqueue_later_round(sa_ctx* c, const LaterRound& L, bool reserve, int log_r
       launch_pack_pairs(c->act_idx, c->act_rank, c->ctl, c->rc, L.n, L.b, c->isa, L.bufs.kA,
                         L.bufs.vA, grid, s);
   }
-  if (split_count)
+  if (L.one)
+    split_one(c, L.bufs, L.npass, log_row, trace_count, s);
+  else if (split_count)
     (void)split_sort(c, L.bufs, split_count, L.npass, trace_dense ? 0 : 1, log_row, s);
   else
     sort_passes(c, L.bufs, L.bound, L.npass, 1, log_row, trace_count, s);
@@ -415,7 +419,7 @@ GraphKey later_key(const sa_ctx* c, const LaterRound& L) {
   const u32 knobs[11] = {u32(L.b),           u32(L.npass),           L.lazy ? 1u : 0u,
                          u32(c->sort_items), u32(c->sort_block),     u32(c->sort_match),
                          u32(c->sort_wgs_per_cu), u32(c->num_cus),   u32(c->radix_bits),
-                         L.quad ? 1u : 0u,   c->stage_isa ? 1u : 0u};
+                         (L.quad ? 1u : 0u) | (L.one ? 2u : 0u),   c->stage_isa ? 1u : 0u};
   std::memcpy(k.knobs, knobs, sizeof(knobs));
   return k;
 }
@@ -574,6 +578,8 @@ sa_status build_rounds(sa_ctx* c, const u8* text, u64 n, u32 max_rounds, u32* d_
   L.npass = npass_for(c, 2 * L.b);
   L.lazy = lazy;
   L.quad = quad;
+  // (A dense round sorts all n.)
+  L.one = !quad && split_one_fits(c, L.dense_n && 4 * L.bound >= 3 * L.dense_n ? n : L.bound);
   L.bufs = full;
   if (lazy) {
     L.bufs.kA = spare;

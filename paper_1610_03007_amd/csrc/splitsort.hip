@@ -119,6 +119,20 @@ __device__ inline void buckets_of(const u64* tree, const u32* fl, int logd, cons
   }
 }
 
+// Adds one to s_cnt[b] for every lane with `on` and returns the lane's place among
+// all so far. Lanes of one bucket, which an LDS atomic takes one after the other, are
+// common where neighbours share their top bits (the texts of a batch, repeated
+// bytes): a wave of one bucket adds once.
+__device__ inline u32 count_in(u32* s_cnt, u32 b, bool on) {
+  const u32 b0 = u32(__builtin_amdgcn_readfirstlane(int(b)));
+  if (__all(on && b == b0)) {
+    u32 base = 0;
+    if (lane_id() == 0) base = atomicAdd(&s_cnt[b0], u32(kWave));
+    return u32(__builtin_amdgcn_readfirstlane(int(base))) + u32(lane_id());
+  }
+  return on ? atomicAdd(&s_cnt[b], 1u) : 0u;
+}
+
 __device__ inline void flag(u64* counters, u64 bits) {
   atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrError), (unsigned long long)bits);
 }
@@ -147,7 +161,8 @@ struct SplitShape {
   u32 nb() const { return 1u << (log1 + log2); }
 };
 
-// What a round 0 in one workgroup needs besides the sort's own arguments.
+// What a round 0 in one workgroup needs besides the sort's own arguments (ctl alone:
+// the sort of a later round, whose count is there).
 struct SplitTiny {
   const u8* text;
   u16* code;
@@ -281,19 +296,22 @@ struct SplitPlanOut {
   u32* log;        // the plan log's row
   int npass, rb;
   u32 final_buf;
+  const RoundCtl* rc;  // set: `log` is the whole log, the row the round's
 };
 __device__ inline void write_plan(const SplitPlanOut& o, u64 varying) {
   const int p = threadIdx.x;
   if (p >= kMaxPasses) return;
   u32 skip = !(p < o.npass && ((varying >> (p * o.rb)) & ((u64(1) << o.rb) - 1)) != 0);
   if (varying == 0) skip = p != o.npass - 1;  // all keys equal: the LSD sort's one copy pass
+  u32* log = o.log;
+  if (o.rc) log += size_t(o.rc->round < u32(kMaxRounds) ? o.rc->round : 0) * kPlanLogWords;
   o.plan->skip[p] = skip;
-  o.log[p] = skip;
-  o.log[kMaxPasses + p] = 0;
-  o.log[2 * kMaxPasses + p] = 0;
+  log[p] = skip;
+  log[kMaxPasses + p] = 0;
+  log[2 * kMaxPasses + p] = 0;
   if (p == 0) {
     o.plan->final_buf = o.final_buf;
-    o.log[3 * kMaxPasses] = o.final_buf;
+    log[3 * kMaxPasses] = o.final_buf;
   }
 }
 
@@ -604,8 +622,8 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
       const u32 e = TEXT ? tid * ITEMS + j : u32(j) * kSplitBlock + tid;
+      (void)count_in(s_cnt, bk[j], e < n);
       if (e < n) {
-        atomicAdd(&s_cnt[bk[j]], 1u);
         if (!SECOND) {
           kor |= key[j];
           knot |= ~key[j];
@@ -636,10 +654,13 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
       o |= s_or[w];
       n |= s_not[w];
     }
-    if (o) atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyOr),
-                    (unsigned long long)o);
-    if (n) atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyNot),
-                    (unsigned long long)n);
+    // (A word that has the bits already, as far as a plain read tells, is left
+    // alone: the atomics of all workgroups on it take 12 ns each.)
+    if (o & ~counters[kCtrKeyOr])
+      atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyOr), (unsigned long long)o);
+    if (n & ~counters[kCtrKeyNot])
+      atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrKeyNot),
+               (unsigned long long)n);
   }
 }
 
@@ -752,7 +773,7 @@ void split_sweep_kernel(
   buckets_of<ITEMS>(s_sp, s_fl, logd, key, place);
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j) {
-    rank[j] = item(j) < t.n ? atomicAdd(&s_cnt[place[j]], 1u) : 0u;
+    rank[j] = count_in(s_cnt, place[j], item(j) < t.n);
   }
   __syncthreads();
   u32 cnt[2] = {0, 0}, off[2] = {0, 0};
@@ -856,7 +877,7 @@ __device__ inline u64 wave_sort(u64 v) {
 }
 
 // Every bucket sorted in place, one workgroup each (a persistent grid strides
-// over them). The workgroup's first BLOCK keys, sorted (each wave its 64 in
+// over them). BLOCK of the bucket's keys, sorted (each wave its 64 in
 // registers, then their places among the other waves' by binary search), are the
 // splitters of BLOCK parts of about four pairs; the pairs go to their parts in
 // LDS, and each takes its place there by counting the smaller keys of its part.
@@ -904,6 +925,13 @@ void split_local_kernel(
   __shared__ u32 s_left, s_taken;  // FINAL: survivors of the bucket
   __shared__ u64 s_out;
   const u32 tid = threadIdx.x;
+  if (!TINY && tiny.ctl) {
+    // A later round: its count (at most CAP, bounded by the host) is on the device,
+    // and a dense round's values are the positions.
+    count = u32(tiny.ctl->count);
+    if (count == 0 || count > u32(CAP)) return;
+    iota = tiny.ctl->dense != 0;
+  }
   if (from) {
     nbuckets = from[0];
     if (blockIdx.x >= nbuckets) return;
@@ -1064,7 +1092,9 @@ void split_local_kernel(
     const bool split = m >= u32(P);  // fewer pairs: one part
     s_cnt[tid] = 0;
     if (split) {
-      const u64 k = wave_sort(key[0]);
+      // (Keys in no particular order, which a whole input need not be in: an earlier
+      // round's survivors come nearly sorted.)
+      const u64 k = wave_sort(TINY || start ? key[0] : keys[u64(tid) * m / P]);
       s_raw[tid] = k;
       __syncthreads();
       // Place among all samples: equal ones of earlier waves come first.
@@ -1502,7 +1532,7 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
                        clear, words, ctr);
   }
   const SplitPlanOut plan{top ? c->plan : nullptr, c->plan_log + size_t(log_row) * kPlanLogWords,
-                          npass, c->radix_bits, S.log1 && !S.log2 ? 1u : 0u};
+                          npass, c->radix_bits, S.log1 && !S.log2 ? 1u : 0u, nullptr};
 #define SA_LOCAL(CAP, BL, GRID, KEYS, VALS, NB, START, SPL, FROM, BIG)                           \
   do {                                                                                           \
     if (final)                                                                                   \
@@ -1554,7 +1584,7 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
                          sorted, S.log1, S.log2, S.over, S.samples, A);
     }
     const bool small = S.tile == 4 * kSplitBlock;
-    const u32 hgrid = S.groups * std::min<u32>(S.per, 2048 / S.groups);
+    const u32 hgrid = S.groups * std::min<u32>(S.per, 4096 / S.groups);
     const u32* vin = iota ? nullptr : bf.vA;
 #define SA_HIST(IT, SECOND, TEXT, GRID, KEYS, CTR)                                              \
   hipLaunchKernelGGL((split_hist_kernel<IT, SECOND, TEXT>), dim3(GRID), dim3(kSplitBlock), 0, s, \
@@ -1615,12 +1645,12 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
     else
       SA_LOCAL(2032, 256, std::min<u32>(nb, u32(c->num_cus) * 4), kout, vout, nb, A.start,
                A.splitters, nullptr, A.big);
-    // (In a single sweep of buckets of 512 pairs on average one larger shape does;
+    // (In a single sweep of buckets of 256 pairs on average one larger shape does;
     // elsewhere what the first one leaves, about 0.3% of the buckets, is mostly
     // little larger: 16 MiB of Markov text 0.90 ms with 1024 threads for it, 0.84.)
     const bool short_buckets = (count >> 9) <= nb;
-    const bool one_tier = !S.log2 && short_buckets;
-    if (!one_tier && short_buckets)
+    const bool one_tier = !S.log2 && (count >> 8) <= nb;
+    if (!one_tier && short_buckets && S.log2)
       SA_LOCAL(2032, 256, std::min<u32>(nb, u32(c->num_cus) * 4), kout, vout, nb, A.start,
                A.splitters, A.big, A.big2);
     else if (!one_tier)
@@ -1687,6 +1717,22 @@ sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, h
   const SplitText T{text, c->code, c->counters, (reinterpret_cast<uintptr_t>(text) & 3) == 0};
   const SplitFinal out{d_sa, c->act_idx, nullptr, c->act_rank, nullptr, 0};
   return split_run(c, full_bufs(c), n, T, out, 1, cv, true, npass, 0, &fin, s);
+}
+
+bool split_one_fits(const sa_ctx* c, u64 bound) {
+  return !c->tuning_explicit && !c->force_lsd && bound <= kSplitOne;
+}
+
+void split_one(sa_ctx* c, const Bufs& bf, int npass, int log_row, u64 trace_count, hipStream_t s) {
+  Tracer t(c, s, SA_KERNEL_SORT_PASS, double(trace_count) * 24.0);
+  const SplitPlanOut plan{c->plan,
+                          log_row >= 0 ? c->plan_log + size_t(log_row) * kPlanLogWords : c->plan_log,
+                          npass, c->radix_bits, 0u, log_row >= 0 ? nullptr : c->rc};
+  SplitTiny tiny{};
+  tiny.ctl = c->ctl;
+  hipLaunchKernelGGL((split_local_kernel<int(kSplitOne), 1024, false, false>), dim3(1), dim3(1024),
+                     0, s, bf.kA, bf.vA, u32(0), 1u, nullptr, nullptr, nullptr, nullptr, 0,
+                     SplitFinal{}, plan, tiny, c->counters);
 }
 
 sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u64* tbase, int idshift, u32* d_sa,
