@@ -188,3 +188,29 @@ def test_bad_suffix_array_is_an_error(builder):
     oob = torch.tensor([5, 4, 3, 2, 1, 9], dtype=torch.int32, device="cuda:0")
     with pytest.raises(SAError):
         builder.lcp(t, oob)
+
+
+def test_index_memory_reused(builder):
+    """Indexes made from the memory of destroyed ones (larger, smaller, several alive
+    at once), counted after their builder is gone."""
+    from paper_1610_03007_amd import SuffixArrayBuilder
+    b = SuffixArrayBuilder(0)
+    rng = np.random.default_rng(5)
+    kept = []
+    for k, n in enumerate([100000, 90000, 300000, 2, 100000, 99000, 700000, 95000]):
+        t = rng.integers(97, 101, n).astype(np.uint8)
+        d, sa = on_gpu(b, t)
+        fm = b.fm_index(d, sa)
+        raw = t.tobytes()
+        pats = [raw[:3], raw[n // 2:n // 2 + 5] or b"a", b"zz"]
+        want = [sum(raw.startswith(p, i) for i in range(n)) for p in pats]
+        got = fm.count(pats).cpu().numpy()
+        assert [int(r[1] - r[0]) for r in got] == want, n
+        if k % 3 == 1:
+            kept.append((fm, pats, want))
+        else:
+            del fm
+    b.close()
+    for fm, pats, want in kept:
+        got = fm.count(pats).cpu().numpy()
+        assert [int(r[1] - r[0]) for r in got] == want

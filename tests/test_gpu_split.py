@@ -138,3 +138,24 @@ def test_batch_and_dc_builds(builder):
             sa = fn(d)
             torch.cuda.synchronize()
             assert np.array_equal(sa.cpu().numpy().view(np.uint32), oracle.sa(t, parallel=True))
+
+
+@pytest.mark.parametrize("copy", [3, 700, 4000, 9000])
+def test_small_later_rounds(builder, copy):
+    """Later rounds of a few suffixes, sorted in one workgroup (up to 4608 pairs)
+    or just past it, dense in the shortest text: a text that holds one piece twice
+    (survivors in two ordered runs), and a batch of such texts (nearly sorted)."""
+    rng = np.random.default_rng(copy)
+    for n in (2 * copy + 1, 60000):
+        t = rng.integers(0, 4, n).astype(np.uint8)
+        t[n - copy:] = t[:copy]
+        check(builder, t)
+        check(builder, t[::-1])
+    texts = [np.concatenate([p, p[:k % 5], p]) for k in range(64)
+             for p in (rng.integers(0, 20, copy // 100 + 24).astype(np.uint8),)]
+    off = np.concatenate([[0], np.cumsum([t.size for t in texts])])
+    sa = builder.build_batch(torch.from_numpy(np.concatenate(texts)).to("cuda:0"), off)
+    torch.cuda.synchronize()
+    sa = sa.cpu().numpy().view(np.uint32)
+    for k, t in enumerate(texts):
+        assert np.array_equal(sa[off[k]:off[k + 1]], oracle.sa(t)), k
