@@ -299,8 +299,8 @@ sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_p
 // split_one_fits() accepts) read from the control words, so that it can be captured.
 bool split_one_fits(const sa_ctx* c, u64 bound);
 void split_one(sa_ctx* c, const Bufs& bf, int npass, int log_row, u64 trace_count, hipStream_t s);
-// Round 0 of one text, or of a batch whose round-0 keys are packed (text slot at
-// idshift, texts in slot order), from the keys' sort to the active list in one go:
+// Round 0 of one text, or of a batch (keys with the text slot at idshift, texts in
+// slot order), from the keys' sort to the active list in one go:
 // sorted keys in the plan's final buffer, their positions in d_sa (in place of a
 // value buffer), the suffixes whose key is not unique in the active list. The ISA's
 // memory is scratch. Only where split_usable().
@@ -308,8 +308,11 @@ void split_one(sa_ctx* c, const Bufs& bf, int npass, int log_row, u64 trace_coun
 // by split_round0 (c->present zero on entry and exit), others before it.
 bool split_small_text(u64 n);
 sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, hipStream_t s);
-sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u64* tbase, int idshift, u32* d_sa,
-                       hipStream_t s);
+sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u8* arena, const TextTab& tab,
+                       const NewList& nl, int idshift, u32* d_sa, hipStream_t s);
+// Whether split_batch0 takes the keys of n suffixes from the texts themselves (not
+// packed before): where the sort begins with a sweep.
+bool split_batch_from_text(u64 n);
 // Runs a whole build; once more with the LSD sort if the split sort overflowed.
 template <typename F>
 sa_status with_lsd_repeat(sa_ctx* c, F&& build) {

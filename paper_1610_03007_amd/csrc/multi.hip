@@ -238,6 +238,7 @@ struct Engine {
         launch_fill_u64(c->counters, kCtrCount, 0, s);
         launch_fill_u32(tab.surv, slots, 0, s);
       }
+      fused = defer_round0_isa && m && !active && split_usable(c, total);
       if (m) {
         {
           Tracer tr(c, s, SA_KERNEL_OTHER, double(A0));
@@ -246,8 +247,10 @@ struct Engine {
           launch_multi_codes(tab, nl, idbits, round0_shift, compact0 ? 0 : c->round0_trim,
                              c->radix_bits, s);
         }
-        Tracer tr(c, s, SA_KERNEL_PACK_TEXT, double(A0) * 13.0);
-        launch_multi_pack0(text_arena, tab, nl, round0_shift, c->keysA, c->valsA, s);
+        if (!(fused && split_batch_from_text(total))) {
+          Tracer tr(c, s, SA_KERNEL_PACK_TEXT, double(A0) * 13.0);
+          launch_multi_pack0(text_arena, tab, nl, round0_shift, c->keysA, c->valsA, s);
+        }
       }
       const Bufs bufs = lazy ? later : full;
       if (active) {
@@ -260,11 +263,11 @@ struct Engine {
           launch_multi_pack_pairs(c->act_ti, c->act_rank, active, tab, B, idshift, c->isa,
                                   c->keysA + A0, c->valsA + A0, s);
       }
-      fused = defer_round0_isa && m && !active && split_usable(c, total);
       if (total) {
         if (fused) {
           const sa_status fs =
-              split_batch0(c, total, npass_for(c, 64), tab.base, round0_shift, sa_arena, s);
+              split_batch0(c, total, npass_for(c, 64), text_arena, tab, nl, round0_shift,
+                           sa_arena, s);
           if (fs != SA_OK) return fs;
         } else {
           run_sort(c, bufs, total, npass_for(c, 64), 1, slot_info, s, true);

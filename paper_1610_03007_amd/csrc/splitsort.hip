@@ -202,8 +202,77 @@ struct SplitText {
   const u16* code;
   const u64* counters;  // kCtrCodeBits, kCtrChars
   int words;            // the text is 4-byte aligned
+  // A batch (nl.m != 0): `text` is the arena and the keys are those of the joining
+  // texts, each with its own codes, w and c and with its slot at idshift.
+  TextTab tab;
+  NewList nl;
+  int idshift;
 };
 constexpr int kKeyHalo = 64;  // c <= 64
+// Where the keys of a first sweep come from.
+constexpr int kFromKeys = 0, kFromText = 1, kFromBatch = 2;
+
+// The joining text that element e of the merged array is in (the last one whose
+// first element is at or before e). Every lane of a wave asks for the same e: 64
+// probes at a time, two reads in turn for up to 4096 texts.
+__device__ inline u32 batch_text_of(const NewList& nl, u32 e) {
+  u32 lo = 0, n = nl.m;
+  while (n > 1) {
+    const u32 step = (n + kWave - 1) / kWave;
+    const u32 at = u32(lane_id()) * step;
+    const u64 below = __ballot(at < n && nl.out[lo + at] <= e);
+    const u32 skip = (u32(__popcll(below)) - 1) * step;  // (probe 0 is: out[lo] <= e)
+    lo += skip;
+    n = n - skip < step ? n - skip : step;
+  }
+  return lo;
+}
+
+// The same by one thread alone, between texts lo and hi.
+__device__ inline u32 batch_text_between(const NewList& nl, u32 lo, u32 hi, u32 e) {
+  while (lo < hi) {
+    const u32 mid = lo + (hi - lo + 1) / 2;
+    if (nl.out[mid] <= e) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// c codes of w bits at a time: key[j] of sym(j) .. sym(j + c - 1).
+template <int ITEMS>
+__device__ inline void roll_keys(const u16* sym, u32 w, u32 c, u64 tag, u64 (&key)[ITEMS]) {
+  const u64 mask = c * w >= 64 ? ~u64(0) : (u64(1) << (c * w)) - 1;
+  u64 k = 0;
+  for (u32 j = 0; j < c; ++j) k = (k << w) | sym[j];
+  key[0] = tag | k;
+#pragma unroll
+  for (int j = 1; j < ITEMS; ++j) {
+    k = ((k << w) | sym[j + c - 1]) & mask;
+    key[j] = tag | k;
+  }
+}
+
+// Codes of positions base .. base + SPAN - 1 of a text of n bytes (0 past its end).
+template <u32 SPAN>
+__device__ inline void text_codes(const u8* text, u64 base, u64 n, bool words, const u16* s_code,
+                                  u16* s_sym) {
+  const u32 tid = threadIdx.x;
+  if (words && base + SPAN <= n) {
+    const u32* tw = reinterpret_cast<const u32*>(text + base);
+    for (u32 q = tid; q < SPAN / 4; q += kSplitBlock) {
+      const u32 v = tw[q];
+      s_sym[4 * q] = s_code[v & 0xFFu];
+      s_sym[4 * q + 1] = s_code[(v >> 8) & 0xFFu];
+      s_sym[4 * q + 2] = s_code[(v >> 16) & 0xFFu];
+      s_sym[4 * q + 3] = s_code[v >> 24];
+    }
+  } else {
+    for (u32 i = tid; i < SPAN; i += kSplitBlock) {
+      const u64 p = base + i;
+      s_sym[i] = p < n ? s_code[text[p]] : u16(0);
+    }
+  }
+}
 
 // The keys of positions base + ITEMS tid .. + ITEMS - 1 of a tile of ITEMS per
 // thread, rolled from the tile's codes in LDS. (Every thread calls; s_sym holds the
@@ -217,31 +286,122 @@ __device__ inline void text_keys(const SplitText& T, u32 base, u32 count, u16* s
   const u32 c = u32(T.counters[kCtrChars]);
   if (tid < 256) s_code[tid] = T.code[tid];
   __syncthreads();
-  if (T.words && u64(base) + SPAN <= count) {
-    const u32* tw = reinterpret_cast<const u32*>(T.text + base);
-    for (u32 q = tid; q < SPAN / 4; q += kSplitBlock) {
-      const u32 v = tw[q];
-      s_sym[4 * q] = s_code[v & 0xFFu];
-      s_sym[4 * q + 1] = s_code[(v >> 8) & 0xFFu];
-      s_sym[4 * q + 2] = s_code[(v >> 16) & 0xFFu];
-      s_sym[4 * q + 3] = s_code[v >> 24];
+  text_codes<SPAN>(T.text, base, count, T.words != 0, s_code, s_sym);
+  __syncthreads();
+  roll_keys<ITEMS>(s_sym + tid * ITEMS, w, c, 0, key);
+}
+
+// The same for elements base + ITEMS tid .. of a batch's merged array (n of the
+// tile's are there), and the suffixes' positions in their texts. A tile inside one
+// text is read and rolled as above; one that several texts share (a quarter of the
+// tiles at 32 KiB a text, all of them below 6 KiB) looks each byte's code up in its
+// text's table, in L2.
+struct BatchText {  // the text of a workgroup's last tile (its codes are in LDS)
+  u64 begin, end;   // its elements
+  u64 len;
+  const u8* text;
+  u32 t, wc;
+};
+template <int ITEMS>
+__device__ inline void batch_keys(const SplitText& T, BatchText& B, u32 base, u32 n, u16* s_code,
+                                  u16* s_sym, u64 (&key)[ITEMS], u32 (&val)[ITEMS]) {
+  constexpr u32 TILE = u32(ITEMS) * kSplitBlock;
+  const u32 tid = threadIdx.x;
+  const NewList& nl = T.nl;
+  const u32 first = tid * ITEMS;
+  u32 i0 = 0;
+  bool one = base >= B.begin && u64(base) + n <= B.end;  // all of this is uniform
+  if (!one) {
+    i0 = batch_text_of(nl, base);
+    B.end = nl.out[i0 + 1];  // (out[m] = all elements)
+    one = u64(base) + n <= B.end;
+    if (one) {
+      B.begin = nl.out[i0];
+      B.t = nl.t[i0];
+      B.len = T.tab.len[B.t];
+      B.text = T.text + T.tab.base[B.t];
+      B.wc = T.tab.wc[B.t];
+      if (tid < 256) s_code[tid] = T.tab.code[u64(B.t) * 256 + tid];
+      __syncthreads();
+    } else {
+      B.end = 0;
     }
-  } else {
-    for (u32 i = tid; i < SPAN; i += kSplitBlock) {
-      const u64 p = u64(base) + i;
-      s_sym[i] = p < count ? s_code[T.text[p]] : u16(0);
+  }
+  if (one) {
+    const u64 at = base - B.begin;
+    text_codes<TILE + kKeyHalo>(B.text, at, B.len,
+                                (reinterpret_cast<uintptr_t>(B.text + at) & 3) == 0, s_code,
+                                s_sym);
+    __syncthreads();
+    roll_keys<ITEMS>(s_sym + first, B.wc & 0xFFFFu, B.wc >> 16, u64(B.t) << T.idshift, key);
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) val[j] = u32(at) + first + j;
+    return;
+  }
+  const u32 i1 = batch_text_of(nl, base + n - 1);
+  // Codes of the thread's own elements, and (64 threads) of the halo's, where only
+  // the last element's text matters.
+  u32 i = first < n ? batch_text_between(nl, i0, i1, base + first) : i1;
+  {
+    // The bytes are all requested before the first code is.
+    u32 k = i, t = nl.t[k];
+    u64 end = nl.out[k + 1];
+    const u8* from = T.text + T.tab.base[t] - nl.out[k];  // of element 0, were it this text's
+    u32 at[ITEMS];
+    u8 byte[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const u64 e = u64(base) + first + j;
+      byte[j] = 0;
+      if (first + j < n) {
+        if (e >= end) {
+          while (end <= e) end = nl.out[++k + 1];  // (ends: e < out[m])
+          t = nl.t[k];
+          from = T.text + T.tab.base[t] - nl.out[k];
+        }
+        byte[j] = from[e];
+      }
+      at[j] = t;
+    }
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const u16 code = T.tab.code[u64(at[j]) * 256 + byte[j]];
+      if (first + j < n) s_sym[first + j] = code;
+    }
+    const u64 e = u64(base) + n + tid;
+    if (tid < kKeyHalo && e < nl.out[i1 + 1]) {
+      const u32 t = nl.t[i1];
+      s_sym[n + tid] = T.tab.code[u64(t) * 256 + T.text[T.tab.base[t] + (e - nl.out[i1])]];
     }
   }
   __syncthreads();
-  const u64 mask = c * w >= 64 ? ~u64(0) : (u64(1) << (c * w)) - 1;
-  const u32 first = tid * ITEMS;
-  u64 k = 0;
-  for (u32 j = 0; j < c; ++j) k = (k << w) | s_sym[first + j];
-  key[0] = k;
+  u32 end = 0, w = 0, c = 0, start = 0;  // of the text in progress, in the tile
+  u64 k = 0, mask = 0, tag = 0;
 #pragma unroll
-  for (int j = 1; j < ITEMS; ++j) {
-    k = ((k << w) | s_sym[first + j + c - 1]) & mask;
-    key[j] = k;
+  for (int j = 0; j < ITEMS; ++j) {
+    const u32 q = first + j;
+    key[j] = 0;
+    val[j] = 0;
+    if (q >= n) continue;
+    if (j == 0 || q >= end) {
+      while (nl.out[i + 1] <= u64(base) + q) ++i;
+      const u32 t = nl.t[i];
+      const u32 wc = T.tab.wc[t];
+      w = wc & 0xFFFFu;
+      c = wc >> 16;
+      mask = c * w >= 64 ? ~u64(0) : (u64(1) << (c * w)) - 1;
+      tag = u64(t) << T.idshift;
+      start = u32(nl.out[i]) - base;  // modulo 2^32
+      const u64 e = nl.out[i + 1] - base;
+      end = e < TILE + kKeyHalo ? u32(e) : TILE + kKeyHalo;
+      k = 0;
+      for (u32 x = q; x < q + c; ++x) k = (k << w) | (x < end ? s_sym[x] : u16(0));
+    } else {
+      const u32 x = q + c - 1;
+      k = ((k << w) | (x < end ? s_sym[x] : u16(0))) & mask;
+    }
+    key[j] = tag | k;
+    val[j] = q - start;
   }
 }
 
@@ -341,7 +501,7 @@ __global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict
                                                            SplitText T, u32 count, u32 samples,
                                                            u64* __restrict__ out) {
   __shared__ u16 s_code[256];
-  if (T.text) {
+  if (T.text && !T.nl.m) {
     s_code[threadIdx.x] = T.code[threadIdx.x];
     __syncthreads();
   }
@@ -350,6 +510,18 @@ __global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict
   const u32 p = sample_position(i, count, samples);
   if (!T.text) {
     out[i] = keys[p];
+    return;
+  }
+  if (T.nl.m) {
+    const u32 x = batch_text_between(T.nl, 0, T.nl.m - 1, p);
+    const u32 t = T.nl.t[x];
+    const u32 w = T.tab.wc[t] & 0xFFFFu, c = T.tab.wc[t] >> 16;
+    const u8* text = T.text + T.tab.base[t];
+    const u64 len = T.tab.len[t];
+    u64 k = 0;
+    for (u64 q = p - T.nl.out[x], e = q + c; q < e; ++q)
+      k = (k << w) | (q < len ? T.tab.code[u64(t) * 256 + text[q]] : u16(0));
+    out[i] = (u64(t) << T.idshift) | k;
     return;
   }
   const u32 cw = u32(T.counters[kCtrCodeBits]), c = u32(T.counters[kCtrChars]);
@@ -563,15 +735,18 @@ __device__ inline void load_splitters(const SplitArrays& A, u32 row, int logd, b
 // Counts per bucket. Bound by the key reads (8 bytes a pair) and the search:
 // log2(D) LDS reads a pair; from a text, by one byte a pair and the search. Level 1
 // also ORs the keys and their complements.
-template <int ITEMS, bool SECOND, bool TEXT>
-__global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __restrict__ keys,
-                                                                 SplitText T, SplitShape S,
-                                                                 SplitArrays A,
-                                                                 u64* __restrict__ counters) {
+template <int ITEMS, bool SECOND, int FROM>
+__global__ __launch_bounds__(kSplitBlock)
+__attribute__((amdgpu_waves_per_eu(FROM == kFromBatch ? 5 : 4))) void split_hist_kernel(
+    const u64* __restrict__ keys, SplitText T, SplitShape S, SplitArrays A,
+    u64* __restrict__ counters) {
+  constexpr bool TEXT = FROM != kFromKeys;
+  // A tile of a batch has few buckets (those of its text): four counts for each.
+  constexpr u32 COPIES = FROM == kFromBatch ? 4 : 1;
   __shared__ u16 s_code[TEXT ? 256 : 1];
   __shared__ u16 s_sym[TEXT ? ITEMS * kSplitBlock + kKeyHalo : 1];
   __shared__ u64 s_sp[kSplitMaxD];
-  __shared__ u32 s_cnt[kSplitMaxD];
+  __shared__ u32 s_cnt[kSplitMaxD * COPIES];
   __shared__ u32 s_fl[kSplitMaxD / 32];
   __shared__ u32 s_row;
   __shared__ u64 s_or[kSplitBlock / kWave], s_not[kSplitBlock / kWave];
@@ -590,9 +765,16 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
     k0 = blockIdx.x / S.groups;
     kstep = gridDim.x / S.groups;
     kend = S.per;
+    if (FROM == kFromBatch) {  // neighbouring tiles, mostly of one text
+      const u32 q = (S.per + kstep - 1) / kstep;
+      k0 *= q;
+      kend = k0 + q < S.per ? k0 + q : S.per;
+      kstep = 1;
+    }
   }
+  BatchText bt{};
   load_splitters<SECOND>(A, row, logd, S.log2 != 0, s_sp, s_fl);
-  for (u32 i = tid; i < d; i += kSplitBlock) s_cnt[i] = 0;
+  for (u32 i = tid; i < d * COPIES; i += kSplitBlock) s_cnt[i] = 0;
   __syncthreads();
   u64 kor = 0, knot = 0;
   for (u32 k = k0; k < kend; k += kstep) {
@@ -608,7 +790,10 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
     }
     u64 key[ITEMS];
     if constexpr (TEXT) {
-      text_keys<ITEMS>(T, base, S.count, s_code, s_sym, key);
+      u32 unused[ITEMS];
+      if constexpr (FROM == kFromBatch)
+        batch_keys<ITEMS>(T, bt, base, n, s_code, s_sym, key, unused);
+      else text_keys<ITEMS>(T, base, S.count, s_code, s_sym, key);
       __syncthreads();  // the next tile's codes go to the same place
     } else {
 #pragma unroll
@@ -622,7 +807,16 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
       const u32 e = TEXT ? tid * ITEMS + j : u32(j) * kSplitBlock + tid;
-      (void)count_in(s_cnt, bk[j], e < n);
+      if (COPIES == 1) {
+        (void)count_in(s_cnt, bk[j], e < n);
+      } else {
+        const u32 b0 = u32(__builtin_amdgcn_readfirstlane(int(bk[j])));
+        if (__all(e < n && bk[j] == b0)) {
+          if (lane_id() == 0) atomicAdd(&s_cnt[b0 * COPIES], u32(kWave));
+        } else if (e < n) {
+          atomicAdd(&s_cnt[bk[j] * COPIES + tid % COPIES], 1u);
+        }
+      }
       if (e < n) {
         if (!SECOND) {
           kor |= key[j];
@@ -645,7 +839,8 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
   __syncthreads();
   u32* tot = SECOND ? A.tot2 : A.tot1;
   for (u32 i = tid; i < d; i += kSplitBlock) {
-    const u32 c = s_cnt[i];
+    u32 c = 0;
+    for (u32 q = 0; q < COPIES; ++q) c += s_cnt[i * COPIES + q];
     if (c) atomicAdd(&tot[(u64(row) << logd) + i], c);
   }
   if (!SECOND && counters && tid == 0) {
@@ -670,13 +865,14 @@ __global__ __launch_bounds__(kSplitBlock) void split_hist_kernel(const u64* __re
 // equal keys is kept, which saves the LSD sweep's ballots).
 // 2^28 suffixes: 1.8 ms from the text (13 bytes a suffix), 1.7 ms the second sweep
 // (24 bytes, 3.8 TB/s).
-template <int ITEMS, bool SECOND, bool TEXT>
+template <int ITEMS, bool SECOND, int FROM>
 __global__ __launch_bounds__(kSplitBlock) __attribute__((amdgpu_waves_per_eu(4)))
 void split_sweep_kernel(
     const u64* __restrict__ kin, const u32* __restrict__ vin, SplitText T, u64* __restrict__ kout,
     u32* __restrict__ vout, SplitShape S, SplitArrays A, int iota, SplitPlanOut plan,
     u64* __restrict__ counters) {
   constexpr u32 TILE = u32(ITEMS) * kSplitBlock;
+  constexpr bool TEXT = FROM != kFromKeys;
   static_assert(kSplitMaxD <= 2 * kSplitBlock, "two buckets per thread");
   __shared__ u64 s_buf[TILE];       // codes of a text, then keys, then values
   static_assert(2 * (TILE + kKeyHalo) <= 8 * TILE, "the tile's codes fit");
@@ -708,7 +904,10 @@ void split_sweep_kernel(
   auto item = [&](int j) { return TEXT ? tid * ITEMS + j : u32(j) * kSplitBlock + tid; };
   u64 key[ITEMS];
   u32 val[ITEMS];
-  if constexpr (TEXT) {
+  if constexpr (FROM == kFromBatch) {
+    BatchText bt{};
+    batch_keys<ITEMS>(T, bt, t.base, t.n, s_code, reinterpret_cast<u16*>(s_buf), key, val);
+  } else if constexpr (TEXT) {
     text_keys<ITEMS>(T, t.base, S.count, s_code, reinterpret_cast<u16*>(s_buf), key);
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) val[j] = t.base + item(j);
@@ -1517,7 +1716,8 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
   *fin = 0;
   // Round 0 of a text short enough for one sweep or none starts with its own
   // kernels (see small_begin_kernel).
-  const bool small_text = T.text && !S.log2;
+  const bool batch = T.nl.m != 0;
+  const bool small_text = T.text && !batch && !S.log2;
   if (small_text && S.log1) {
     Tracer t(c, s, SA_KERNEL_OTHER, double(count));
     const u8* text = T.text;
@@ -1586,31 +1786,37 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
     const bool small = S.tile == 4 * kSplitBlock;
     const u32 hgrid = S.groups * std::min<u32>(S.per, 4096 / S.groups);
     const u32* vin = iota ? nullptr : bf.vA;
-#define SA_HIST(IT, SECOND, TEXT, GRID, KEYS, CTR)                                              \
-  hipLaunchKernelGGL((split_hist_kernel<IT, SECOND, TEXT>), dim3(GRID), dim3(kSplitBlock), 0, s, \
+#define SA_HIST(IT, SECOND, FROM, GRID, KEYS, CTR)                                              \
+  hipLaunchKernelGGL((split_hist_kernel<IT, SECOND, FROM>), dim3(GRID), dim3(kSplitBlock), 0, s, \
                      KEYS, T, S, A, CTR)
-#define SA_SWEEP(IT, SECOND, TEXT, GRID, KIN, VIN, KOUT, VOUT, IOTA)                              \
-  hipLaunchKernelGGL((split_sweep_kernel<IT, SECOND, TEXT>), dim3(GRID), dim3(kSplitBlock), 0, s, \
+#define SA_SWEEP(IT, SECOND, FROM, GRID, KIN, VIN, KOUT, VOUT, IOTA)                              \
+  hipLaunchKernelGGL((split_sweep_kernel<IT, SECOND, FROM>), dim3(GRID), dim3(kSplitBlock), 0, s, \
                      KIN, VIN, T, KOUT, VOUT, S, A, IOTA, plan, ctr)
     {
       Tracer t(c, s, SA_KERNEL_HISTOGRAM, double(count) * (T.text ? 1.0 : 8.0));
-      if (T.text) {
-        if (small) SA_HIST(4, false, true, hgrid, bf.kA, ctr_top);
-        else SA_HIST(kSweepItems, false, true, hgrid, bf.kA, ctr_top);
+      if (batch) {
+        if (small) SA_HIST(4, false, kFromBatch, hgrid, bf.kA, ctr_top);
+        else SA_HIST(kSweepItems, false, kFromBatch, hgrid, bf.kA, ctr_top);
+      } else if (T.text) {
+        if (small) SA_HIST(4, false, kFromText, hgrid, bf.kA, ctr_top);
+        else SA_HIST(kSweepItems, false, kFromText, hgrid, bf.kA, ctr_top);
       } else {
-        if (small) SA_HIST(4, false, false, hgrid, bf.kA, ctr_top);
-        else SA_HIST(kSweepItems, false, false, hgrid, bf.kA, ctr_top);
+        if (small) SA_HIST(4, false, kFromKeys, hgrid, bf.kA, ctr_top);
+        else SA_HIST(kSweepItems, false, kFromKeys, hgrid, bf.kA, ctr_top);
       }
     }
     {
       Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * (T.text ? 13.0 : iota ? 20.0 : 24.0));
       const u32 grid = S.groups * S.per;
-      if (T.text) {
-        if (small) SA_SWEEP(4, false, true, grid, bf.kA, vin, bf.kB, bf.vB, iota);
-        else SA_SWEEP(kSweepItems, false, true, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+      if (batch) {
+        if (small) SA_SWEEP(4, false, kFromBatch, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+        else SA_SWEEP(kSweepItems, false, kFromBatch, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+      } else if (T.text) {
+        if (small) SA_SWEEP(4, false, kFromText, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+        else SA_SWEEP(kSweepItems, false, kFromText, grid, bf.kA, vin, bf.kB, bf.vB, iota);
       } else {
-        if (small) SA_SWEEP(4, false, false, grid, bf.kA, vin, bf.kB, bf.vB, iota);
-        else SA_SWEEP(kSweepItems, false, false, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+        if (small) SA_SWEEP(4, false, kFromKeys, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+        else SA_SWEEP(kSweepItems, false, kFromKeys, grid, bf.kA, vin, bf.kB, bf.vB, iota);
       }
     }
     u64* kout = bf.kB;
@@ -1621,13 +1827,13 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
       const u32 grid = u32(ceil_div(u64(S.tiles) + (u64(1) << S.log1), kSplitXcds) * kSplitXcds);
       {
         Tracer t(c, s, SA_KERNEL_HISTOGRAM, double(count) * 8.0);
-        if (small) SA_HIST(4, true, false, grid, bf.kB, nullptr);
-        else SA_HIST(kSweepItems, true, false, grid, bf.kB, nullptr);
+        if (small) SA_HIST(4, true, kFromKeys, grid, bf.kB, nullptr);
+        else SA_HIST(kSweepItems, true, kFromKeys, grid, bf.kB, nullptr);
       }
       {
         Tracer t(c, s, SA_KERNEL_SORT_PASS, double(count) * 24.0);
-        if (small) SA_SWEEP(4, true, false, grid, bf.kB, bf.vB, bf.kA, bf.vA, 0);
-        else SA_SWEEP(kSweepItems, true, false, grid, bf.kB, bf.vB, bf.kA, bf.vA, 0);
+        if (small) SA_SWEEP(4, true, kFromKeys, grid, bf.kB, bf.vB, bf.kA, bf.vA, 0);
+        else SA_SWEEP(kSweepItems, true, kFromKeys, grid, bf.kB, bf.vB, bf.kA, bf.vA, 0);
       }
       kout = bf.kA;
       vout = bf.vA;
@@ -1714,7 +1920,8 @@ bool split_small_text(u64 n) { return split_shape(n).log2 == 0; }
 sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, hipStream_t s) {
   u32 fin = 0;
   const Carver cv{reinterpret_cast<char*>(c->isa), size_t(c->cap) * 4};
-  const SplitText T{text, c->code, c->counters, (reinterpret_cast<uintptr_t>(text) & 3) == 0};
+  const SplitText T{text, c->code, c->counters, (reinterpret_cast<uintptr_t>(text) & 3) == 0,
+                    {}, {}, 0};
   const SplitFinal out{d_sa, c->act_idx, nullptr, c->act_rank, nullptr, 0};
   return split_run(c, full_bufs(c), n, T, out, 1, cv, true, npass, 0, &fin, s);
 }
@@ -1735,12 +1942,22 @@ void split_one(sa_ctx* c, const Bufs& bf, int npass, int log_row, u64 trace_coun
                      SplitFinal{}, plan, tiny, c->counters);
 }
 
-sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u64* tbase, int idshift, u32* d_sa,
-                       hipStream_t s) {
+bool split_batch_from_text(u64 n) { return split_shape(n).log1 != 0; }
+
+sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u8* arena, const TextTab& tab,
+                       const NewList& nl, int idshift, u32* d_sa, hipStream_t s) {
   u32 fin = 0;
+  const u64* tbase = tab.base;
+  SplitText T{};
+  if (split_batch_from_text(n)) {
+    T.text = arena;
+    T.tab = tab;
+    T.nl = nl;
+    T.idshift = idshift;
+  }
   const Carver cv{reinterpret_cast<char*>(c->isa), size_t(c->cap) * 4};
   const SplitFinal out{d_sa, nullptr, c->act_ti, c->act_rank, tbase, idshift};
-  return split_run(c, full_bufs(c), n, SplitText{}, out, 0, cv, true, npass, 0, &fin, s);
+  return split_run(c, full_bufs(c), n, T, out, 0, cv, true, npass, 0, &fin, s);
 }
 
 }  // namespace drv

@@ -159,3 +159,27 @@ def test_small_later_rounds(builder, copy):
     sa = sa.cpu().numpy().view(np.uint32)
     for k, t in enumerate(texts):
         assert np.array_equal(sa[off[k]:off[k + 1]], oracle.sa(t)), k
+
+
+@pytest.mark.parametrize("lo,hi,total", [(0, 3, 20000), (1, 90, 200000), (500, 9000, 1500000),
+                                         (2000, 40000, 3000000)])
+def test_batch_keys_from_texts(builder, lo, hi, total):
+    """Round-0 keys of a batch taken from the texts: tiles inside one text and tiles
+    that many share, empty texts, alphabets (code widths) of their own, and an arena
+    that starts off a word."""
+    rng = np.random.default_rng(total)
+    texts, size = [], 0
+    while size < total:
+        n = int(rng.integers(lo, hi))
+        sigma = int(rng.choice([1, 2, 4, 20, 256]))
+        texts.append(rng.integers(0, sigma, n).astype(np.uint8) * (255 // max(1, sigma - 1)))
+        size += n
+    off = np.concatenate([[0], np.cumsum([t.size for t in texts])])
+    flat = np.concatenate([[0], *texts]).astype(np.uint8)
+    for shift in (0, 1):
+        d = torch.from_numpy(flat[1 - shift:]).to("cuda:0")[shift:]
+        sa = builder.build_batch(d, off)
+        torch.cuda.synchronize()
+        sa = sa.cpu().numpy().view(np.uint32)
+        for k, t in enumerate(texts):
+            assert np.array_equal(sa[off[k]:off[k + 1]], oracle.sa(t)), (k, t.size)
