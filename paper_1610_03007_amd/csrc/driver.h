@@ -299,6 +299,11 @@ sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_p
 // split_one_fits() accepts) read from the control words, so that it can be captured.
 bool split_one_fits(const sa_ctx* c, u64 bound);
 void split_one(sa_ctx* c, const Bufs& bf, int npass, int log_row, u64 trace_count, hipStream_t s);
+// The same for a dense round, its keys formed from the names in the ISA (values
+// generated) where the sort begins with a sweep: split_from_names().
+bool split_from_names(u64 count);
+sa_status split_dense(sa_ctx* c, const Bufs& bf, u64 n, int bits, int npass, int slot,
+                      hipStream_t s);
 // Round 0 of one text, or of a batch (keys with the text slot at idshift, texts in
 // slot order), from the keys' sort to the active list in one go:
 // sorted keys in the plan's final buffer, their positions in d_sa (in place of a

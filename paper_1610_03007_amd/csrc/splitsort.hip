@@ -207,10 +207,20 @@ struct SplitText {
   TextTab tab;
   NewList nl;
   int idshift;
+  // A dense round (names set): key i is the names of suffixes i and i + h, `bits` each.
+  const u32* names;
+  const RoundCtl* rc;  // h
+  int bits;
 };
 constexpr int kKeyHalo = 64;  // c <= 64
 // Where the keys of a first sweep come from.
-constexpr int kFromKeys = 0, kFromText = 1, kFromBatch = 2;
+constexpr int kFromKeys = 0, kFromText = 1, kFromBatch = 2, kFromNames = 3;
+
+// Key of suffix i in a dense round of n suffixes, at offset h.
+__device__ inline u64 pair_key(const u32* __restrict__ names, int bits, u64 h, u32 i, u32 n) {
+  const u64 j = i + h;
+  return (u64(names[i]) << bits) | u64(j < n ? names[j] : 0u);
+}
 
 // The joining text that element e of the merged array is in (the last one whose
 // first element is at or before e). Every lane of a wave asks for the same e: 64
@@ -509,7 +519,7 @@ __global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict
   if (i >= samples) return;
   const u32 p = sample_position(i, count, samples);
   if (!T.text) {
-    out[i] = keys[p];
+    out[i] = T.names ? pair_key(T.names, T.bits, T.rc->h, p, count) : keys[p];
     return;
   }
   if (T.nl.m) {
@@ -740,7 +750,7 @@ __global__ __launch_bounds__(kSplitBlock)
 __attribute__((amdgpu_waves_per_eu(FROM == kFromBatch ? 5 : 4))) void split_hist_kernel(
     const u64* __restrict__ keys, SplitText T, SplitShape S, SplitArrays A,
     u64* __restrict__ counters) {
-  constexpr bool TEXT = FROM != kFromKeys;
+  constexpr bool TEXT = FROM == kFromText || FROM == kFromBatch;
   // A tile of a batch has few buckets (those of its text): four counts for each.
   constexpr u32 COPIES = FROM == kFromBatch ? 4 : 1;
   __shared__ u16 s_code[TEXT ? 256 : 1];
@@ -773,6 +783,7 @@ __attribute__((amdgpu_waves_per_eu(FROM == kFromBatch ? 5 : 4))) void split_hist
     }
   }
   BatchText bt{};
+  const u64 h = FROM == kFromNames ? T.rc->h : 0;
   load_splitters<SECOND>(A, row, logd, S.log2 != 0, s_sp, s_fl);
   for (u32 i = tid; i < d * COPIES; i += kSplitBlock) s_cnt[i] = 0;
   __syncthreads();
@@ -799,7 +810,10 @@ __attribute__((amdgpu_waves_per_eu(FROM == kFromBatch ? 5 : 4))) void split_hist
 #pragma unroll
       for (int j = 0; j < ITEMS; ++j) {
         const u32 e = u32(j) * kSplitBlock + tid;
-        key[j] = e < n ? keys[u64(base) + e] : 0;
+        if constexpr (FROM == kFromNames)
+          key[j] = e < n ? pair_key(T.names, T.bits, h, base + e, S.count) : 0;
+        else
+          key[j] = e < n ? keys[u64(base) + e] : 0;
       }
     }
     u32 bk[ITEMS];
@@ -872,7 +886,7 @@ void split_sweep_kernel(
     u32* __restrict__ vout, SplitShape S, SplitArrays A, int iota, SplitPlanOut plan,
     u64* __restrict__ counters) {
   constexpr u32 TILE = u32(ITEMS) * kSplitBlock;
-  constexpr bool TEXT = FROM != kFromKeys;
+  constexpr bool TEXT = FROM == kFromText || FROM == kFromBatch;
   static_assert(kSplitMaxD <= 2 * kSplitBlock, "two buckets per thread");
   __shared__ u64 s_buf[TILE];       // codes of a text, then keys, then values
   static_assert(2 * (TILE + kKeyHalo) <= 8 * TILE, "the tile's codes fit");
@@ -904,6 +918,7 @@ void split_sweep_kernel(
   auto item = [&](int j) { return TEXT ? tid * ITEMS + j : u32(j) * kSplitBlock + tid; };
   u64 key[ITEMS];
   u32 val[ITEMS];
+  const u64 h = FROM == kFromNames ? T.rc->h : 0;
   if constexpr (FROM == kFromBatch) {
     BatchText bt{};
     batch_keys<ITEMS>(T, bt, t.base, t.n, s_code, reinterpret_cast<u16*>(s_buf), key, val);
@@ -915,7 +930,10 @@ void split_sweep_kernel(
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
       const u32 e = item(j);
-      key[j] = e < t.n ? __builtin_nontemporal_load(kin + t.base + e) : 0;
+      if constexpr (FROM == kFromNames)
+        key[j] = e < t.n ? pair_key(T.names, T.bits, h, t.base + e, S.count) : 0;
+      else
+        key[j] = e < t.n ? __builtin_nontemporal_load(kin + t.base + e) : 0;
     }
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
@@ -1800,6 +1818,9 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
       } else if (T.text) {
         if (small) SA_HIST(4, false, kFromText, hgrid, bf.kA, ctr_top);
         else SA_HIST(kSweepItems, false, kFromText, hgrid, bf.kA, ctr_top);
+      } else if (T.names) {
+        if (small) SA_HIST(4, false, kFromNames, hgrid, bf.kA, ctr_top);
+        else SA_HIST(kSweepItems, false, kFromNames, hgrid, bf.kA, ctr_top);
       } else {
         if (small) SA_HIST(4, false, kFromKeys, hgrid, bf.kA, ctr_top);
         else SA_HIST(kSweepItems, false, kFromKeys, hgrid, bf.kA, ctr_top);
@@ -1814,6 +1835,9 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
       } else if (T.text) {
         if (small) SA_SWEEP(4, false, kFromText, grid, bf.kA, vin, bf.kB, bf.vB, iota);
         else SA_SWEEP(kSweepItems, false, kFromText, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+      } else if (T.names) {
+        if (small) SA_SWEEP(4, false, kFromNames, grid, bf.kA, vin, bf.kB, bf.vB, iota);
+        else SA_SWEEP(kSweepItems, false, kFromNames, grid, bf.kA, vin, bf.kB, bf.vB, iota);
       } else {
         if (small) SA_SWEEP(4, false, kFromKeys, grid, bf.kA, vin, bf.kB, bf.vB, iota);
         else SA_SWEEP(kSweepItems, false, kFromKeys, grid, bf.kA, vin, bf.kB, bf.vB, iota);
@@ -1915,13 +1939,29 @@ sa_status split_sort(sa_ctx* c, const Bufs& bf, u64 count, int npass, int vals_p
                    slot, &fin, s);
 }
 
+bool split_from_names(u64 count) { return split_shape(count).log1 != 0; }
+
+sa_status split_dense(sa_ctx* c, const Bufs& bf, u64 n, int bits, int npass, int slot,
+                      hipStream_t s) {
+  u32 fin = 0;
+  const Carver cv{reinterpret_cast<char*>(c->act_idx), size_t(c->cap) * 4};
+  SplitText T{};
+  T.names = c->isa;
+  T.rc = c->rc;
+  T.bits = bits;
+  return split_run(c, bf, n, T, SplitFinal{}, 1, cv, true, npass, slot, &fin, s);
+}
+
 bool split_small_text(u64 n) { return split_shape(n).log2 == 0; }
 
 sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, hipStream_t s) {
   u32 fin = 0;
   const Carver cv{reinterpret_cast<char*>(c->isa), size_t(c->cap) * 4};
-  const SplitText T{text, c->code, c->counters, (reinterpret_cast<uintptr_t>(text) & 3) == 0,
-                    {}, {}, 0};
+  SplitText T{};
+  T.text = text;
+  T.code = c->code;
+  T.counters = c->counters;
+  T.words = (reinterpret_cast<uintptr_t>(text) & 3) == 0;
   const SplitFinal out{d_sa, c->act_idx, nullptr, c->act_rank, nullptr, 0};
   return split_run(c, full_bufs(c), n, T, out, 1, cv, true, npass, 0, &fin, s);
 }
