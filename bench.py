@@ -106,24 +106,22 @@ def measured_traffic(workload: str):
     return rec.get("bytes_per_launch")
 
 
-def algorithmic_bytes(info: dict) -> float:
-    """Bytes the method must move for one build (whole-build roofline):
-    13 per suffix for the round-0 keys (text, key, value), 4 per suffix for the
-    SA, and per round k with A_k suffixes sorted in P_k radix passes:
-    A_k * (24 P_k + 24) (sweeps, the up-front histogram and the re-rank),
-    24 A_k for the pair build (k >= 1) and 8 A_{k+1} for the survivors. A dense
-    round (every suffix, names read in position order) builds its keys from 16
-    bytes per suffix and its first sweep generates the values (4 fewer)."""
-    A, P, n = info["active"], info["passes_run"], info["n"]
-    dense = set(info.get("dense_rounds", []))
-    b = 17.0 * n
-    for k, a in enumerate(A):
-        b += a * (24.0 * P[k] + 24.0)
-        if k >= 1:
-            b += (12.0 if k in dense else 24.0) * a
-        if k + 1 < len(A):
-            b += 8.0 * A[k + 1]
-    return b
+# Suffixes that the split sort takes at once (the library's limit): a longer single
+# text, or an explicit tuning, is sorted by the LSD sweeps.
+SPLIT_MAX = 1280 << 20
+
+
+def sort_kernels(explicit: bool, n: int, batch: bool) -> str:
+    """Names of the kernels that move the pairs of a build's sorts."""
+    if explicit or (n > SPLIT_MAX and not batch):
+        return "onesweep_pass_kernel"
+    return "split_sweep_kernel + split_local_kernel"
+
+
+def algorithmic_bytes(stats: dict, steps: int) -> float:
+    """Bytes one build must move (whole-build roofline): what every launch of the
+    traced builds reports for its step (inputs read and outputs written once)."""
+    return sum(k["bytes"] for k in stats.values()) / max(1, steps)
 
 
 def cpu_model() -> str:
@@ -246,7 +244,8 @@ def run_build(name: str, steps: int, warmup: int, cpu: bool, sort_items: int = 0
     stats = b.kernel_stats()
     ms = gpu_ms / steps
     value = n / (ms / 1e3) / 1e6
-    balg = algorithmic_bytes(info)
+    balg = algorithmic_bytes(stats, steps)
+    kernel = sort_kernels(sort_items > 0, n, offsets is not None)
     whole = balg / (ms / 1e3) / 1e9
     sweep = stats["sort_pass"]
     achieved = sweep["bytes"] / (sweep["ms"] / 1e3) / 1e9 if sweep["ms"] > 0 else 0.0
@@ -264,9 +263,9 @@ def run_build(name: str, steps: int, warmup: int, cpu: bool, sort_items: int = 0
             "bound": "hbm", "algorithmic_bytes": round(balg), "achieved": round(whole, 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(whole / HBM_PEAK_GBS, 4)},
         "sweep_roofline": {
-            "bound": "hbm", "kernel": "onesweep_pass_kernel", "achieved": round(achieved, 1),
+            "bound": "hbm", "kernel": kernel, "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": measured_traffic(name),
+            "traffic": measured_traffic(name) if kernel == "onesweep_pass_kernel" else None,
             "algorithmic_bytes_per_launch": round(sweep["bytes"] / max(1, sweep["launches"])),
             "launches": sweep["launches"],
             "avg_launch_us": round(sweep["ms"] * 1e3 / max(1, sweep["launches"]), 2)},

@@ -155,7 +155,8 @@ typedef struct {
   uint64_t dense_rounds;  /* bit k: round k was dense (most suffixes still active, so it
                              sorted all n with the names read in position order) */
   uint64_t active[SA_MAX_ROUNDS];       /* suffixes sorted in round k */
-  uint32_t passes_run[SA_MAX_ROUNDS];   /* radix passes executed in round k */
+  uint32_t passes_run[SA_MAX_ROUNDS];   /* digits of the keys of round k that vary: the
+                                           passes of a radix sort of them */
   uint32_t key_bits[SA_MAX_ROUNDS];     /* key bits sorted in round k */
 } sa_build_info;
 
@@ -244,7 +245,9 @@ sa_status sa_ctx_set_isa_mode(sa_ctx* ctx, int mode);
 /* Tuning knobs (none changes a result). Unknown or unsupported values give
  * SA_EINVAL and leave the context unchanged. Defaults: 512-thread sweep
  * workgroups of 8 items, the workgroups one CU holds, lazy_ratio 8, trimmed
- * round-0 keys. */
+ * round-0 keys. The sort_ knobs and radix_bits describe the LSD sweeps, which every
+ * sort of a context takes once sa_ctx_set_tuning() has set them; without, builds sort
+ * by sampled splitters where that is possible and these knobs apply to the rest. */
 typedef struct {
   uint32_t sort_items;   /* radix-sort items per thread: 8, 12, 16, 20 or 24 with 256-thread
                             workgroups (tile = sort_block x sort_items) */
@@ -384,8 +387,8 @@ size_t sa_workspace_bytes(uint64_t total_n, uint32_t num_texts);
  * bytes of those launches (what the step must read and write, random 4-byte
  * accesses counted at 4 bytes). */
 enum {
-  SA_KERNEL_SORT_PASS = 0,   /* one radix-sort sweep */
-  SA_KERNEL_HISTOGRAM = 1,   /* up-front digit histograms */
+  SA_KERNEL_SORT_PASS = 0,   /* one radix-sort or scattering sweep, or the sorts in LDS */
+  SA_KERNEL_HISTOGRAM = 1,   /* digit histograms, bucket counts */
   SA_KERNEL_RERANK = 2,      /* re-rank, ISA scatter, finalise, compact */
   SA_KERNEL_PACK_TEXT = 3,   /* round-0 keys from the text */
   SA_KERNEL_PACK_PAIRS = 4,  /* round >= 1 keys (ISA gather) */

@@ -18,7 +18,8 @@
 //      comparison ties. The merge splits the output into tiles along the merge
 //      path (a binary search per tile boundary) and merges each tile in LDS.
 //
-// The sorts are the library's LSD radix sort. A triple of b-bit symbols fits a
+// The sorts are the split sort where equal tuples may come out in any order and the
+// LSD radix sort where they may not. A triple of b-bit symbols fits a
 // 64-bit key while 3b <= 64 (the bytes of the text: 27 bits); wider levels
 // sort it as two words, (x[i+1], x[i+2]) first and then x[i] with the first
 // word's run names as tie words, exactly as the quadrupling rounds do.

@@ -6,13 +6,13 @@
 //
 //   1. The sample as the string x0 x1 x3 (positions 0, 7, 14, ... then 1, 8,
 //      ... then 3, 10, ...), each entry named by its seven characters
-//      (9 bits each with the sentinel below every byte: 63-bit radix keys).
+//      (9 bits each with the sentinel below every byte: 63-bit keys).
 //      A part whose last tuple has no sentinel (n mod 7 == 0 for x0, 1 for x1)
 //      ends with a dummy position n: an all-sentinel tuple, unique and the
 //      smallest, so that no suffix of the name string compares across parts.
 //   2. The sample's suffix order: from the sorted tuples when the names are
 //      unique, else by DC3 on the name string.
-//   3. The four other classes (2, 4, 5, 6 mod 7) in one radix sort, keyed by
+//   3. The four other classes (2, 4, 5, 6 mod 7) in one sort, keyed by
 //      (class, the characters up to the next sample position, its rank).
 //   4. Five sorted lists (four classes and the sample by rank) merged pairwise
 //      along the merge path, with the comparison above on 24-byte records of

@@ -313,8 +313,14 @@ sa_status split_dense(sa_ctx* c, const Bufs& bf, u64 n, int bits, int npass, int
 // by split_round0 (c->present zero on entry and exit), others before it.
 bool split_small_text(u64 n);
 sa_status split_round0(sa_ctx* c, const u8* text, u64 n, int npass, u32* d_sa, hipStream_t s);
-sa_status split_batch0(sa_ctx* c, u64 n, int npass, const u8* arena, const TextTab& tab,
-                       const NewList& nl, int idshift, u32* d_sa, hipStream_t s);
+// A batch's joining texts, elements out[i] .. out[i + 1] each, are sorted in groups of
+// whole texts (their slots lead the keys, so the groups' sorted keys follow one
+// another): cut holds the groups' first texts and, last, their number. False where the
+// split sort may not take them.
+bool split_batch_groups(const sa_ctx* c, const std::vector<u64>& out, std::vector<u32>* cut);
+sa_status split_batch0(sa_ctx* c, const std::vector<u64>& nout, const std::vector<u32>& cut,
+                       int npass, const u8* arena, const TextTab& tab, const NewList& nl,
+                       int idshift, u32* d_sa, hipStream_t s);
 // Whether split_batch0 takes the keys of n suffixes from the texts themselves (not
 // packed before): where the sort begins with a sweep.
 bool split_batch_from_text(u64 n);

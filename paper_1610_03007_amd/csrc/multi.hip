@@ -238,7 +238,8 @@ struct Engine {
         launch_fill_u64(c->counters, kCtrCount, 0, s);
         launch_fill_u32(tab.surv, slots, 0, s);
       }
-      fused = defer_round0_isa && m && !active && split_usable(c, total);
+      std::vector<u32> cut;
+      fused = defer_round0_isa && m && !active && split_batch_groups(c, nout, &cut);
       if (m) {
         {
           Tracer tr(c, s, SA_KERNEL_OTHER, double(A0));
@@ -266,7 +267,7 @@ struct Engine {
       if (total) {
         if (fused) {
           const sa_status fs =
-              split_batch0(c, total, npass_for(c, 64), text_arena, tab, nl, round0_shift,
+              split_batch0(c, nout, cut, npass_for(c, 64), text_arena, tab, nl, round0_shift,
                            sa_arena, s);
           if (fs != SA_OK) return fs;
         } else {

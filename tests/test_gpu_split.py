@@ -183,3 +183,29 @@ def test_batch_keys_from_texts(builder, lo, hi, total):
         sa = sa.cpu().numpy().view(np.uint32)
         for k, t in enumerate(texts):
             assert np.array_equal(sa[off[k]:off[k + 1]], oracle.sa(t)), (k, t.size)
+
+
+def test_batch_groups():
+    """A batch of more suffixes than one split sort takes (1280 * 2^20), whose texts are
+    sorted in groups, against the LSD sort of the whole (an explicit tuning asks for
+    it)."""
+    rng = np.random.default_rng(29)
+    sizes = rng.integers(0, 7_000_000, 400)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    assert off[-1] > (1280 << 20)
+    gen = torch.Generator(device="cuda:0").manual_seed(29)
+    d = torch.randint(0, 200, (int(off[-1]),), dtype=torch.uint8, device="cuda:0", generator=gen)
+    d[int(off[100]):int(off[130])] %= 3
+    d[int(off[200]):int(off[201])] = 7
+    got = []
+    for explicit in (False, True):
+        b = SuffixArrayBuilder(0, tune_cache="")
+        if explicit:
+            b.set_tuning(**b.tuning())
+        got.append(b.build_batch(d, off))
+        torch.cuda.synchronize()
+        got.append(b.last_info())
+        b.close()
+    assert torch.equal(got[0], got[2])
+    for key in ("rounds", "active"):
+        assert got[1][key] == got[3][key]
