@@ -209,3 +209,28 @@ def test_batch_groups():
     assert torch.equal(got[0], got[2])
     for key in ("rounds", "active"):
         assert got[1][key] == got[3][key]
+
+
+def test_batch_overflow_repeats_with_lsd(builder):
+    """The same in a batch, whose repeat packs the keys that the first try took from
+    the texts."""
+    n, samples, cut = 20000, 512, 137
+    rng = np.random.default_rng(6)
+    t = rng.integers(1, 256, n).astype(np.uint8)
+    for i in range(samples):
+        lo, hi = i * n // samples, (i + 1) * n // samples
+        p = lo + mix32((i + 0x9e3779b9) & 0xFFFFFFFF) % (hi - lo)
+        t[p:p + 8] = 1
+    d = torch.from_numpy(t).to("cuda:0")
+    builder.set_trace(True)
+    try:
+        builder.reset_stats()
+        sa = builder.build_batch(d, [0, cut, n])
+        torch.cuda.synchronize()
+        stats = builder.kernel_stats()
+    finally:
+        builder.set_trace(False)
+    sa = sa.cpu().numpy().view(np.uint32)
+    assert np.array_equal(sa[:cut], oracle.sa(t[:cut]))
+    assert np.array_equal(sa[cut:], oracle.sa(t[cut:]))
+    assert stats["pack_text"]["launches"] == 1 and stats["sort_pass"]["launches"] > 8
