@@ -395,7 +395,8 @@ void enqueue_later_round(sa_ctx* c, const LaterRound& L, bool reserve, int log_r
   begin_sort(c, L.bound, c->counters + kCtrActive, c->rc, L.npass, reserve, s, L.dense_n, 1,
              !L.one && !split_count);
   // A dense round's keys go from the names straight into the sort's first count and
-  // sweep (2^30 suffixes: writing and reading them first took 5.0 ms of 46).
+  // sweep (2^30 suffixes: packing them first took 5.0 ms of 46; the sweep, whose reads
+  // are two streams of 4 bytes, takes 1.7 ms more).
   const bool from_names = split_count && trace_dense && split_from_names(split_count);
   if (!from_names) {
     // A dense round reads two names and writes a key per suffix (16 bytes);

@@ -307,7 +307,9 @@ __device__ inline void text_keys(const SplitText& T, u32 base, u32 count, u16* s
 // tile's are there), and the suffixes' positions in their texts. A tile inside one
 // text is read and rolled as above; one that several texts share (a quarter of the
 // tiles at 32 KiB a text, all of them below 6 KiB) looks each byte's code up in its
-// text's table, in L2.
+// text's table, in L2. 1024 texts of 1.1e9 bytes: 42.5 -> 39.3 ms a build against
+// packing the keys first (4.5 ms, and 2.9 to count them); 4096 of 1.4e8 bytes 2.82 ->
+// 2.77.
 struct BatchText {  // the text of a workgroup's last tile (its codes are in LDS)
   u64 begin, end;   // its elements
   u64 len;
@@ -759,7 +761,8 @@ __attribute__((amdgpu_waves_per_eu(FROM == kFromBatch ? 5 : 4))) void split_hist
     const u64* __restrict__ keys, SplitText T, SplitShape S, SplitArrays A,
     u64* __restrict__ counters) {
   constexpr bool TEXT = FROM == kFromText || FROM == kFromBatch;
-  // A tile of a batch has few buckets (those of its text): four counts for each.
+  // A tile of a batch has few buckets (those of its text), on whose counts the LDS adds
+  // of a wave queue: four counts for each (1.1e9 suffixes: 4.1 -> 3.5 ms).
   constexpr u32 COPIES = FROM == kFromBatch ? 4 : 1;
   __shared__ u16 s_code[TEXT ? 256 : 1];
   __shared__ u16 s_sym[TEXT ? ITEMS * kSplitBlock + kKeyHalo : 1];
