@@ -1106,10 +1106,15 @@ __device__ inline u64 wave_sort(u64 v) {
 }
 
 // Every bucket sorted in place, one workgroup each (a persistent grid strides
-// over them). BLOCK of the bucket's keys, sorted (each wave its 64 in
-// registers, then their places among the other waves' by binary search), are the
-// splitters of BLOCK parts of about four pairs; the pairs go to their parts in
+// over them). BLOCK of the bucket's keys, taken evenly from all of it and sorted (each
+// wave its 64 in registers, then their places among the other waves' by binary search),
+// are the splitters of BLOCK parts of about four pairs; the pairs go to their parts in
 // LDS, and each takes its place there by counting the smaller keys of its part.
+// (The bucket's first BLOCK keys are no sample where pairs come nearly in key order: 1 MiB
+// of ascending numbers, a line each, took 506 us a build with them, 130 with these, and
+// 318 with the LSD sort.) A bucket of fewer than BLOCK pairs has all its keys as samples,
+// one of fewer than BLOCK / 4 is one part, which counting sorts sooner (1000 bytes as
+// one bucket: 129 us a build as one part, 48 split).
 // Bound by memory (24 bytes a pair) as long as the LDS work (about 25 reads a
 // pair) and the waits between its steps stay below it: the next bucket's pairs
 // are requested as soon as this one's are in LDS, and a workgroup is small (two
@@ -1318,12 +1323,20 @@ void split_local_kernel(
       if (plan.plan) write_plan(plan, o & n);
       __syncthreads();
     }
-    const bool split = m >= u32(P);  // fewer pairs: one part
+    const bool split = m >= u32(P) / 4;  // fewer pairs: one part
     s_cnt[tid] = 0;
     if (split) {
-      // (Keys in no particular order, which a whole input need not be in: an earlier
-      // round's survivors come nearly sorted.)
-      const u64 k = wave_sort(TINY || start ? key[0] : keys[u64(tid) * m / P]);
+      // One key of each thread, of its rows of the bucket in turn (a bit-reversed
+      // thread number spreads them evenly over each row): pairs may come in the order
+      // of their keys (sorted records, an earlier round's survivors), where the first P
+      // alone would leave all others in one part.
+      const u32 rows = (m + BLOCK - 1) / BLOCK;  // <= IT
+      u32 row = __umulhi(__brev(tid), rows);
+      if (row > 0 && row * BLOCK + tid >= m) --row;
+      u64 k = row * BLOCK + tid < m ? key[0] : ~u64(0);
+#pragma unroll
+      for (int j = 1; j < IT; ++j) k = row == u32(j) ? key[j] : k;
+      k = wave_sort(k);
       s_raw[tid] = k;
       __syncthreads();
       // Place among all samples: equal ones of earlier waves come first.
