@@ -1105,6 +1105,21 @@ __device__ inline u64 wave_sort(u64 v) {
   return v;
 }
 
+// First place of the run of equal keys that place q of a sorted bucket is in (k: its
+// key above the low sh bits): steps back that double while they stay in the run, then
+// halve, so that a run of r pairs takes 2 log2(r) reads (one key at a time, a text of
+// 4608 equal bytes took 1.45 ms a build).
+__device__ inline u32 run_head(const u64* s_key, u32 q, int sh, u64 k) {
+  u32 h = q, step = 1;
+  while (step <= h && s_key[h - step] >> sh == k) {
+    h -= step;
+    step *= 2;
+  }
+  while (step >>= 1)
+    if (step <= h && s_key[h - step] >> sh == k) h -= step;
+  return h;
+}
+
 // Every bucket sorted in place, one workgroup each (a persistent grid strides
 // over them). BLOCK of the bucket's keys, taken evenly from all of it and sorted (each
 // wave its 64 in registers, then their places among the other waves' by binary search),
@@ -1528,8 +1543,7 @@ void split_local_kernel(
             if ((same >> j) & 1u) {
               const u64 x = s_key[q], k = x >> sh;
               const u32 v = s_val[narrow ? u32(x) & PMASK : q];
-              u32 h = q;
-              while (h > 0 && s_key[h - 1] >> sh == k) --h;
+              const u32 h = run_head(s_key, q, sh, k);
               const u64 o = s_out + atomicAdd(&s_taken, 1u);
               u64 name = fin.first + a + h + 1;
               if (fin.tbase) {

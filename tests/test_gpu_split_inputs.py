@@ -83,3 +83,42 @@ def test_small_buckets(builders, n):
         sa = builders[0].build(torch.from_numpy(t).to("cuda:0"))
         torch.cuda.synchronize()
         assert np.array_equal(sa.cpu().numpy().view(np.uint32), oracle.sa(t))
+
+
+def repeats(kind, n):
+    if kind == "period":
+        return np.tile(np.arange(65, 67, dtype=np.uint8), n // 2 + 1)[:n]
+    if kind == "runs":
+        return np.random.default_rng(n).integers(0, 250, n // 100 + 1).astype(np.uint8).repeat(100)[:n]
+    return np.full(n, 65, dtype=np.uint8)
+
+
+@pytest.mark.parametrize("kind,n", [("one", 300), ("one", 2000), ("one", 4095), ("one", 4608),
+                                    ("period", 4608), ("runs", 4608), ("runs", 1 << 20)])
+def test_runs_of_equal_keys(builders, kind, n):
+    """Runs of equal keys inside buckets that are no equality buckets: each survivor
+    looks for the head of its run."""
+    t = repeats(kind, n)
+    d = torch.from_numpy(t.copy()).to("cuda:0")
+    want = oracle.sa(t, parallel=True)
+    for b in builders:
+        sa = b.build(d)
+        torch.cuda.synchronize()
+        assert np.array_equal(sa.cpu().numpy().view(np.uint32), want)
+    if (kind, n) in (("one", 4608), ("runs", 1 << 20)):
+        split, lsd = (best_ms(lambda: b.build(d)) for b in builders)
+        assert split < lsd, (split, lsd)
+
+
+@pytest.mark.parametrize("texts,n", [(2, 2304), (4096, 1000)])
+def test_runs_in_a_batch(builders, texts, n):
+    """The same in a batch of texts of one byte each: every text is one run."""
+    t = np.repeat(np.arange(texts) % 251, n).astype(np.uint8)
+    off = np.arange(texts + 1, dtype=np.uint64) * np.uint64(n)
+    d = torch.from_numpy(t).to("cuda:0")
+    want = torch.arange(n - 1, -1, -1, dtype=torch.int32, device="cuda:0").repeat(texts)
+    for b in builders:
+        assert torch.equal(b.build_batch(d, off), want)
+    if texts == 2:  # (round 0 in one bucket)
+        split, lsd = (best_ms(lambda: b.build_batch(d, off)) for b in builders)
+        assert split < lsd, (split, lsd)
