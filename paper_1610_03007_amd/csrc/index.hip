@@ -113,10 +113,11 @@ __device__ inline Head suffix_head(const u8* __restrict__ text, u64 n, u64 x) {
 // Bound by the random reads of the text (a line per suffix): each suffix's first
 // 16 bytes are read once, by one lane, and its successor takes them from that lane
 // (neighbours used to read both suffixes of every pair: two lines per entry, 2^26
-// suffixes of a Markov text in 1.62 ms). A wave goes through kLcpRows rows of 64
-// consecutive entries, kLcpGang of them at a time so that their reads overlap.
-constexpr int kLcpRows = 16;
-constexpr int kLcpGang = 4;
+// suffixes of a Markov text in 1.62 ms). A wave takes kLcpRows rows of 64 consecutive
+// entries, whose reads overlap. (16 rows, four at a time, save few second reads and
+// leave short texts to few waves: 1000 bytes 35 us a call, 43 with 16; 2^26 the same,
+// 0.74 and 0.84 ms for sorted lines.)
+constexpr int kLcpRows = 4;
 __global__ __launch_bounds__(256) void lcp_direct_kernel(const u8* __restrict__ text, u64 n,
                                                          const u32* __restrict__ sa,
                                                          u32* __restrict__ lcp,
@@ -131,51 +132,49 @@ __global__ __launch_bounds__(256) void lcp_direct_kernel(const u8* __restrict__ 
   // The suffix before the wave's first entry.
   u32 carry_s = first > 0 ? sa[first - 1] : 0;
   Head carry = first > 0 ? suffix_head(text, n, carry_s) : Head{0, 0};
-  for (int r0 = 0; r0 < kLcpRows; r0 += kLcpGang) {
-    u32 b[kLcpGang];
-    Head h[kLcpGang];
+  u32 b[kLcpRows];
+  Head h[kLcpRows];
 #pragma unroll
-    for (int g = 0; g < kLcpGang; ++g) {
-      const u64 j = first + u64(r0 + g) * kWave + lane;
-      b[g] = j < n ? sa[j] : 0;
+  for (int g = 0; g < kLcpRows; ++g) {
+    const u64 j = first + u64(g) * kWave + lane;
+    b[g] = j < n ? sa[j] : 0;
+  }
+#pragma unroll
+  for (int g = 0; g < kLcpRows; ++g) h[g] = suffix_head(text, n, b[g]);
+#pragma unroll
+  for (int g = 0; g < kLcpRows; ++g) {
+    const u64 j = first + u64(g) * kWave + lane;
+    u32 a = __shfl_up(b[g], 1, kWave);
+    Head p{__shfl_up(h[g].lo, 1, kWave), __shfl_up(h[g].hi, 1, kWave)};
+    if (lane == 0) {
+      a = carry_s;
+      p = carry;
     }
-#pragma unroll
-    for (int g = 0; g < kLcpGang; ++g) h[g] = suffix_head(text, n, b[g]);
-#pragma unroll
-    for (int g = 0; g < kLcpGang; ++g) {
-      const u64 j = first + u64(r0 + g) * kWave + lane;
-      u32 a = __shfl_up(b[g], 1, kWave);
-      Head p{__shfl_up(h[g].lo, 1, kWave), __shfl_up(h[g].hi, 1, kWave)};
-      if (lane == 0) {
-        a = carry_s;
-        p = carry;
-      }
-      carry_s = __shfl(b[g], kWave - 1, kWave);
-      carry.lo = __shfl(h[g].lo, kWave - 1, kWave);
-      carry.hi = __shfl(h[g].hi, kWave - 1, kWave);
-      if (j >= n) continue;
-      if (j == 0) {
-        lcp[0] = 0;
-        continue;
-      }
-      if (a >= n || b[g] >= n || a == b[g]) {
-        flag_error(err);
-        lcp[j] = 0;
-        continue;
-      }
-      const u64 room = n - (a > b[g] ? a : b[g]);
-      const u64 dl = p.lo ^ h[g].lo, dh = p.hi ^ h[g].hi;
-      u32 m = dl ? u32(__builtin_ctzll(dl) / 8) : dh ? 8 + u32(__builtin_ctzll(dh) / 8) : 16u;
-      if (m > room) m = u32(room);
-      if (m == 16) m += common_prefix(text, n, u64(a) + 16, u64(b[g]) + 16, kLcpCap - 16);
-      if (m < kLcpCap) {
-        lcp[j] = m;
-      } else {
-        lcp[j] = kLcpLong;
-        phi[b[g]] = a;
-        atomicOr(&long_bits[b[g] >> 5], 1u << (b[g] & 31u));
-        *any_long = 1;
-      }
+    carry_s = __shfl(b[g], kWave - 1, kWave);
+    carry.lo = __shfl(h[g].lo, kWave - 1, kWave);
+    carry.hi = __shfl(h[g].hi, kWave - 1, kWave);
+    if (j >= n) continue;
+    if (j == 0) {
+      lcp[0] = 0;
+      continue;
+    }
+    if (a >= n || b[g] >= n || a == b[g]) {
+      flag_error(err);
+      lcp[j] = 0;
+      continue;
+    }
+    const u64 room = n - (a > b[g] ? a : b[g]);
+    const u64 dl = p.lo ^ h[g].lo, dh = p.hi ^ h[g].hi;
+    u32 m = dl ? u32(__builtin_ctzll(dl) / 8) : dh ? 8 + u32(__builtin_ctzll(dh) / 8) : 16u;
+    if (m > room) m = u32(room);
+    if (m == 16) m += common_prefix(text, n, u64(a) + 16, u64(b[g]) + 16, kLcpCap - 16);
+    if (m < kLcpCap) {
+      lcp[j] = m;
+    } else {
+      lcp[j] = kLcpLong;
+      phi[b[g]] = a;
+      atomicOr(&long_bits[b[g] >> 5], 1u << (b[g] & 31u));
+      *any_long = 1;
     }
   }
 }

@@ -214,3 +214,14 @@ def test_index_memory_reused(builder):
     for fm, pats, want in kept:
         got = fm.count(pats).cpu().numpy()
         assert [int(r[1] - r[0]) for r in got] == want
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 65535, 65537])
+def test_lcp_rows(builder, n):
+    """LCP arrays whose last wave (256 entries) and last workgroup (1024) are full, hold
+    one entry, or lack one."""
+    rng = np.random.default_rng(n)
+    for t in (rng.integers(0, 3, n).astype(np.uint8), np.tile(np.arange(40, dtype=np.uint8), n)[:n]):
+        d, sa = on_gpu(builder, t)
+        want = oracle.lcp(t, sa.cpu().numpy().view(np.uint32))
+        assert np.array_equal(builder.lcp(d, sa).cpu().numpy().view(np.uint32), want)
