@@ -324,15 +324,18 @@ sa_status split_batch0(sa_ctx* c, const std::vector<u64>& nout, const std::vecto
 // Whether split_batch0 takes the keys of n suffixes from the texts themselves (not
 // packed before): where the sort begins with a sweep.
 bool split_batch_from_text(u64 n);
-// Runs a whole build; once more with the LSD sort if the split sort overflowed.
+// Runs a whole build, or one round of a batch; once more with the LSD sort if the split
+// sort overflowed. The trace records of the failed attempt go, those of earlier rounds
+// stay.
 template <typename F>
 sa_status with_lsd_repeat(sa_ctx* c, F&& build) {
   c->split_over = false;
+  const size_t records = c->recs.size(), events = c->event_used;
   sa_status st = build();
   if (st == SA_OK || !c->split_over) return st;
   c->split_over = false;
-  c->recs.clear();
-  c->event_used = 0;
+  c->recs.resize(records);
+  c->event_used = events;
   c->force_lsd = true;
   st = build();
   c->force_lsd = false;
