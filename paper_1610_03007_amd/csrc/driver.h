@@ -5,8 +5,6 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
-#include <memory>
-#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -59,22 +57,7 @@ struct TraceRec {
   u64 count;
 };
 
-// The device memory of the last FM index destroyed, for the next one: allocating
-// and freeing it took a fifth of an index's making (2^26 bytes: 0.4 of 2.0 ms). At
-// most one block of kFmSpareMax bytes, shared by a context and its indexes and freed
-// with the last of them (or when the context runs out of memory).
-constexpr size_t kFmSpareMax = size_t(1) << 30;
-struct FmSpare {
-  std::mutex mu;
-  int device = 0;
-  void* p = nullptr;
-  size_t bytes = 0;
-  void release();
-  ~FmSpare() { release(); }
-};
-
 struct sa_ctx {
-  std::shared_ptr<FmSpare> fm_spare;  // made by the first index
   int device = 0;
   u64 cap = 0;  // element capacity of the workspace
   u64* keysA = nullptr;
@@ -195,13 +178,14 @@ static_assert(kSmallCounters % 8 == 0 && kSmallRoundCtl % 8 == 0, "mirror alignm
 static_assert(sizeof(SortCtl) <= kSmallCtl, "control block");
 
 
-// Device memory for a context: asked for again without the spare index block if
-// there is too little.
-bool ctx_malloc(sa_ctx* c, void** p, size_t bytes);
-
 template <typename T>
-bool dev_alloc(sa_ctx* c, T** p, u64 count) {
-  return ctx_malloc(c, reinterpret_cast<void**>(p), std::max<u64>(count, 1) * sizeof(T));
+bool dev_alloc(T** p, u64 count) {
+  if (hipMalloc(reinterpret_cast<void**>(p), std::max<u64>(count, 1) * sizeof(T)) != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+    return false;
+  }
+  return true;
 }
 
 u64 sort_status_words(u64 cap);

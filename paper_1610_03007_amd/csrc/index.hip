@@ -539,8 +539,6 @@ sa_status finish(sa_ctx* c, hipStream_t s) {
 
 // The FM index: the transform rows, the occurrence samples and the tables.
 struct sa_fm {
-  std::shared_ptr<FmSpare> spare;
-  size_t bytes = 0;  // of dev
   int device = 0;
   u64 n = 0, dollar = 0, nblocks = 0, stride_b = 0;
   u32 sigma = 0;
@@ -550,15 +548,6 @@ struct sa_fm {
   u64* C = nullptr;
   u16* code = nullptr;
 };
-
-void FmSpare::release() {
-  std::lock_guard<std::mutex> lk(mu);
-  if (!p) return;
-  (void)hipSetDevice(device);
-  (void)hipFree(p);
-  p = nullptr;
-  bytes = 0;
-}
 
 extern "C" {
 
@@ -663,32 +652,10 @@ sa_status sa_fm_create(sa_fm** out, sa_ctx* ctx, const uint8_t* d_text, uint64_t
   const size_t off_occ = b_bytes, off_C = off_occ + occ_bytes, off_code = off_C + 256 * 8,
                off_tot = off_code + 512 + 256,
                total = off_tot + size_t(std::max<u32>(fm->sigma, 1)) * chunks * 8;
-  try {
-    if (!ctx->fm_spare) {
-      ctx->fm_spare = std::make_shared<FmSpare>();
-      ctx->fm_spare->device = ctx->device;
-    }
-  } catch (...) {
+  if (hipMalloc(&fm->dev, total) != hipSuccess) {
+    (void)hipGetLastError();
     delete fm;
     return SA_ENOMEM;
-  }
-  fm->spare = ctx->fm_spare;
-  {
-    // The spare block, if it is large enough and not much too large.
-    std::lock_guard<std::mutex> lk(fm->spare->mu);
-    if (fm->spare->p && fm->spare->bytes >= total && fm->spare->bytes / 2 <= total) {
-      fm->dev = fm->spare->p;
-      fm->bytes = fm->spare->bytes;
-      fm->spare->p = nullptr;
-      fm->spare->bytes = 0;
-    }
-  }
-  if (!fm->dev) {
-    fm->bytes = total;
-    if (!ctx_malloc(ctx, &fm->dev, total)) {
-      delete fm;
-      return SA_ENOMEM;
-    }
   }
   char* p = static_cast<char*>(fm->dev);
   fm->B = reinterpret_cast<u8*>(p);
@@ -767,19 +734,7 @@ sa_status sa_fm_info(const sa_fm* fm, uint64_t* n, uint64_t* dollar, uint32_t* s
 sa_status sa_fm_destroy(sa_fm* fm) {
   if (!fm) return SA_OK;
   (void)hipSetDevice(fm->device);
-  void* free_now = fm->dev;
-  // Whatever still reads the index, on any stream, ends first (as it would before its
-  // memory is freed).
-  if (fm->dev && fm->spare && fm->bytes <= kFmSpareMax &&
-      hipDeviceSynchronize() == hipSuccess) {
-    std::lock_guard<std::mutex> lk(fm->spare->mu);
-    if (fm->spare->bytes < fm->bytes) {
-      free_now = fm->spare->p;
-      fm->spare->p = fm->dev;
-      fm->spare->bytes = fm->bytes;
-    }
-  }
-  (void)hipFree(free_now);
+  (void)hipFree(fm->dev);
   delete fm;
   return SA_OK;
 }

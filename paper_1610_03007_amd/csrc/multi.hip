@@ -126,7 +126,11 @@ struct Engine {
     o_up_base = o_base, o_up_len = o_len, o_up_h = o_h, o_up_r0 = o_r0, o_up_nt = o_nt,
     o_up_no = o_no, o_up_nc = o_nc;
     o_up_start = L.o_start;
-    if (!ctx_malloc(c, &dev, bytes)) return SA_ENOMEM;
+    if (hipMalloc(&dev, bytes) != hipSuccess) {
+      dev = nullptr;
+      (void)hipGetLastError();
+      return SA_ENOMEM;
+    }
     if (hipMemset(dev, 0, bytes) != hipSuccess) return SA_EDEVICE;
     char* p = static_cast<char*>(dev);
     tab.base = reinterpret_cast<u64*>(p + o_base);
@@ -402,7 +406,7 @@ sa_status build_batch_impl(sa_ctx* c, const u8* text, const u64* h_off, u32 T, u
     (void)hipFree(c->act_ti);
     c->act_ti = nullptr;
     c->act_ti_cap = 0;
-    if (!dev_alloc(c, &c->act_ti, c->cap)) return SA_ENOMEM;
+    if (!dev_alloc(&c->act_ti, c->cap)) return SA_ENOMEM;
     c->act_ti_cap = c->cap;
   }
   Engine eng;
@@ -694,9 +698,9 @@ sa_status lane_create(std::unique_ptr<Lane>& out, int device, u64 capacity_bytes
   sa_ctx* c = L->ctx;
   st = ensure_workspace(c, L->arena_cap);
   if (st != SA_OK) return st;
-  if (!dev_alloc(c, &c->act_ti, c->cap)) return SA_ENOMEM;
+  if (!dev_alloc(&c->act_ti, c->cap)) return SA_ENOMEM;
   c->act_ti_cap = c->cap;
-  if (!dev_alloc(c, &L->d_text, L->arena_cap) || !dev_alloc(c, &L->d_sa, L->arena_cap))
+  if (!dev_alloc(&L->d_text, L->arena_cap) || !dev_alloc(&L->d_sa, L->arena_cap))
     return SA_ENOMEM;
   const u32 slots = 1u << idbits;
   st = L->eng.init(c, slots, idbits, B);

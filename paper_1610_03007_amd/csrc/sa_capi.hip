@@ -43,10 +43,10 @@ sa_status ensure_workspace(sa_ctx* c, u64 n) {
   if (n <= c->cap) return SA_OK;
   free_workspace(c);
   u64 cap = std::max<u64>(n, 1 << 16);
-  bool ok = dev_alloc(c, &c->keysA, cap) && dev_alloc(c, &c->keysB, cap) && dev_alloc(c, &c->valsA, cap) &&
-            dev_alloc(c, &c->valsB, cap) && dev_alloc(c, &c->isa, cap) &&
-            dev_alloc(c, &c->act_idx, 2 * cap) && dev_alloc(c, &c->live, ceil_div(cap, 32)) &&
-            dev_alloc(c, &c->status, sort_status_words(cap));
+  bool ok = dev_alloc(&c->keysA, cap) && dev_alloc(&c->keysB, cap) && dev_alloc(&c->valsA, cap) &&
+            dev_alloc(&c->valsB, cap) && dev_alloc(&c->isa, cap) && dev_alloc(&c->act_idx, 2 * cap) &&
+            dev_alloc(&c->live, ceil_div(cap, 32)) &&
+            dev_alloc(&c->status, sort_status_words(cap));
   if (!ok) {
     free_workspace(c);
     return SA_ENOMEM;
@@ -90,18 +90,6 @@ sa_status init_small(char* p) {
   return SA_OK;
 }
 
-bool ctx_malloc(sa_ctx* c, void** p, size_t bytes) {
-  if (hipMalloc(p, bytes) == hipSuccess) return true;
-  (void)hipGetLastError();
-  *p = nullptr;
-  if (!c->fm_spare) return false;
-  c->fm_spare->release();
-  if (hipMalloc(p, bytes) == hipSuccess) return true;
-  (void)hipGetLastError();
-  *p = nullptr;
-  return false;
-}
-
 void* level_buf(sa_ctx* c, u32 depth, u32 slot, size_t bytes) {
   const size_t k = size_t(depth) * kLevelSlots + slot;
   if (c->level_bufs.size() <= k) c->level_bufs.resize(k + 1, {nullptr, 0});
@@ -110,7 +98,10 @@ void* level_buf(sa_ctx* c, u32 depth, u32 slot, size_t bytes) {
   (void)hipFree(e.first);
   e = {nullptr, 0};
   void* p = nullptr;
-  if (!ctx_malloc(c, &p, bytes)) return nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
   e = {p, bytes};
   return p;
 }

@@ -124,7 +124,7 @@ sa_status ensure_pair_workspace(sa_ctx* c, u64 n) {
   free_pair_workspace(c);
   const u64 cap = std::max<u64>(n, 1 << 16);
   for (int j = 0; j < 3; ++j)
-    if (!dev_alloc(c, &c->pair_k[j], cap) || !dev_alloc(c, &c->pair_v[j], cap)) {
+    if (!dev_alloc(&c->pair_k[j], cap) || !dev_alloc(&c->pair_v[j], cap)) {
       free_pair_workspace(c);
       return SA_ENOMEM;
     }
