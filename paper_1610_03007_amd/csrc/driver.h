@@ -126,6 +126,7 @@ struct sa_ctx {
   // build looks its input up in the cache table (defaults when absent).
   bool tuning_explicit = false;
   sa_tuning explicit_tuning{};
+  const sa_tuning* tune_trial = nullptr;  // the candidate that sa_tune is timing
   TuneTable* tune = nullptr;
   std::string tune_path;
   std::string arch;         // architecture name without feature suffixes

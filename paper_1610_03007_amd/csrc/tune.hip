@@ -356,10 +356,15 @@ sa_tuning current_tuning(const sa_ctx* c) {
 
 u32 log2_floor(u64 n) { return n ? u32(63 - __builtin_clzll(n)) : 0; }
 
-// Chooses the knobs of the next build: the explicit tuning if the caller set
-// one, else the cache entry for this input, else the defaults.
+// Chooses the knobs of the next build: the tuner's candidate while it times one, the
+// explicit tuning if the caller set one, else the cache entry for this input, else the
+// defaults.
 void resolve_tuning(sa_ctx* c, const char* mode, u64 n, u32 code_bits) {
   c->tuned_from_cache = 0;
+  if (c->tune_trial) {
+    apply_tuning(c, *c->tune_trial);
+    return;
+  }
   if (c->tuning_explicit) {
     apply_tuning(c, c->explicit_tuning);
     return;
@@ -380,6 +385,11 @@ using namespace drv;
 
 namespace {
 
+// A candidate has to be this much faster than the best so far: where the split sort
+// takes every sort of a build, the sweeps' knobs change nothing, and chance would
+// choose among them for the inputs that do use them.
+constexpr double kTuneGain = 0.99;
+
 // Times one build with the context's current knobs: the best of `reps` runs
 // after one warm-up, in milliseconds on the stream's clock.
 sa_status time_build(sa_ctx* c, const u8* text, const u64* off, u32 T, u32* d_sa, hipStream_t s,
@@ -397,8 +407,7 @@ sa_status time_build(sa_ctx* c, const u8* text, const u64* off, u32 T, u32* d_sa
       st = SA_EDEVICE;
       break;
     }
-    st = T == 1 ? build_rounds(c, text, off[1], 0, d_sa, nullptr, s)
-                : build_batch_impl(c, text, off, T, d_sa, s);
+    st = build_batch_impl(c, text, off, T, d_sa, s);
     if (st != SA_OK) break;
     if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
       st = SA_EDEVICE;
@@ -437,11 +446,12 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
     if (!ctx->tune) return SA_ENOMEM;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // The search sets the knobs directly; the caller's explicit tuning and the
+  // A candidate is timed as a build that finds it in the cache runs (an explicit tuning
+  // would send every sort to the LSD sweeps); the caller's explicit tuning and the
   // statistics are put back afterwards.
   const bool was_explicit = ctx->tuning_explicit;
   const bool was_trace = ctx->trace;
-  ctx->tuning_explicit = true;
+  ctx->tuning_explicit = false;
   ctx->trace = false;
   sa_tuning best = default_tuning();
   double best_t = 0;
@@ -449,9 +459,10 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
   // SA_TUNE_LOG set in the environment: one line per candidate on stderr.
   const bool log = std::getenv("SA_TUNE_LOG") != nullptr;
   auto trial = [&](const sa_tuning& t) -> sa_status {
-    ctx->explicit_tuning = t;
     double ms = 0;
+    ctx->tune_trial = &t;
     sa_status e = time_build(ctx, d_texts, h_offsets, num_texts, d_sas, s, reps, &ms);
+    ctx->tune_trial = nullptr;
     if (e != SA_OK) return e;
     if (log) {
       std::fprintf(stderr,
@@ -461,12 +472,13 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
                    t.round0_full, t.lazy_ratio, ms);
       std::fflush(stderr);
     }
-    if (best_t == 0 || ms < best_t) {
+    if (best_t == 0 || ms < kTuneGain * best_t) {
       best_t = ms;
       best = t;
     }
     return SA_OK;
   };
+  st = trial(default_tuning());
   // Stage 1: tile shape and persistent grid of the radix sweeps (the default
   // grid first, then explicit workgroups per CU).
   struct Shape {
@@ -484,6 +496,8 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
       t.sort_wgs_per_cu = w;
       if (w != 0 && int(w) == default_wgs_per_cu(int(sh.items), int(sh.block), false, kRadixBits))
         continue;  // same as w = 0
+      if (w == 0 && sh.items == u32(kSortItemsDefault) && sh.block == u32(kSortBlockDefault))
+        continue;  // the defaults
       st = trial(t);
     }
   }
@@ -492,7 +506,7 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
   struct Width {
     u32 rb, items;
   };
-  const Width widths[] = {{6, 4}, {6, 8}, {6, 12}, {7, 4}, {7, 8}, {7, 12}, {9, 8}};
+  const Width widths[] = {{6, 8}, {6, 4}, {6, 12}, {7, 8}, {7, 4}, {7, 12}, {9, 8}};
   for (const Width& wd : widths) {
     if (st != SA_OK) break;
     sa_tuning t = best;
@@ -526,9 +540,10 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
   u32 code_bits = 0;
   if (st == SA_OK) {
     // One more build with the winner, for the code width of the entry.
-    ctx->explicit_tuning = best;
+    ctx->tune_trial = &best;
     double ms = 0;
     st = time_build(ctx, d_texts, h_offsets, num_texts, d_sas, s, 1, &ms);
+    ctx->tune_trial = nullptr;
     code_bits = num_texts == 1 ? ctx->info.code_bits : 0;
   }
   ctx->tuning_explicit = was_explicit;

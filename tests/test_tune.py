@@ -207,3 +207,37 @@ def test_digit_width_entries(tmp_path, rb, items):
     p = write(tmp_path, [entry(radix_bits=rb, sort_block=512, sort_items=items)])
     found, t = _native.tune_lookup(p, "gfx950", "single", 1 << 28, 7)
     assert found and t["radix_bits"] == rb and t["sort_items"] == items
+
+
+@pytest.mark.gpu
+def test_autotune_times_what_builds_run(tmp_path):
+    """The recorded time is that of a build which takes the entry (the split sort among
+    it, which an explicit tuning turns off), and the caller's explicit tuning, in force
+    while the tuner runs, is the same after it."""
+    import time
+
+    import torch
+
+    import workloads as W
+    from paper_1610_03007_amd import SuffixArrayBuilder
+
+    d = torch.from_numpy(W.dna(1 << 20, seed=78)).to("cuda:0")
+    b = SuffixArrayBuilder(0, tune_cache=str(tmp_path / "tune.json"))
+    try:
+        b.set_tuning(lazy_ratio=5, sort_items=12)
+        mine = b.tuning()
+        best, ms = b.tune(d, reps=5)
+        b.build(d)
+        assert b.tuning_source() == "explicit" and b.tuning() == mine
+        b.auto_tuning()
+        took = float("inf")
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            b.build(d, sigma=4)
+            torch.cuda.synchronize()
+            took = min(took, (time.perf_counter() - t0) * 1e3)
+        assert b.tuning_source() == "cache" and b.tuning() == best
+        assert ms < 1.3 * took, (ms, took)
+    finally:
+        b.close()
