@@ -294,10 +294,11 @@ sa_status sa_ctx_tuning_source(const sa_ctx* ctx, int* source);
  * build that finds it in the cache runs it, and records the fastest in the context's
  * cache table (a candidate has to gain 1%), keyed by (GPU architecture, mode,
  * floor(log2 of the total length), bits per character code of the input):
- *   stage 1: (sort_items, sort_block) in {8, 12, 16, 20, 24} x 256 and
+ *   stage 1: round0_full flipped;
+ *   stage 2: (sort_items, sort_block) in {8, 12, 16, 20, 24} x 256 and
  *            {4, 8, 12} x 512, x sort_wgs_per_cu in {default, 1, 2, 3, 4};
- *   stage 2: radix_bits in {6, 7, 9}; stage 3: sort_match 1 (the LDS table);
- *   stage 4: round0_full flipped; stage 5: lazy_ratio in {3, 4, 8, 16, 64}.
+ *   stage 3: radix_bits in {6, 7, 9}; stage 4: sort_match 1 (the LDS table);
+ *   stage 5: lazy_ratio in {3, 4, 8, 16, 64}.
  * Each candidate is one warm-up build plus the best of `reps` timed builds
  * (0 = 3) on `stream`, measured with HIP events. d_texts / h_offsets /
  * num_texts / d_sas are as sa_build_batch (num_texts = 1 tunes sa_build,

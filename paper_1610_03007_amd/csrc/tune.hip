@@ -479,7 +479,16 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
     return SA_OK;
   };
   st = trial(default_tuning());
-  // Stage 1: tile shape and persistent grid of the radix sweeps (the default
+  // Stage 1: round-0 key width. Before the digit width, which trims the keys to its own
+  // multiples: an input whose codes fit one of them would choose it over the full key,
+  // and inputs of another code width that find the entry would lose a character (7-bit
+  // codes: 9 characters either way; 8-bit codes: 8 in a full key, 7 in 9 digits of 7).
+  if (st == SA_OK) {
+    sa_tuning t = best;
+    t.round0_full = 1 - best.round0_full;
+    st = trial(t);
+  }
+  // Stage 2: tile shape and persistent grid of the radix sweeps (the default
   // grid first, then explicit workgroups per CU).
   struct Shape {
     u32 items, block;
@@ -490,7 +499,7 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
   for (const Shape& sh : shapes) {
     for (u32 w : wgs_set) {
       if (st != SA_OK) break;
-      sa_tuning t = default_tuning();
+      sa_tuning t = best;
       t.sort_items = sh.items;
       t.sort_block = sh.block;
       t.sort_wgs_per_cu = w;
@@ -501,7 +510,7 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
       st = trial(t);
     }
   }
-  // Stage 2: radix digit width (6, 7 and 9 bits run with 512-thread
+  // Stage 3: radix digit width (6, 7 and 9 bits run with 512-thread
   // workgroups and ballot matching) at the default grid.
   struct Width {
     u32 rb, items;
@@ -517,16 +526,11 @@ sa_status sa_tune(sa_ctx* ctx, const uint8_t* d_texts, const uint64_t* h_offsets
     t.sort_wgs_per_cu = 0;
     st = trial(t);
   }
-  // Stage 3: digit matching of the sweep (8-bit digits); stage 4: round-0 key
-  // width; stage 5: the lazy-ISA threshold.
+  // Stage 4: digit matching of the sweep (8-bit digits); stage 5: the lazy-ISA
+  // threshold.
   if (st == SA_OK && best.radix_bits == u32(kRadixBits)) {
     sa_tuning t = best;
     t.sort_match = 1;
-    st = trial(t);
-  }
-  if (st == SA_OK) {
-    sa_tuning t = best;
-    t.round0_full = 1 - best.round0_full;
     st = trial(t);
   }
   const u32 lazy_set[] = {3, 4, 16, 64};
