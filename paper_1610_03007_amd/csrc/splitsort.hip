@@ -6,18 +6,18 @@
 // pair for a round-0 key). Here the number of sweeps depends on the count only:
 //
 //   1. A stratified sample of the keys, sorted, gives F - 1 splitters (F a power
-//      of two, count / 1024 <= F, at most 2^20): bucket b holds the keys in
+//      of two, at most 2^20): bucket b holds the keys in
 //      (splitter[b - 1], splitter[b]]. Whatever the keys' distribution, a bucket
-//      holds about count / F pairs. A key that the sample holds several times
+//      holds about count / F pairs (at most 1024, 1280 above 2^30 pairs). A key that the sample holds several times
 //      fills several splitters; all its pairs go to the bucket that begins with
 //      the second of them, which holds nothing else (an equality bucket: it is
 //      sorted already, however large).
 //   2. Up to kSplitMaxD buckets: one sweep scatters the pairs into them. Above:
 //      F = D1 * D2, one sweep into D1 groups of D2 neighbouring buckets, one
 //      inside each group.
-//   3. Every bucket is sorted in LDS by one workgroup: again a sample (128 keys),
-//      a scatter into 128 parts of about eight pairs, and each pair's place in its
-//      part by counting the smaller keys.
+//   3. Every bucket is sorted in LDS by one workgroup: again a sample (a key per
+//      thread), a scatter into as many parts of about four pairs, and each pair's place
+//      in its part by counting the smaller keys.
 //
 // Measured on MI355X for the 2^28 round-0 keys of a Markov text (7 varying bytes):
 // 8.4 ms from the text to the SA and the survivors (sample 0.3, histograms 0.6 + 0.6,
@@ -29,7 +29,7 @@
 // keys (and inside a bucket before step 3) varies from run to run.
 //
 // A bucket that is no equality bucket and is larger than LDS holds
-// (kSplitCap pairs, nine times the largest mean) raises kCtrSplitOver: the keys
+// (kSplitCap pairs, seven times the largest mean) raises kCtrSplitOver: the keys
 // are then unsorted, the re-rank returns at once, and the host repeats the work
 // with the LSD sort. With `over` samples per bucket the size of a bucket follows
 // a Gamma(over) law; over = 12 (6 up to 1024 buckets, 4 where their mean is at
@@ -137,6 +137,7 @@ __device__ inline void flag(u64* counters, u64 bits) {
   atomicOr(reinterpret_cast<unsigned long long*>(counters + kCtrError), (unsigned long long)bits);
 }
 
+// The 32-bit integer hash "lowbias32" (Chris Wellons, hash-prospector).
 __device__ inline u32 mix32(u32 x) {
   x ^= x >> 16;
   x *= 0x7feb352du;
@@ -1133,7 +1134,7 @@ __device__ inline u32 run_head(const u64* s_key, u32 q, int sh, u64 k) {
 // Bound by memory (24 bytes a pair) as long as the LDS work (about 25 reads a
 // pair) and the waits between its steps stay below it: the next bucket's pairs
 // are requested as soon as this one's are in LDS, and a workgroup is small (two
-// waves and ten workgroups a CU for buckets of 512, four and five for 1024) so
+// waves and eight workgroups a CU for buckets of 512, four and four for 1024) so
 // that others work while one waits.
 // A bucket of more than CAP pairs goes to the list `big` for a launch of a larger
 // shape (which takes its buckets from there: `from`), or if there is no list raises
