@@ -172,8 +172,8 @@ constexpr int kSortItemsDefault = 8;
 constexpr int kSortTileMin = 2048;       // smallest tile (512 x 4); status arrays are sized for it
 constexpr int kHistBlock = 256;
 // Staged ISA writes of a re-rank over a large active set: (position, name) pairs
-// grouped by stretches of kStageSpan positions (in two steps above
-// kStageMaxDigits stretches), each stretch then filled in LDS and written in order.
+// grouped by stretches of kStageSpan positions (in two steps), each stretch then filled
+// in LDS and written in order.
 // A position has at most one pair, so the pairs of a stretch are given its own range
 // [first position, last position] of a buffer of n pairs and need no counting.
 constexpr int kStageShift = 14;

@@ -1755,12 +1755,10 @@ constexpr int kFillBlock = 512;
 __global__ __launch_bounds__(kFillBlock) void stage_fill_kernel(
     const u64* __restrict__ keysA, const u64* __restrict__ keysB,
     const SortPlan* __restrict__ plan, const SortCtl* __restrict__ ctl,
-    const u32* __restrict__ cur, int two_steps, const u64* __restrict__ counters, u64 n,
-    u32* __restrict__ isa) {
+    const u32* __restrict__ cur, const u64* __restrict__ counters, u64 n, u32* __restrict__ isa) {
   const u64 count = ctl->count;
   if (count < kStageMinCount || counters[kCtrSplitOver]) return;
-  const u32 fb = plan->final_buf;
-  const u64* in = (fb != 0) == (two_steps != 0) ? keysA : keysB;
+  const u64* in = plan->final_buf ? keysA : keysB;  // where the second step's pairs went
   __shared__ u32 s_isa[kStageSpan];
   const u32 tid = threadIdx.x;
   const u64 p0 = u64(blockIdx.x) * kStageSpan;
@@ -1796,23 +1794,19 @@ void launch_stage_isa(u64* keysA, u64* keysB, const SortPlan* plan, const SortCt
   // (A dense round ranks all n suffixes, whatever bound its launches have.)
   constexpr int kFirst = 1024, kSecond = 512;
   const u32 tiles = u32(ceil_div(n, kFirst * kStageItems));
-  const bool two = spans > kStageMaxDigits;
-  if (!two) {
-    hipLaunchKernelGGL((stage_group_kernel<true, kFirst>), dim3(tiles), dim3(kFirst), 0, s, keysA,
-                       keysB, plan, ctl, nullptr, 0, 0u, cur2, kStageShift, n, counters);
-  } else {
-    int shift = kStageShift;
-    while (ceil_div(n, u64(1) << shift) > kStageFirstDigits) ++shift;
-    const u32 parents = u32(ceil_div(n, u64(1) << shift));
-    const u32 per_parent = u32(ceil_div(u64(1) << shift, kSecond * kStageItems));
-    hipLaunchKernelGGL((stage_group_kernel<true, kFirst>), dim3(tiles), dim3(kFirst), 0, s, keysA,
-                       keysB, plan, ctl, nullptr, 0, 0u, cur, shift, n, counters);
-    hipLaunchKernelGGL((stage_group_kernel<false, kSecond>), dim3(parents * per_parent),
-                       dim3(kSecond), 0, s, keysA, keysB, plan, ctl, cur, shift, per_parent, cur2, kStageShift, n,
-                       counters);
-  }
+  // Two steps: a text that stages has more stretches than one can tell apart.
+  static_assert(kStageMinN / kStageSpan > kStageMaxDigits, "two steps");
+  int shift = kStageShift;
+  while (ceil_div(n, u64(1) << shift) > kStageFirstDigits) ++shift;
+  const u32 parents = u32(ceil_div(n, u64(1) << shift));
+  const u32 per_parent = u32(ceil_div(u64(1) << shift, kSecond * kStageItems));
+  hipLaunchKernelGGL((stage_group_kernel<true, kFirst>), dim3(tiles), dim3(kFirst), 0, s, keysA,
+                     keysB, plan, ctl, nullptr, 0, 0u, cur, shift, n, counters);
+  hipLaunchKernelGGL((stage_group_kernel<false, kSecond>), dim3(parents * per_parent),
+                     dim3(kSecond), 0, s, keysA, keysB, plan, ctl, cur, shift, per_parent, cur2,
+                     kStageShift, n, counters);
   hipLaunchKernelGGL(stage_fill_kernel, dim3(spans), dim3(kFillBlock), 0, s, keysA, keysB, plan,
-                     ctl, cur2, two ? 1 : 0, counters, n, isa);
+                     ctl, cur2, counters, n, isa);
 }
 
 // ---------------------------------------------------------------------------

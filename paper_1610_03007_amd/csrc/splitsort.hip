@@ -49,7 +49,9 @@ constexpr int kSplitMaxLogD = 10;
 constexpr u32 kSplitMaxD = 1u << kSplitMaxLogD;
 constexpr u32 kSplitOne = 4608;       // pairs of an input sorted as one bucket
 constexpr u32 kSplitCap = 9216;       // pairs of a bucket sorted in LDS at most
-constexpr u32 kSplitRankMax = 8192;   // samples sorted by counting
+constexpr u32 kSplitRankMax = 8192;   // samples sorted by counting at most
+constexpr u32 kSplitOverOne = 6;      // samples per bucket of one sweep at most
+static_assert((kSplitOverOne << kSplitMaxLogD) <= kSplitRankMax, "one sweep's samples");
 constexpr u32 kSplitXcds = 8;
 // Pairs per thread of a sweep over a large input: two workgroups a CU with 1024
 // buckets. (8 and 10 give three and two, and 2-5% longer builds: shorter runs.)
@@ -556,9 +558,10 @@ __global__ __launch_bounds__(256) void split_sample_kernel(const u64* __restrict
 // Sorts up to kSplitRankMax samples by counting, for each, the smaller ones
 // (ties by index): 16 samples per workgroup, each counted by 32 threads that
 // read neighbouring samples, so that 8192 samples occupy every CU.
-// over != 0 (an input of one sweep): every over-th sorted sample is a splitter of
-// the f buckets, written to `out` by itself (and the last, all ones); the lists of
-// larger buckets start empty and `present`, if any, is cleared for the next build.
+// Every over-th sorted sample is a splitter of the f buckets, written to `out` by
+// itself (and the last, all ones); the lists of larger buckets start empty and
+// `present`, if any, is cleared for the next build. (So many samples at most only an
+// input of one sweep has: two sweeps take 12 for each of 2048 buckets or more.)
 __global__ __launch_bounds__(kSplitBlock) void split_rank_kernel(
     const u64* __restrict__ in, u32 samples, u64* __restrict__ out, u32 over, u32 f,
     u32* __restrict__ big, u32* __restrict__ big2, u32* __restrict__ present) {
@@ -584,12 +587,9 @@ __global__ __launch_bounds__(kSplitBlock) void split_rank_kernel(
   __syncthreads();
   if (p == 0 && i < samples) {
     const u32 r = s_r[threadIdx.x];
-    if (!over)
-      out[r] = s_k[i];
-    else if (r > 0 && r % over == 0 && r / over < f)
-      out[r / over - 1] = s_k[i];
+    if (r > 0 && r % over == 0 && r / over < f) out[r / over - 1] = s_k[i];
   }
-  if (over && blockIdx.x == 0) {
+  if (blockIdx.x == 0) {
     if (threadIdx.x == 0) {
       out[f - 1] = ~u64(0);
       big[0] = big2[0] = 0;
@@ -726,7 +726,6 @@ __device__ inline SplitTile split_tile2(const SplitArrays& A, u32 d1, u32 tile, 
   t.base = t.out0 + k * tile;
   const u32 left = k * tile < size ? size - k * tile : 0;
   t.n = left < tile ? left : tile;
-  if (t.n == 0 && !t.first) t.first = false;
   return t;
 }
 
@@ -1691,7 +1690,7 @@ SplitShape split_shape(u64 count) {
     S.log2 = std::min(kSplitMaxLogD, lf - 3);
     S.log1 = lf - S.log2;
   }
-  S.over = lf > kSplitMaxLogD ? 12 : count > (u64(512) << lf) ? 6 : 4;
+  S.over = lf > kSplitMaxLogD ? 12 : count > (u64(512) << lf) ? kSplitOverOne : 4;
   S.samples = S.over << lf;
   // Small inputs: small tiles, so that more CUs take part.
   S.tile = count < (u64(1) << 22) ? 4 * kSplitBlock : kSweepItems * kSplitBlock;
@@ -1824,24 +1823,19 @@ static sa_status split_run(sa_ctx* c, const Bufs& bf, u64 count, const SplitText
       else
         hipLaunchKernelGGL(split_sample_kernel, dim3(u32(ceil_div(S.samples, 256))), dim3(256), 0,
                            s, bf.kA, T, S.count, S.samples, sk);
-      u64* sorted = sk2;
-      if (S.samples <= kSplitRankMax) {
-        const bool direct = S.log2 == 0;
+      if (!S.log2) {
         hipLaunchKernelGGL(split_rank_kernel, dim3(u32(ceil_div(S.samples, 16))),
-                           dim3(kSplitBlock), 0, s, sk, S.samples, direct ? A.splitters : sk2,
-                           direct ? S.over : 0u, S.nb(), A.big, A.big2,
-                           small_text ? c->present : nullptr);
+                           dim3(kSplitBlock), 0, s, sk, S.samples, A.splitters, S.over, S.nb(),
+                           A.big, A.big2, small_text ? c->present : nullptr);
       } else {
         u32 sf = 0;
         const Bufs sb{sk, sk2, nullptr, nullptr};
         const sa_status st = split_run(c, sb, S.samples, SplitText{}, SplitFinal{}, 0, cv, false, 0,
                                        0, &sf, s);
         if (st != SA_OK) return st;
-        sorted = sf ? sk2 : sk;
-      }
-      if (S.log2)
         hipLaunchKernelGGL(split_pick_kernel, dim3(u32(ceil_div(S.nb(), 256))), dim3(256), 0, s,
-                         sorted, S.log1, S.log2, S.over, S.samples, A);
+                           sf ? sk2 : sk, S.log1, S.log2, S.over, S.samples, A);
+      }
     }
     const bool small = S.tile == 4 * kSplitBlock;
     const u32 hgrid = S.groups * std::min<u32>(S.per, 4096 / S.groups);
@@ -1969,7 +1963,7 @@ bool split_usable(const sa_ctx* c, u64 count) {
       cv.get<u64>(S.samples);
     }
     need += ~size_t(0) - cv.left;
-    if (S.log1 == 0 || S.samples <= kSplitRankMax) break;
+    if (S.log2 == 0) break;
     n = S.samples;
   }
   return need <= size_t(c->cap) * 4;
