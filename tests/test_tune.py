@@ -241,3 +241,42 @@ def test_autotune_times_what_builds_run(tmp_path):
         assert ms < 1.3 * took, (ms, took)
     finally:
         b.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("knobs", [{"prefix_mult": 4}, {"radix_bits": 6, "sort_items": 12},
+                                   {"radix_bits": 7, "round0_full": 1}, {"radix_bits": 9},
+                                   {"lazy_ratio": 3}, {"lazy_ratio": 64, "sort_match": 1}])
+def test_builds_from_cache_entries(tmp_path, knobs):
+    """Builds that find an entry (the split sort runs, unlike with an explicit tuning)
+    with each knob that still matters to them: the oracle's arrays, in one bucket, one
+    sweep and two, with later rounds, and in a batch."""
+    import torch
+
+    import oracle
+    import workloads as W
+    from paper_1610_03007_amd import SuffixArrayBuilder
+
+    base = dict(sort_block=512, sort_items=8, code_bits=0)
+    path = write(tmp_path, [entry(**{**base, "mode": m, "log2n": k, **knobs})
+                            for m in ("single", "batch") for k in (12, 16, 20, 24)])
+    b = SuffixArrayBuilder(0, tune_cache=path)
+    rng = np.random.default_rng(12)
+    try:
+        for n in (3000, 70001, 3000001):
+            planted = rng.integers(0, 200, n).astype(np.uint8)
+            planted[n // 2:n // 2 + n // 3] = planted[:n // 3]
+            for t in (W.dna(n, seed=n), planted, np.tile(planted[:n // 50], 51)[:n]):
+                sa = b.build(torch.from_numpy(t.copy()).to("cuda:0"))
+                torch.cuda.synchronize()
+                assert b.tuning_source() == "cache"
+                assert all(b.tuning()[k] == v for k, v in knobs.items())
+                want = oracle.sa(t, parallel=True)
+                assert np.array_equal(sa.cpu().numpy().view(np.uint32), want), n
+            off = [0, n // 5, n // 5, n // 2, n]
+            sa = b.build_batch(torch.from_numpy(planted).to("cuda:0"), off)
+            sa = sa.cpu().numpy().view(np.uint32)
+            for a, z in zip(off[:-1], off[1:]):
+                assert np.array_equal(sa[a:z], oracle.sa(planted[a:z], parallel=True))
+    finally:
+        b.close()
