@@ -157,7 +157,11 @@ sa_status build_sortpair(sa_ctx* c, const u8* text, u64 n, u32* d_sa, u64* h_cou
   {
     Tracer t(c, s, SA_KERNEL_OTHER, double(n));
     launch_byte_presence(text, n, c->present, s);
-    launch_alphabet_codes(c->present, c->code, c->counters, c->round0_trim, 0, c->radix_bits, s);
+    // A cache entry's full keys (round0_full) are for the split sort of sa_build, which has
+    // no digits. These sorts are LSD: a character that half-fills a digit costs a sweep
+    // (2^28 Markov bytes: 34.0 ms with 9 characters, 32.8 with 8).
+    const int trim = c->tuning_explicit ? c->round0_trim : 1;
+    launch_alphabet_codes(c->present, c->code, c->counters, trim, 0, c->radix_bits, s);
     // (Builds of short texts expect it clear.)
     launch_fill_u64(reinterpret_cast<u64*>(c->present), 256 / 2, 0, s);
   }

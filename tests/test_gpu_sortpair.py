@@ -121,3 +121,23 @@ def test_two_mib_markov_and_dna(builder):
     for t in (W.markov3(1 << 21, chain_seed=21), W.dna(1 << 21, seed=21)):
         info, counts = check(builder, t, parallel=True)
         print(f"n={t.size} rounds={info['rounds']} counts={counts.tolist()}", flush=True)
+
+
+def test_cache_entry_of_full_keys(tmp_path):
+    """A cache entry's full round-0 keys are those of sa_build; the LSD sorts here keep
+    whole digits unless an explicit tuning asks for full keys."""
+    import json
+
+    from paper_1610_03007_amd import SuffixArrayBuilder
+    entry = {"arch": "gfx950", "mode": "single", "log2n": 16, "code_bits": 0, "sort_items": 8,
+             "sort_block": 512, "sort_wgs_per_cu": 0, "lazy_ratio": 8, "round0_full": 1, "ms": 1.0}
+    path = tmp_path / "tune.json"
+    path.write_text(json.dumps({"format": "sa_mi355x_tune/1", "entries": [entry]}))
+    b = SuffixArrayBuilder(0, tune_cache=str(path))
+    t = W.markov3(70001, chain_seed=5)  # 7-bit codes
+    b.build(dev(t))
+    assert b.tuning_source() == "cache" and b.last_info()["chars0"] == 9
+    assert check(b, t)[0]["chars0"] == 8
+    b.set_tuning(round0_full=1)
+    assert check(b, t)[0]["chars0"] == 9
+    b.close()
