@@ -51,7 +51,9 @@ BUILD_ORDER = ("batch_4096", "repetitive_1g", "markov_256m", "dna_1m")
 SERVE_RATE = 330.5
 SERVE_LO, SERVE_HI = 1024, 1 << 26
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1610_03007_amd", "csrc", "sa_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_1610_03007_amd", "csrc")
+LSD_KERNEL = "onesweep_pass_kernel"
+SPLIT_KERNELS = "split_sweep_kernel + split_local_kernel"
 
 # Bounded CPU-oracle samples (bytes): (one thread, all cores).
 CPU_SAMPLES = {
@@ -80,28 +82,34 @@ def make_text(name: str):
     raise SystemExit(f"unknown workload {name}")
 
 
-def kernel_source_hash() -> str:
-    """sha256[:16] of the sort sweep's source: common.h, sa_kernels.hip from its
-    top through the helper namespace (digit extraction, scans, look-back), and
-    the sweep kernel from its leading comment to onesweep_supported."""
-    with open(KERNEL_SOURCE) as f:
-        src = f.read()
-    with open(os.path.join(os.path.dirname(KERNEL_SOURCE), "common.h")) as f:
-        common = f.read()
-    head = src[:src.index("}  // namespace")]
-    sweep = src[src.index("// One stable counting sweep over digit"):src.index("bool onesweep_supported(")]
-    return hashlib.sha256((common + head + sweep).encode()).hexdigest()[:16]
+def kernel_source_hash(kernel: str) -> str:
+    """sha256[:16] of the source of the kernels that move a sort's pairs: common.h and,
+    for the split sort, splitsort.hip up to its host code; for the LSD sweep,
+    sa_kernels.hip from its top through the helper namespace (digit extraction, scans,
+    look-back) and the sweep from its leading comment to onesweep_supported."""
+    def text(name):
+        with open(os.path.join(CSRC, name)) as f:
+            return f.read()
+    if kernel == SPLIT_KERNELS:
+        src = text("splitsort.hip")
+        body = src[:src.index("namespace drv {")]
+    else:
+        src = text("sa_kernels.hip")
+        body = src[:src.index("}  // namespace")] + src[
+            src.index("// One stable counting sweep over digit"):src.index("bool onesweep_supported(")]
+    return hashlib.sha256((text("common.h") + body).encode()).hexdigest()[:16]
 
 
-def measured_traffic(workload: str):
-    """HBM bytes per sort-sweep launch from committed rocprofv3 counter runs,
-    or None when absent or taken on a different kernel source."""
+def measured_traffic(workload: str, kernel: str):
+    """HBM bytes per launch of a build's sorts (the launches of the `sort_pass` row) from
+    committed rocprofv3 counter runs, or None when absent or taken on a different kernel
+    source."""
     try:
         with open(TRAFFIC_FILE) as f:
-            rec = json.load(f).get(workload)
+            rec = json.load(f).get(workload, {}).get(kernel)
     except (OSError, ValueError):
         return None
-    if not rec or rec.get("kernel_source_sha") != kernel_source_hash():
+    if not rec or rec.get("kernel_source_sha") != kernel_source_hash(kernel):
         return None
     return rec.get("bytes_per_launch")
 
@@ -114,8 +122,8 @@ SPLIT_MAX = 1280 << 20
 def sort_kernels(explicit: bool, n: int, batch: bool) -> str:
     """Names of the kernels that move the pairs of a build's sorts."""
     if explicit or (n > SPLIT_MAX and not batch):
-        return "onesweep_pass_kernel"
-    return "split_sweep_kernel + split_local_kernel"
+        return LSD_KERNEL
+    return SPLIT_KERNELS
 
 
 def algorithmic_bytes(stats: dict, steps: int) -> float:
@@ -265,7 +273,7 @@ def run_build(name: str, steps: int, warmup: int, cpu: bool, sort_items: int = 0
         "sweep_roofline": {
             "bound": "hbm", "kernel": kernel, "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": measured_traffic(name) if kernel == "onesweep_pass_kernel" else None,
+            "traffic": measured_traffic(name, kernel),
             "algorithmic_bytes_per_launch": round(sweep["bytes"] / max(1, sweep["launches"])),
             "launches": sweep["launches"],
             "avg_launch_us": round(sweep["ms"] * 1e3 / max(1, sweep["launches"]), 2)},
